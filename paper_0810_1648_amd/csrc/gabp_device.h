@@ -97,6 +97,15 @@ template <int N> __device__ inline void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
+// Device-scope accesses of values that workgroups of one launch hand to each
+// other: written through to, and read from, where every XCD sees them.
+template <class T> __device__ inline void store_agent(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T> __device__ inline T load_agent(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Address of a lane's element from a wave-uniform base (scalar registers)
 // and a 32-bit lane offset: loads and stores then take the scalar-base form
 // and the per-step address arithmetic stays off the vector ALU.

@@ -20,6 +20,7 @@ namespace gabp {
 constexpr int TILE = 256;
 constexpr int TT = TILE * TILE;
 constexpr int WG = 256;               // threads per workgroup (4 wave64)
+constexpr int FB = 64;                // nodes per finalize workgroup
 
 enum Prec : int { PREC_FP64 = 0, PREC_FP32 = 1, PREC_MIXED = 2 };
 enum GramKind : int { GRAM_F32 = 0, GRAM_BF16 = 1, GRAM_BF16X3 = 2, GRAM_F64 = 3, GRAM_BF16X6 = 4 };
@@ -36,6 +37,7 @@ struct DevStatus {
     int32_t since_best;  // sweeps since the smallest change so far
     int32_t bad;         // set when a cavity precision <= 0 or a value is not finite
     int32_t g;           // served grouped schedule: the group the next step visits
+    uint32_t ticket;     // finalize workgroups of the running sweep that have written their maxima
     double delta;        // ||alpha^t - alpha^(t-1)||_inf
     double amax;         // ||alpha^t||_inf
     double best_delta;
@@ -242,14 +244,29 @@ hipError_t launch_sweep_mixed(int ksrc, int gram, int levels, bool first, int se
                               hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_sweep_f64(int ksrc, int gram, int levels, bool first, int ser, const SweepArgs& a,
                             hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+// Arguments of one finalize launch: the new aggregates of the nodes
+// [b0 FB, N) (b1 > 0: of the 256-node blocks [b0, b1)) from the partial sums.
 // Inv / Mean (optional, with Pt / S): the new 1/P~ and S/P~ of the series
 // sweeps, formed once per node here instead of in every tile.  part32: the
-// partial sums are FP32 (SweepArgs::part32).
-hipError_t launch_finalize(int prec, int64_t N, int NB, const void* partP, const void* partE,
-                           const double* Adiag, const float* y, void* Pt, void* S,
-                           double* alpha, double* blk_delta, double* blk_amax,
-                           DevStatus* st, hipStream_t s, double boxC = 0.0, void* Inv = nullptr,
-                           void* Mean = nullptr, int part32 = 0);
+// partial sums are FP32 (SweepArgs::part32).  trace: the last workgroup to
+// finish applies the stop rule to the sweep (null: no stop rule, as after the
+// visits of all groups but the last).
+struct FinalizeArgs {
+    int64_t N;
+    int NB;                       // slots per block - 1
+    const void *partP, *partE;
+    const double* Adiag;
+    const float* y;
+    void *Pt, *S, *Inv, *Mean;
+    double *alpha, *blk_delta, *blk_amax;
+    DevStatus* st;
+    double boxC;
+    int part32;
+    int64_t b0, b1;               // 256-node blocks (b1 = 0: all)
+    double* trace;
+    StopRule rule;
+};
+hipError_t launch_finalize(int prec, const FinalizeArgs& f, hipStream_t s);
 // Inv / Mean of every ring slot from Pt / S (R slots of NPAD entries).
 hipError_t launch_ring_recip(int prec, int64_t NPAD, int R, const void* Pt, const void* S, void* Inv, void* Mean,
                              hipStream_t s);
@@ -318,14 +335,6 @@ hipError_t launch_sp_sweep(int prec, int64_t E, int64_t N, const int32_t* ei, co
                            const void* Pt, const void* S, void* PS, void* RF, void* RB, const int64_t* off_i,
                            const int64_t* off_j, const int32_t* perm, void* partP, void* partE, DevStatus* st,
                            hipStream_t s);
-// Finalize of the node blocks [b0, b0 + nb) only (the group just visited).
-hipError_t launch_finalize_range(int prec, int64_t b0, int64_t nb, int64_t N, int NB, const void* partP,
-                                 const void* partE, const double* Adiag, const float* y, void* Pt, void* S,
-                                 double* alpha, double* blk_delta, double* blk_amax, DevStatus* st,
-                                 hipStream_t s, double boxC = 0.0, void* Inv = nullptr, void* Mean = nullptr,
-                                 int part32 = 0);
-hipError_t launch_status(int nblk, const double* blk_delta, const double* blk_amax,
-                         DevStatus* st, double* trace, StopRule rule, hipStream_t s);
 // A-priori contraction bound: one[0] = -m* (minus the aggregate lower
 // bound), one[1] = rho (+inf when no bound exists).
 hipError_t launch_rho_bound(int64_t N, const double* Adiag, const double* rowmax, const double* rsum,

@@ -591,7 +591,7 @@ __global__ void k_diag_shift(int64_t N, const double* __restrict__ kdiag,
 
 __global__ void k_reset_status(DevStatus* st) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        st->t = 0; st->done = 0; st->reason = R_NONE; st->since_best = 0; st->bad = 0; st->g = 0;
+        st->t = 0; st->done = 0; st->reason = R_NONE; st->since_best = 0; st->bad = 0; st->g = 0; st->ticket = 0;
         st->delta = 0.0; st->amax = 0.0; st->best_delta = INFINITY;
     }
 }
@@ -634,136 +634,16 @@ __global__ void k_init(int64_t N, int64_t NPAD, int R, const double* __restrict_
     }
 }
 
-// Aggregates of the new sweep from the partial sums (fixed order) into ring
-// slot `wslot`, the new alpha and the per-block change / magnitude maxima.
-// boxC > 0: the belief mean is clipped to [0, boxC] (alpha space) and S is
-// replaced by P~ times the clipped mean.
-template <class AT, class PT>
-__device__ inline void finalize_block(int64_t blk, int64_t N, int NB, const PT* __restrict__ partP,
-                                      const PT* __restrict__ partE,
-                                      const double* __restrict__ Adiag,
-                                      const float* __restrict__ y, AT* __restrict__ Pt,
-                                      AT* __restrict__ S, double* __restrict__ alpha,
-                                      double* __restrict__ blk_delta,
-                                      double* __restrict__ blk_amax, DevStatus* st, double boxC,
-                                      AT* __restrict__ Inv, AT* __restrict__ Mean) {
-    __shared__ double sh4[4];
-    __shared__ AT shp[4][TILE], she[4][TILE];
-    // the NB + 1 partial slots of the block, split into four contiguous
-    // ranges, one per wave; each lane sums four nodes (64 apart) over its
-    // wave's range, so every wave keeps eight independent loads in flight
-    {
-        const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-        const int S1 = NB + 1, qn = (S1 + 3) / 4;
-        const int s0 = w * qn, s1 = (s0 + qn < S1) ? s0 + qn : S1;
-        AT ap[4] = {0, 0, 0, 0}, ae[4] = {0, 0, 0, 0};
-        for (int s = s0; s < s1; ++s) {
-            const size_t o = ((size_t)blk * S1 + s) * TILE + l;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) { ap[k] += (AT)partP[o + 64 * k]; ae[k] += (AT)partE[o + 64 * k]; }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) { shp[w][l + 64 * k] = ap[k]; she[w][l + 64 * k] = ae[k]; }
-    }
-    __syncthreads();
-    const int64_t i = blk * blockDim.x + threadIdx.x;
-    double d = 0.0, am = 0.0;
-    bool bad = false;
-    if (i < N) {
-        const int t = threadIdx.x;
-        AT p = (AT)Adiag[i] + ((shp[0][t] + shp[1][t]) + (shp[2][t] + shp[3][t]));
-        AT e = (AT)y[i] + ((she[0][t] + she[1][t]) + (she[2][t] + she[3][t]));
-        double an = (double)(e / p) * (double)y[i];
-        bad = !(p > (AT)0) || !isfinite((double)p) || !isfinite((double)e);
-        if (boxC > 0.0) {
-            an = fmin(fmax(an, 0.0), boxC);
-            e = p * (AT)(an * (double)y[i]);
-        }
-        Pt[i] = p;
-        S[i] = e;
-        if (Inv) { Inv[i] = (AT)1 / p; Mean[i] = e / p; }
-        d = fabs(an - alpha[i]);
-        am = fabs(an);
-        alpha[i] = an;
-    }
-    if (__any(bad) && (threadIdx.x & 63) == 0) st->bad = 1;
-    d = block_max(d, sh4);
-    am = block_max(am, sh4);
-    if (threadIdx.x == 0) { blk_delta[blk] = d; blk_amax[blk] = am; }
-}
-
-template <class AT, class PT>
-__global__ __launch_bounds__(WG) void k_finalize(int64_t N, int NB, const PT* __restrict__ partP,
-                                                const PT* __restrict__ partE,
-                                                const double* __restrict__ Adiag,
-                                                const float* __restrict__ y, AT* __restrict__ Pt,
-                                                AT* __restrict__ S, double* __restrict__ alpha,
-                                                double* __restrict__ blk_delta,
-                                                double* __restrict__ blk_amax, DevStatus* st, double boxC,
-                                                AT* __restrict__ Inv, AT* __restrict__ Mean) {
-    if (st->done) return;
-    finalize_block<AT, PT>(blockIdx.x, N, NB, partP, partE, Adiag, y, Pt, S, alpha, blk_delta, blk_amax, st, boxC,
-                           Inv, Mean);
-}
-
-// 1/P~ and S/P~ of every ring slot (series sweeps): P~ = +inf, S = 0 give 0
-// and 0, the values a tile would form from them.
-template <class AT>
-__global__ void k_ring_recip(int64_t n, const AT* __restrict__ Pt, const AT* __restrict__ S,
-                             AT* __restrict__ Inv, AT* __restrict__ Mean) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    Inv[i] = (AT)1 / Pt[i];
-    Mean[i] = S[i] / Pt[i];
-}
-
-// Grouped schedule: the node blocks [b0, b0 + gridDim.x) of one group.
-template <class AT, class PT>
-__global__ __launch_bounds__(WG) void k_finalize_range(int64_t b0, int64_t N, int NB, const PT* __restrict__ partP,
-                                                      const PT* __restrict__ partE,
-                                                      const double* __restrict__ Adiag,
-                                                      const float* __restrict__ y, AT* __restrict__ Pt,
-                                                      AT* __restrict__ S, double* __restrict__ alpha,
-                                                      double* __restrict__ blk_delta,
-                                                      double* __restrict__ blk_amax, DevStatus* st, double boxC,
-                                                      AT* __restrict__ Inv, AT* __restrict__ Mean) {
-    if (st->done) return;
-    finalize_block<AT, PT>(b0 + blockIdx.x, N, NB, partP, partE, Adiag, y, Pt, S, alpha, blk_delta, blk_amax, st,
-                           boxC, Inv, Mean);
-}
-
-// Served form: items are (request, block of 256 nodes).
-template <class AT>
-__global__ __launch_bounds__(WG) void k_finalize_batched(const ReqDesc* __restrict__ reqs,
-                                                        const uint2* __restrict__ items, int nitems) {
-    for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-        const uint2 w = items[it];
-        const ReqDesc& rd = reqs[w.x];
-        if (rd.sw.st->done) continue;
-        const int64_t wslot = (int64_t)((rd.sw.st->t + 1) % rd.sw.R) * rd.sw.NPAD;
-        AT* const Pt = static_cast<AT*>(const_cast<void*>(rd.sw.HP)) + wslot;
-        AT* const S = static_cast<AT*>(const_cast<void*>(rd.sw.HS)) + wslot;
-        // slots per block: NB + 1, or NBc + 1 after a sweep over chunks
-        const int ns = (rd.sw.chunk > 1) ? (rd.sw.NB + rd.sw.chunk - 1) / rd.sw.chunk : rd.sw.NB;
-        if (rd.sw.part32)
-            finalize_block<AT, float>((int64_t)w.y, rd.N, ns, static_cast<const float*>(rd.sw.partP),
-                                      static_cast<const float*>(rd.sw.partE), rd.Adiag, rd.y, Pt, S, rd.alpha,
-                                      rd.blk_delta, rd.blk_amax, rd.sw.st, 0.0, nullptr, nullptr);
-        else
-            finalize_block<AT, AT>((int64_t)w.y, rd.N, ns, static_cast<const AT*>(rd.sw.partP),
-                                   static_cast<const AT*>(rd.sw.partE), rd.Adiag, rd.y, Pt, S, rd.alpha,
-                                   rd.blk_delta, rd.blk_amax, rd.sw.st, 0.0, nullptr, nullptr);
-        __syncthreads();
-    }
-}
-
 // Stop rule (Algorithm 2 step "Check", tested on alpha).
 __device__ inline void status_update(int nblk, const double* __restrict__ bd,
                                      const double* __restrict__ ba, DevStatus* st,
                                      double* __restrict__ trace, const StopRule& rule) {
     __shared__ double sh4[4];
     double d = 0.0, a = 0.0;
-    for (int k = threadIdx.x; k < nblk; k += blockDim.x) { d = fmax(d, bd[k]); a = fmax(a, ba[k]); }
+    for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
+        d = fmax(d, load_agent(bd + k));
+        a = fmax(a, load_agent(ba + k));
+    }
     d = block_max(d, sh4);
     a = block_max(a, sh4);
     if (threadIdx.x == 0) {
@@ -772,7 +652,7 @@ __device__ inline void status_update(int nblk, const double* __restrict__ bd,
         st->delta = d;
         st->amax = a;
         trace[t - 1] = d;
-        if (st->bad) {
+        if (load_agent(&st->bad)) {
             st->done = 1; st->reason = R_DIVERGED;
         } else if (d <= rule.tol_abs + rule.tol_rel * a) {
             st->done = 1; st->reason = R_CONVERGED;
@@ -788,16 +668,145 @@ __device__ inline void status_update(int nblk, const double* __restrict__ bd,
     }
 }
 
-__global__ __launch_bounds__(WG) void k_status(int nblk, const double* __restrict__ bd,
-                                              const double* __restrict__ ba, DevStatus* st,
-                                              double* __restrict__ trace, StopRule rule) {
-    if (st->done) return;
-    status_update(nblk, bd, ba, st, trace, rule);
+// Aggregates of the FB nodes of finalize block `blk` from the partial sums
+// (fixed order), the new alpha and the block's change / magnitude maxima.
+// boxC > 0: the belief mean is clipped to [0, boxC] (alpha space) and S is
+// replaced by P~ times the clipped mean.  The block's slots are split into
+// four contiguous ranges, one per wave, a lane adding one node over its
+// wave's range, eight slots' loads in flight (the additions keep the slot
+// order); wave 0 adds the four parts and forms the node.  The reads of the
+// partials are a short latency chain, so the node range is spread over as
+// many workgroups as it has waves: with 256 nodes per workgroup and one slot
+// in flight a 158-slot group visit took 17.8 us and an 80-slot sweep 10.6 us.
+template <class AT, class PT>
+__device__ inline void finalize_block(int64_t blk, int64_t N, int NB, const PT* __restrict__ partP,
+                                      const PT* __restrict__ partE,
+                                      const double* __restrict__ Adiag,
+                                      const float* __restrict__ y, AT* __restrict__ Pt,
+                                      AT* __restrict__ S, double* __restrict__ alpha,
+                                      double* __restrict__ blk_delta,
+                                      double* __restrict__ blk_amax, DevStatus* st, double boxC,
+                                      AT* __restrict__ Inv, AT* __restrict__ Mean) {
+    __shared__ AT shp[4][FB], she[4][FB];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int64_t i = blk * FB + l;
+    {
+        const int S1 = NB + 1, qn = (S1 + 3) / 4;
+        const int s0 = w * qn, s1 = (s0 + qn < S1) ? s0 + qn : S1;
+        const size_t o = (size_t)(i / TILE) * S1 * TILE + (size_t)(i % TILE);
+        const PT* pp = partP + o;
+        const PT* pe = partE + o;
+        AT ap = 0, ae = 0;
+        int s = s0;
+        for (; s + 8 <= s1; s += 8) {
+            PT vp[8], ve[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { vp[k] = pp[(size_t)(s + k) * TILE]; ve[k] = pe[(size_t)(s + k) * TILE]; }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { ap += (AT)vp[k]; ae += (AT)ve[k]; }
+        }
+        for (; s < s1; ++s) { ap += (AT)pp[(size_t)s * TILE]; ae += (AT)pe[(size_t)s * TILE]; }
+        shp[w][l] = ap;
+        she[w][l] = ae;
+    }
+    __syncthreads();
+    if (w != 0) return;
+    double d = 0.0, am = 0.0;
+    bool bad = false;
+    if (i < N) {
+        AT p = (AT)Adiag[i] + ((shp[0][l] + shp[1][l]) + (shp[2][l] + shp[3][l]));
+        AT e = (AT)y[i] + ((she[0][l] + she[1][l]) + (she[2][l] + she[3][l]));
+        double an = (double)(e / p) * (double)y[i];
+        bad = !(p > (AT)0) || !isfinite((double)p) || !isfinite((double)e);
+        if (boxC > 0.0) {
+            an = fmin(fmax(an, 0.0), boxC);
+            e = p * (AT)(an * (double)y[i]);
+        }
+        Pt[i] = p;
+        S[i] = e;
+        if (Inv) { Inv[i] = (AT)1 / p; Mean[i] = e / p; }
+        d = fabs(an - alpha[i]);
+        am = fabs(an);
+        alpha[i] = an;
+    }
+    if (__any(bad) && l == 0) store_agent(&st->bad, 1);
+    d = wave_max(d);
+    am = wave_max(am);
+    if (l == 0) { store_agent(blk_delta + blk, d); store_agent(blk_amax + blk, am); }
 }
 
-// Served form: one workgroup per active request; also copies the request's
-// status into a packed array the host reads back in one transfer.
-// Stop rule of served requests: a step visits one group of a grouped
+// One finalize launch; with `trace` the workgroup that takes the last ticket
+// applies the stop rule (no workgroup waits).  Each workgroup's maxima are
+// written through to device scope and have completed before its ticket, and
+// the last workgroup reads them at device scope, so no cache is written back
+// for them (a fence per workgroup costs more than the launch it saves).
+template <class AT, class PT>
+__global__ __launch_bounds__(WG) void k_finalize(FinalizeArgs f) {
+    if (f.st->done) return;
+    __shared__ int last;
+    finalize_block<AT, PT>(f.b0 * (TILE / FB) + blockIdx.x, f.N, f.NB, static_cast<const PT*>(f.partP),
+                           static_cast<const PT*>(f.partE), f.Adiag, f.y, static_cast<AT*>(f.Pt),
+                           static_cast<AT*>(f.S), f.alpha, f.blk_delta, f.blk_amax, f.st, f.boxC,
+                           static_cast<AT*>(f.Inv), static_cast<AT*>(f.Mean));
+    if (!f.trace) return;
+    if (threadIdx.x == 0) {
+        wait_vm<0>();
+        last = atomicAdd(&f.st->ticket, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    if (threadIdx.x == 0) f.st->ticket = 0;
+    status_update((int)((f.N + FB - 1) / FB), f.blk_delta, f.blk_amax, f.st, f.trace, f.rule);
+}
+
+// 1/P~ and S/P~ of every ring slot (series sweeps): P~ = +inf, S = 0 give 0
+// and 0, the values a tile would form from them.
+template <class AT>
+__global__ void k_ring_recip(int64_t n, const AT* __restrict__ Pt, const AT* __restrict__ S,
+                             AT* __restrict__ Inv, AT* __restrict__ Mean) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    Inv[i] = (AT)1 / Pt[i];
+    Mean[i] = S[i] / Pt[i];
+}
+
+// The stop rule as a launch of its own.
+__global__ __launch_bounds__(WG) void k_status(FinalizeArgs f) {
+    if (f.st->done) return;
+    status_update((int)((f.N + FB - 1) / FB), f.blk_delta, f.blk_amax, f.st, f.trace, f.rule);
+}
+
+// Served form: items are (request, block of 256 nodes), four finalize blocks
+// each.
+template <class AT>
+__global__ __launch_bounds__(WG) void k_finalize_batched(const ReqDesc* __restrict__ reqs,
+                                                        const uint2* __restrict__ items, int nitems) {
+    constexpr int SUB = TILE / FB;
+    for (int it = blockIdx.x; it < nitems * SUB; it += gridDim.x) {
+        const uint2 w = items[it / SUB];
+        const ReqDesc& rd = reqs[w.x];
+        const int64_t blk = (int64_t)w.y * SUB + it % SUB;
+        if (rd.sw.st->done || blk * FB >= rd.N) continue;
+        const int64_t wslot = (int64_t)((rd.sw.st->t + 1) % rd.sw.R) * rd.sw.NPAD;
+        AT* const Pt = static_cast<AT*>(const_cast<void*>(rd.sw.HP)) + wslot;
+        AT* const S = static_cast<AT*>(const_cast<void*>(rd.sw.HS)) + wslot;
+        // slots per block: NB + 1, or NBc + 1 after a sweep over chunks
+        const int ns = (rd.sw.chunk > 1) ? (rd.sw.NB + rd.sw.chunk - 1) / rd.sw.chunk : rd.sw.NB;
+        if (rd.sw.part32)
+            finalize_block<AT, float>(blk, rd.N, ns, static_cast<const float*>(rd.sw.partP),
+                                      static_cast<const float*>(rd.sw.partE), rd.Adiag, rd.y, Pt, S, rd.alpha,
+                                      rd.blk_delta, rd.blk_amax, rd.sw.st, 0.0, nullptr, nullptr);
+        else
+            finalize_block<AT, AT>(blk, rd.N, ns, static_cast<const AT*>(rd.sw.partP),
+                                   static_cast<const AT*>(rd.sw.partE), rd.Adiag, rd.y, Pt, S, rd.alpha,
+                                   rd.blk_delta, rd.blk_amax, rd.sw.st, 0.0, nullptr, nullptr);
+        __syncthreads();
+    }
+}
+
+// Stop rule of served requests, one workgroup per active request; also copies
+// the request's status into a packed array the host reads back in one
+// transfer.  A step visits one group of a grouped
 // request (G groups; G = 1 for the synchronous schedule); after the visit of
 // the last group the stop rule runs (one sweep done), and the group index
 // advances for every request still running.
@@ -1058,7 +1067,7 @@ hipError_t launch_served_sweep(int prec, int levels, int ser, bool grouped, cons
 }
 
 hipError_t launch_served_finalize(bool agg_f32, const ReqDesc* reqs, const uint2* items, int n, hipStream_t s) {
-    const int gf = std::max(1, std::min(n, 2048));
+    const int gf = std::max(1, std::min(n * (TILE / FB), 8192));
     if (agg_f32)
         hipLaunchKernelGGL(k_finalize_batched<float>, dim3(gf), dim3(WG), 0, s, reqs, items, n);
     else
@@ -1072,24 +1081,22 @@ hipError_t launch_served_status(const ReqDesc* reqs, const int* slots, int nslot
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(int prec, int64_t N, int NB, const void* partP, const void* partE,
-                           const double* Adiag, const float* y, void* Pt, void* S, double* alpha,
-                           double* blk_delta, double* blk_amax, DevStatus* st, hipStream_t s, double boxC,
-                           void* Inv, void* Mean, int part32) {
-    if ((Inv == nullptr) != (Mean == nullptr)) return hipErrorInvalidValue;
-    const dim3 g(grid1(N)), b(WG);
-    if (prec == PREC_FP32)
-        hipLaunchKernelGGL((k_finalize<float, float>), g, b, 0, s, N, NB, (const float*)partP,
-                           (const float*)partE, Adiag, y, (float*)Pt, (float*)S, alpha, blk_delta,
-                           blk_amax, st, boxC, (float*)Inv, (float*)Mean);
-    else if (part32)
-        hipLaunchKernelGGL((k_finalize<double, float>), g, b, 0, s, N, NB, (const float*)partP,
-                           (const float*)partE, Adiag, y, (double*)Pt, (double*)S, alpha,
-                           blk_delta, blk_amax, st, boxC, (double*)Inv, (double*)Mean);
-    else
-        hipLaunchKernelGGL((k_finalize<double, double>), g, b, 0, s, N, NB, (const double*)partP,
-                           (const double*)partE, Adiag, y, (double*)Pt, (double*)S, alpha,
-                           blk_delta, blk_amax, st, boxC, (double*)Inv, (double*)Mean);
+// Above this many finalize workgroups the stop rule is a launch of its own.
+constexpr int64_t kFuseStatusMax = 512;
+
+hipError_t launch_finalize(int prec, const FinalizeArgs& f, hipStream_t s) {
+    if ((f.Inv == nullptr) != (f.Mean == nullptr)) return hipErrorInvalidValue;
+    const int64_t nb = (f.N + FB - 1) / FB, b0 = f.b0 * (TILE / FB);
+    const int64_t b1 = f.b1 > 0 ? std::min(nb, f.b1 * (TILE / FB)) : nb;
+    if (b1 <= b0) return f.trace ? hipErrorInvalidValue : hipSuccess;
+    const dim3 g((unsigned)(b1 - b0)), b(WG);
+    FinalizeArgs a = f;
+    const bool own = f.trace && b1 - b0 > kFuseStatusMax;
+    if (own) a.trace = nullptr;
+    if (prec == PREC_FP32) hipLaunchKernelGGL((k_finalize<float, float>), g, b, 0, s, a);
+    else if (f.part32) hipLaunchKernelGGL((k_finalize<double, float>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_finalize<double, double>), g, b, 0, s, a);
+    if (own) hipLaunchKernelGGL(k_status, dim3(1), b, 0, s, f);
     return hipGetLastError();
 }
 
@@ -1102,34 +1109,6 @@ hipError_t launch_ring_recip(int prec, int64_t NPAD, int R, const void* Pt, cons
     else
         hipLaunchKernelGGL(k_ring_recip<double>, dim3(grid1(n)), dim3(WG), 0, s, n, (const double*)Pt,
                            (const double*)S, (double*)Inv, (double*)Mean);
-    return hipGetLastError();
-}
-
-hipError_t launch_finalize_range(int prec, int64_t b0, int64_t nb, int64_t N, int NB, const void* partP,
-                                 const void* partE, const double* Adiag, const float* y, void* Pt, void* S,
-                                 double* alpha, double* blk_delta, double* blk_amax, DevStatus* st,
-                                 hipStream_t s, double boxC, void* Inv, void* Mean, int part32) {
-    if (nb <= 0) return hipSuccess;
-    if ((Inv == nullptr) != (Mean == nullptr)) return hipErrorInvalidValue;
-    const dim3 g((unsigned)nb), b(WG);
-    if (prec == PREC_FP32)
-        hipLaunchKernelGGL((k_finalize_range<float, float>), g, b, 0, s, b0, N, NB, (const float*)partP,
-                           (const float*)partE, Adiag, y, (float*)Pt, (float*)S, alpha, blk_delta, blk_amax, st,
-                           boxC, (float*)Inv, (float*)Mean);
-    else if (part32)
-        hipLaunchKernelGGL((k_finalize_range<double, float>), g, b, 0, s, b0, N, NB, (const float*)partP,
-                           (const float*)partE, Adiag, y, (double*)Pt, (double*)S, alpha, blk_delta, blk_amax,
-                           st, boxC, (double*)Inv, (double*)Mean);
-    else
-        hipLaunchKernelGGL((k_finalize_range<double, double>), g, b, 0, s, b0, N, NB, (const double*)partP,
-                           (const double*)partE, Adiag, y, (double*)Pt, (double*)S, alpha, blk_delta, blk_amax,
-                           st, boxC, (double*)Inv, (double*)Mean);
-    return hipGetLastError();
-}
-
-hipError_t launch_status(int nblk, const double* blk_delta, const double* blk_amax, DevStatus* st,
-                         double* trace, StopRule rule, hipStream_t s) {
-    hipLaunchKernelGGL(k_status, dim3(1), dim3(WG), 0, s, nblk, blk_delta, blk_amax, st, trace, rule);
     return hipGetLastError();
 }
 

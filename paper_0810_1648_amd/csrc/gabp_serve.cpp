@@ -175,7 +175,7 @@ void plan_sizes(Req& r) {
     z[B_NRM] = (size_t)r.NPAD * 4;
     z[B_KDIAG] = z[B_ADIAG] = z[B_ROWMAX] = z[B_RSUM] = z[B_ALPHA] = (size_t)r.N * 8;
     z[B_PT] = z[B_S] = (size_t)kRing * r.NPAD * 8;
-    z[B_BLK1] = z[B_BLK2] = (size_t)(r.NPAD / WG + 1) * 8;
+    z[B_BLK1] = z[B_BLK2] = (size_t)(r.NPAD / FB + 1) * 8;
     z[B_ONE] = 64;
     z[B_STATUS] = sizeof(DevStatus);
     z[B_TRACE] = (size_t)r.p.max_sweeps * 8;
@@ -398,7 +398,7 @@ hipError_t setup_request(gabp_server* S, Req& r) {
     d.blk_amax = (double*)P(B_BLK2);
     d.trace = (double*)P(B_TRACE);
     d.rule = StopRule{r.p.tol_abs, r.p.tol_rel, r.p.stagnation_rel, r.p.max_sweeps, r.p.stagnation_window};
-    d.nblk = (int)((r.N + WG - 1) / WG);
+    d.nblk = (int)((r.N + FB - 1) / FB);
     d.G = r.G;
     CK(hipMemcpyAsync(S->d_reqs + r.slot, S->h_reqs + r.slot, sizeof(ReqDesc), hipMemcpyHostToDevice, s));
 #undef CK

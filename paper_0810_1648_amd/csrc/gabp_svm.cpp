@@ -295,7 +295,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     A(h->rsum, (size_t)N * 8);
     A(h->Pt, (size_t)R * NPAD * 8); A(h->S, (size_t)R * NPAD * 8);
     A(h->alpha_d, (size_t)N * 8); A(h->tmp, (size_t)NPAD * 8);
-    A(h->blk1, (size_t)(NPAD / WG + 1) * 8); A(h->blk2, (size_t)(NPAD / WG + 1) * 8);
+    A(h->blk1, (size_t)(NPAD / FB + 1) * 8); A(h->blk2, (size_t)(NPAD / FB + 1) * 8);
     A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64);
     A(h->trace_d, (size_t)p.max_sweeps * 8);
     if (rbf) {
@@ -539,7 +539,6 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     sa.F = F;
     sa.kp = kp;
     StopRule rule{p.tol_abs, p.tol_rel, p.stagnation_rel, p.max_sweeps, p.stagnation_window};
-    const int nblk = (int)((N + WG - 1) / WG);
 
     // grouped schedule: groups of whole block rows, block I in group I G / NB;
     // per group the single-direction entries (stateless: every message into
@@ -593,6 +592,19 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
                 HIPCHK(h, hipMemsetAsync(pl->p, 0, plane, s));
         HIPCHK(h, hipStreamSynchronize(s));
     }
+    FinalizeArgs fa{};
+    fa.N = N;
+    fa.NB = nslot;
+    fa.partP = h->partP.p; fa.partE = h->partE.p;
+    fa.Adiag = h->Adiag.as<double>();
+    fa.y = h->yd.as<float>();
+    fa.alpha = h->alpha_d.as<double>();
+    fa.blk_delta = h->blk1.as<double>(); fa.blk_amax = h->blk2.as<double>();
+    fa.st = st;
+    fa.boxC = boxC;
+    fa.part32 = sa.part32;
+    fa.trace = h->trace_d.as<double>();
+    fa.rule = rule;
     DevStatus hs{};
     double sweep_kernel_ms = 0.0;
     int64_t launches = 0;
@@ -611,10 +623,8 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
             // the events take the sweep dispatch's own timestamps
             HIPCHK(h, launch_sweep(prec, ksrc, gram, sa.levels, t == 0, ser, sa, s,
                                    p.time_sweeps ? sev[2 * slot] : nullptr, p.time_sweeps ? sev[2 * slot + 1] : nullptr));
-            HIPCHK(h, launch_finalize(prec, N, nslot, h->partP.p, h->partE.p, h->Adiag.as<double>(),
-                                      h->yd.as<float>(), wP, wS, h->alpha_d.as<double>(),
-                                      h->blk1.as<double>(), h->blk2.as<double>(), st, s, boxC, wI, wM,
-                                      sa.part32));
+            fa.Pt = wP; fa.S = wS; fa.Inv = wI; fa.Mean = wM;
+            HIPCHK(h, launch_finalize(prec, fa, s));
         } else {
             // one visit per group: its messages, then its aggregates (the
             // timed span covers the visits and their group finalizes)
@@ -624,16 +634,14 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
                 HIPCHK(h, launch_sweep_grouped(prec, ksrc, gram, sa.levels, ser, sa, gl + g_within_off[g],
                                                (int)(g_within_off[g + 1] - g_within_off[g]), gl + g_dir_off[g],
                                                (int)(g_dir_off[g + 1] - g_dir_off[g]), t, s));
-                const int64_t b0 = g_b0[g], b1 = std::min<int64_t>(g_b0[g + 1], nblk);
-                HIPCHK(h, launch_finalize_range(prec, b0, b1 - b0, N, NB, h->partP.p, h->partE.p,
-                                                h->Adiag.as<double>(), h->yd.as<float>(), wP, wS,
-                                                h->alpha_d.as<double>(), h->blk1.as<double>(),
-                                                h->blk2.as<double>(), st, s, boxC, wI, wM, sa.part32));
+                // the stop rule runs with the last group's aggregates
+                fa.Pt = wP; fa.S = wS; fa.Inv = wI; fa.Mean = wM;
+                fa.b0 = g_b0[g]; fa.b1 = g_b0[g + 1];
+                fa.trace = (g == G - 1) ? h->trace_d.as<double>() : nullptr;
+                HIPCHK(h, launch_finalize(prec, fa, s));
             }
             if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot + 1], s));
         }
-        HIPCHK(h, launch_status(nblk, h->blk1.as<double>(), h->blk2.as<double>(), st,
-                                h->trace_d.as<double>(), rule, s));
         if ((t + 1) % ce == 0 || t + 1 == p.max_sweeps) {
             HIPCHK(h, hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
             HIPCHK(h, hipStreamSynchronize(s));
@@ -809,7 +817,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     A(h->rsum, (size_t)N * 8);
     A(h->Pt, (size_t)NPAD * 8); A(h->S, (size_t)NPAD * 8);
     A(h->alpha_d, (size_t)N * 8); A(h->tmp, (size_t)NPAD * 8);
-    A(h->blk1, (size_t)(NPAD / WG + 1) * 8); A(h->blk2, (size_t)(NPAD / WG + 1) * 8);
+    A(h->blk1, (size_t)(NPAD / FB + 1) * 8); A(h->blk2, (size_t)(NPAD / FB + 1) * 8);
     A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64);
     A(h->trace_d, (size_t)p.max_sweeps * 8);
     A(h->sp_degi, (size_t)(N + 1) * 4); A(h->sp_degj, (size_t)(N + 1) * 4);
@@ -1025,8 +1033,18 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     HIPCHK(h, hipEventRecord(ev[3], s));
 
     // ---- sweeps: edge update + per-node gather, finalize, stop rule
-    StopRule rule{p.tol_abs, p.tol_rel, p.stagnation_rel, p.max_sweeps, p.stagnation_window};
-    const int nblk = (int)((N + WG - 1) / WG);
+    FinalizeArgs fa{};
+    fa.N = N;
+    fa.partP = h->partP.p; fa.partE = h->partE.p;
+    fa.Adiag = h->Adiag.as<double>();
+    fa.y = h->yd.as<float>();
+    fa.Pt = h->Pt.p; fa.S = h->S.p;
+    fa.alpha = h->alpha_d.as<double>();
+    fa.blk_delta = h->blk1.as<double>(); fa.blk_amax = h->blk2.as<double>();
+    fa.st = st;
+    fa.boxC = boxC;
+    fa.trace = h->trace_d.as<double>();
+    fa.rule = StopRule{p.tol_abs, p.tol_rel, p.stagnation_rel, p.max_sweeps, p.stagnation_window};
     DevStatus hs{};
     double sweep_kernel_ms = 0.0;
     int64_t launches = 0;
@@ -1039,11 +1057,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
                                   h->sp_offj.as<int64_t>(), h->sp_perm.as<int32_t>(), h->partP.p, h->partE.p,
                                   st, s));
         if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot + 1], s));
-        HIPCHK(h, launch_finalize(prec, N, 0, h->partP.p, h->partE.p, h->Adiag.as<double>(), h->yd.as<float>(),
-                                  h->Pt.p, h->S.p, h->alpha_d.as<double>(), h->blk1.as<double>(),
-                                  h->blk2.as<double>(), st, s, boxC));
-        HIPCHK(h, launch_status(nblk, h->blk1.as<double>(), h->blk2.as<double>(), st, h->trace_d.as<double>(),
-                                rule, s));
+        HIPCHK(h, launch_finalize(prec, fa, s));
         if ((t + 1) % ce == 0 || t + 1 == p.max_sweeps) {
             HIPCHK(h, hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
             HIPCHK(h, hipStreamSynchronize(s));
