@@ -559,6 +559,16 @@ struct TileSums {
     AT cp[4], ce[4];
 };
 
+// Offsets of a tile's partial sums (part_stride, part_slots).
+struct PartSlots {
+    int NB, split;
+    __device__ size_t at(int K, int slot) const { return ((size_t)K * part_stride(NB, split) + slot) * TILE; }
+    __device__ size_t row(int I, int J) const { return at(I, I * split + J - I); }
+    __device__ size_t col(int I, int J, int sub) const {
+        return at(J, I < J ? I * split + sub : J * split + NB - J + sub);
+    }
+};
+
 // Stores one partial sum of a tile: in FP32 when the plan keeps its partials
 // in FP32 (the FP32-message form, whose tile sums are FP32 sums rounded once
 // more here), else in the aggregate type.
@@ -593,7 +603,8 @@ struct MsgT {
 //      messages), lower levels in LT (see below);
 //   FIRST: the stored planes are all zero (sweep 1) and are not read.
 // Work of one tile: its row and column sums go to the tile's partial slots,
-// or, with `out`, to the caller (a chunk adds them up first).  SER (stateless
+// or, with `out`, to the caller (a chunk adds them up first).  split > 1: only
+// the sub-th of `split` equal row parts of the tile.  SER (stateless
 // only; 0 = exact reciprocals): the
 // reciprocals of the cavity precisions Q = P~ (1 - e), e = P_reverse / P~,
 // are formed from the per-node u = 1/P~ by the series
@@ -608,7 +619,8 @@ struct MsgT {
 // nothing, a middle level costs four operations per direction (two with
 // G = u).
 template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER>
-__device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top, TileSums<AT>* out = nullptr) {
+__device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top, TileSums<AT>* out = nullptr,
+                                  int split = 1, int sub = 0) {
     DevStatus* st = a.st;
     // lower levels: FP32 storage precision; with the series and up to three
     // levels they run in the top level's type (FP64 FMA issues at the FP32
@@ -669,11 +681,14 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
     constexpr bool RING = (KSRC == KSRC_PLANE) && !STORED && std::is_same<ST, float>::value;
     constexpr int KR = RING ? KRING : 1;
     constexpr int SU = (RING && 8 % KR == 0) ? KR : 1;   // row steps unrolled (static ring slots)
+    // this part's 32-row bands [bb0, bb1), its first row step and the end
+    const int bb0 = sub * (TILE / 32 / split), bb1 = bb0 + TILE / 32 / split;
+    const int u0 = 8 * bb0, u1 = 8 * bb1;
     __shared__ __attribute__((aligned(16))) float kring[KR][4][RING ? 256 : 4];
     if constexpr (RING) {
 #pragma unroll
         for (int u = 0; u < KR; ++u)
-            dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)u * 4 * TILE, lo * 4u,
+            dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)(u0 + u) * 4 * TILE, lo * 4u,
                   lds_offset(&kring[u][w][0]));
     }
 
@@ -760,7 +775,7 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
     __syncthreads();
 
     // row offset (wave-uniform: tile base plus 4 TILE per row step)
-    size_t off = tbase;
+    size_t off = tbase + (size_t)u0 * 4 * TILE;
     V4<ST> k{}, pf{}, pb{}, ef{}, eb{};
     if constexpr (!RING && KSRC == KSRC_PLANE) k = ld4nt(lane_ptr(Kp + off, lo));
     if constexpr (STORED && !FIRST) {
@@ -768,7 +783,7 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
         ef = ld4nt(lane_ptr(Ef + off, lo)); eb = ld4nt(lane_ptr(Eb + off, lo));
     }
 
-    for (int b = 0; b < TILE / 32; ++b) {
+    for (int b = bb0; b < bb1; ++b) {
         if constexpr (KSRC == KSRC_RECOMPUTE) {
             gram_band<GK>(a.F, a.kp, tc.I, tc.J, 32 * b, 64 * w, kband[w]);
             wave_lds_sync();
@@ -778,7 +793,7 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
             const int r = 32 * b + 4 * s2 + g;
             // prefetch the lane's next row (the last row re-reads itself: the
             // offset stays inside the tile and no branch is needed)
-            const bool more = (b * 8 + s2 + 1) < TILE / 4;
+            const bool more = (b * 8 + s2 + 1) < u1;
             const size_t off2 = more ? off + 4 * TILE : off;
             V4<ST> k2, pf2, pb2, ef2, eb2;
             const int u = b * 8 + s2;                 // row step
@@ -786,7 +801,7 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
                 // this step's slot has landed once at most KR - 1 loads are
                 // in flight (every later step issued one), or all of them near
                 // the tile's end
-                if (u + KR <= TILE / 4) wait_vm<KR - 1>();
+                if (u + KR <= u1) wait_vm<KR - 1>();
                 else wait_vm<0>();
                 const float4 kk = *reinterpret_cast<const float4*>(&kring[u % KR][w][4 * l]);
                 k = V4<ST>{{(ST)kk.x, (ST)kk.y, (ST)kk.z, (ST)kk.w}};
@@ -932,7 +947,7 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
             }
             if constexpr (RING) {
                 // the slot's next row step (k was read from it and used above)
-                if (u + KR < TILE / 4)
+                if (u + KR < u1)
                     dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)(u + KR) * 4 * TILE, lo * 4u,
                           lds_offset(&kring[u % KR][w][0]));
             } else if constexpr (KSRC == KSRC_PLANE) {
@@ -960,12 +975,14 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
         return;
     }
     const bool p32 = a.part32 != 0;
-    const size_t rowslot = ((size_t)tc.I * (NB + 1) + tc.J) * TILE + tid;
-    put_part(a.partP, rowslot, rowP, p32);
-    put_part(a.partE, rowslot, rowE, p32);
+    const PartSlots ps{NB, split};
+    if (tid >= 4 * u0 && tid < 4 * u1) {
+        const size_t rowslot = ps.row(tc.I, tc.J) + tid;
+        put_part(a.partP, rowslot, rowP, p32);
+        put_part(a.partE, rowslot, rowE, p32);
+    }
     if (g == 0) {
-        const int slot = (tc.I < tc.J) ? tc.I : NB;
-        const size_t cb = ((size_t)tc.J * (NB + 1) + slot) * TILE + col0;
+        const size_t cb = ps.col(tc.I, tc.J, sub) + col0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) { put_part(a.partP, cb + c, cP[c], p32); put_part(a.partE, cb + c, cE[c], p32); }
     }
@@ -974,7 +991,8 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
 template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER>
 __global__ __launch_bounds__(WG) void k_sweep(SweepArgs a) {
     if (a.st->done) return;
-    sweep_tile<ST, MT, AT, KSRC, GK, D, FIRST, SER>(a, blockIdx.x, a.slot_top);
+    sweep_tile<ST, MT, AT, KSRC, GK, D, FIRST, SER>(a, blockIdx.x / a.split, a.slot_top, nullptr, a.split,
+                                                    blockIdx.x % a.split);
 }
 
 // The sweeps chunk_plan selects (a.chunk = 2, single solves and served
@@ -1061,7 +1079,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4, 8))) void
 template <class ST, class MT, class AT, int GK, int D, int SER>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_sweep_rc(SweepArgs a) {
     if (a.st->done) return;
-    sweep_tile<ST, MT, AT, KSRC_RECOMPUTE, GK, D, false, SER>(a, blockIdx.x, a.slot_top);
+    sweep_tile<ST, MT, AT, KSRC_RECOMPUTE, GK, D, false, SER>(a, blockIdx.x / a.split, a.slot_top, nullptr, a.split,
+                                                              blockIdx.x % a.split);
 }
 
 // ------------------------------------------------ grouped (Gauss-Seidel) --
@@ -1128,7 +1147,7 @@ struct DirTypes {
 // aggregates at version v sit in ring slot v mod R (R = 1 for stored
 // records: every read is the node's latest value).
 template <class ST, class MT, class AT, int KSRC, int GK, int D, int SER, bool FWD, class SM>
-__device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool within, int t, SM& sm) {
+__device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool within, int t, SM& sm, int sub) {
     using DT = DirTypes<ST, MT, AT, D, SER>;
     using LT = typename DT::LT;
     using XT = typename DT::XT;
@@ -1156,10 +1175,13 @@ __device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool wit
     constexpr bool RING = (SM::RING_STEPS > 0) && (KSRC == KSRC_PLANE) && !STORED && std::is_same<ST, float>::value;
     constexpr int KR = RING ? SM::RING_STEPS : 1;
     constexpr int SU = (RING && 8 % KR == 0) ? KR : 1;   // row steps unrolled (static ring slots)
+    // the sub-th row part of the tile: bands [bb0, bb1), row steps [u0, u1)
+    const int bb0 = sub * (TILE / 32 / a.split), bb1 = bb0 + TILE / 32 / a.split;
+    const int u0 = 8 * bb0, u1 = 8 * bb1;
     if constexpr (RING) {
 #pragma unroll
         for (int u = 0; u < KR; ++u)
-            dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)u * 4 * TILE, lo * 4u,
+            dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)(u0 + u) * 4 * TILE, lo * 4u,
                   lds_offset(&sm.kring[u][w][0]));
     }
     auto slot_of = [&](int k) -> int64_t {
@@ -1233,12 +1255,12 @@ __device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool wit
     ST* Pwr = static_cast<ST*>(FWD ? a.Pf : a.Pb);
     ST* Ewr = static_cast<ST*>(FWD ? a.Ef : a.Eb);
 
-    size_t off = tbase;                                   // wave-uniform row offset
+    size_t off = tbase + (size_t)u0 * 4 * TILE;                                   // wave-uniform row offset
     V4<ST> k4{}, pr{}, er{};
     if constexpr (KSRC == KSRC_PLANE && !RING) k4 = ld4nt(lane_ptr(Kp + off, lo));
     if constexpr (STORED) { pr = ld4nt(lane_ptr(Prd + off, lo)); er = ld4nt(lane_ptr(Erd + off, lo)); }
 
-    for (int b = 0; b < TILE / 32; ++b) {
+    for (int b = bb0; b < bb1; ++b) {
         if constexpr (KSRC == KSRC_RECOMPUTE) {
             gram_band<GK>(a.F, a.kp, tc.I, tc.J, 32 * b, 64 * w, sm.kband[w]);
             wave_lds_sync();
@@ -1246,12 +1268,12 @@ __device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool wit
 #pragma unroll SU
         for (int s2 = 0; s2 < 8; ++s2) {
             const int r = 32 * b + 4 * s2 + g;
-            const bool more = (b * 8 + s2 + 1) < TILE / 4;
+            const bool more = (b * 8 + s2 + 1) < u1;
             const size_t off2 = more ? off + 4 * TILE : off;
             V4<ST> k2, pr2, er2;
             const int u = b * 8 + s2;                 // row step
             if constexpr (RING) {
-                if (u + KR <= TILE / 4) wait_vm<KR - 1>();
+                if (u + KR <= u1) wait_vm<KR - 1>();
                 else wait_vm<0>();
                 const float4 kk = *reinterpret_cast<const float4*>(&sm.kring[u % KR][w][4 * l]);
                 k4 = V4<ST>{{(ST)kk.x, (ST)kk.y, (ST)kk.z, (ST)kk.w}};
@@ -1372,7 +1394,7 @@ __device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool wit
             }
             if constexpr (RING) {
                 // the slot's next row step (k4 was read from it and used above)
-                if (u + KR < TILE / 4)
+                if (u + KR < u1)
                     dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)(u + KR) * 4 * TILE, lo * 4u,
                           lds_offset(&sm.kring[u % KR][w][0]));
             } else if constexpr (KSRC == KSRC_PLANE) {
@@ -1384,6 +1406,7 @@ __device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool wit
         if constexpr (KSRC == KSRC_RECOMPUTE) wave_lds_sync();
     }
     const bool p32 = a.part32 != 0;
+    const PartSlots ps{NB, a.split};
     if constexpr (FWD) {
         if constexpr (XF) {
 #pragma unroll
@@ -1392,16 +1415,17 @@ __device__ inline void sweep_tile_dir(const SweepArgs& a, int64_t tile, bool wit
 #pragma unroll
         for (int c = 0; c < 4; ++c) { cP[c] = sum_groups(cP[c]); cE[c] = sum_groups(cE[c]); }
         if (g == 0) {
-            const int slot = (tc.I < tc.J) ? tc.I : NB;
-            const size_t cb = ((size_t)tc.J * (NB + 1) + slot) * TILE + col0;
+            const size_t cb = ps.col(tc.I, tc.J, sub) + col0;
 #pragma unroll
             for (int c = 0; c < 4; ++c) { put_part(a.partP, cb + c, cP[c], p32); put_part(a.partE, cb + c, cE[c], p32); }
         }
     } else {
         __syncthreads();
-        const size_t rowslot = ((size_t)tc.I * (NB + 1) + tc.J) * TILE + tid;
-        put_part(a.partP, rowslot, ((AT)sm.rP[0][tid] + (AT)sm.rP[1][tid]) + ((AT)sm.rP[2][tid] + (AT)sm.rP[3][tid]), p32);
-        put_part(a.partE, rowslot, ((AT)sm.rE[0][tid] + (AT)sm.rE[1][tid]) + ((AT)sm.rE[2][tid] + (AT)sm.rE[3][tid]), p32);
+        if (tid >= 4 * u0 && tid < 4 * u1) {
+            const size_t rowslot = ps.row(tc.I, tc.J) + tid;
+            put_part(a.partP, rowslot, ((AT)sm.rP[0][tid] + (AT)sm.rP[1][tid]) + ((AT)sm.rP[2][tid] + (AT)sm.rP[3][tid]), p32);
+            put_part(a.partE, rowslot, ((AT)sm.rE[0][tid] + (AT)sm.rE[1][tid]) + ((AT)sm.rE[2][tid] + (AT)sm.rE[3][tid]), p32);
+        }
     }
     if (__any(bad) && l == 0) st->bad = 1;
 }
@@ -1413,11 +1437,12 @@ __global__ __launch_bounds__(WG) void k_sweep_dir(SweepArgs a, const uint32_t* _
     __shared__ DirSmem<typename DT::XT, typename DT::LT, AT, typename DT::RT, DT::NRL, KSRC == KSRC_RECOMPUTE,
                        (KSRC == KSRC_PLANE && D >= 1 && std::is_same<ST, float>::value) ? KRING : 0> sm;
     if (a.st->done) return;
-    const uint32_t e = list[blockIdx.x];
+    const uint32_t e = list[blockIdx.x / a.split];
+    const int sub = blockIdx.x % a.split;
     const int64_t tile = (int64_t)(e & GE_TILE);
     const bool within = (e & GE_WITHIN) != 0;
-    if (e & GE_BWD) sweep_tile_dir<ST, MT, AT, KSRC, GK, D, SER, false>(a, tile, within, t, sm);
-    else sweep_tile_dir<ST, MT, AT, KSRC, GK, D, SER, true>(a, tile, within, t, sm);
+    if (e & GE_BWD) sweep_tile_dir<ST, MT, AT, KSRC, GK, D, SER, false>(a, tile, within, t, sm, sub);
+    else sweep_tile_dir<ST, MT, AT, KSRC, GK, D, SER, true>(a, tile, within, t, sm, sub);
 }
 
 // Served grouped visit: items are (request, list entry) pairs of every
@@ -1430,14 +1455,15 @@ __global__ __launch_bounds__(WG) void k_sweep_dir_batched(const ReqDesc* __restr
     __shared__ DirSmem<typename DT::XT, typename DT::LT, AT, typename DT::RT, DT::NRL, 0> sm;
     for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
         const uint2 w = items[it];
-        const ReqDesc& rd = reqs[w.x];
+        const ReqDesc& rd = reqs[w.x & 0xFFFFu];
+        const int sub = (int)(w.x >> 16);
         const DevStatus* st = rd.sw.st;
         if (st->done) continue;
         const uint32_t e = w.y;
         const int64_t tile = (int64_t)(e & GE_TILE);
         const bool within = (e & GE_WITHIN) != 0;
-        if (e & GE_BWD) sweep_tile_dir<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, SER, false>(rd.sw, tile, within, st->t, sm);
-        else sweep_tile_dir<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, SER, true>(rd.sw, tile, within, st->t, sm);
+        if (e & GE_BWD) sweep_tile_dir<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, SER, false>(rd.sw, tile, within, st->t, sm, sub);
+        else sweep_tile_dir<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, SER, true>(rd.sw, tile, within, st->t, sm, sub);
         __syncthreads();
     }
 }
@@ -1447,11 +1473,12 @@ __global__ __launch_bounds__(WG) void k_sweep_dir_batched(const ReqDesc* __restr
 template <class ST, class MT, class AT, int KSRC, int GK>
 __global__ __launch_bounds__(WG) void k_sweep_listed(SweepArgs a, const uint32_t* __restrict__ list) {
     if (a.st->done) return;
-    sweep_tile<ST, MT, AT, KSRC, GK, 0, false, 0>(a, (int64_t)(list[blockIdx.x] & GE_TILE), 0);
+    sweep_tile<ST, MT, AT, KSRC, GK, 0, false, 0>(a, (int64_t)(list[blockIdx.x / a.split] & GE_TILE), 0, nullptr,
+                                                  a.split, blockIdx.x % a.split);
 }
 
-// Served form: one persistent grid walks the union work list of (request,
-// tile) items of the active requests of one group (same precision, edge
+// Served form: one persistent grid walks the union work list of (request
+// | row part << 16, tile) items of the active requests of one group (same precision, edge
 // state and level count).  Each request keeps its own planes or aggregate
 // ring, partial sums and status, so its arithmetic does not depend on the
 // mix; the ring slot of the previous sweep follows from the request's own
@@ -1462,10 +1489,11 @@ __global__ __launch_bounds__(WG) void k_sweep_batched(const ReqDesc* __restrict_
                                                      const uint2* __restrict__ items, int nitems) {
     for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
         const uint2 w = items[it];
-        const ReqDesc& rd = reqs[w.x];
+        const ReqDesc& rd = reqs[w.x & 0xFFFFu];
         const DevStatus* st = rd.sw.st;
         if (st->done) continue;
-        sweep_tile<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, false, SER>(rd.sw, (int64_t)w.y, st->t % rd.sw.R);
+        sweep_tile<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, false, SER>(rd.sw, (int64_t)w.y, st->t % rd.sw.R, nullptr,
+                                                                    rd.sw.split, (int)(w.x >> 16));
         __syncthreads();
     }
 }
@@ -1479,13 +1507,14 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     const ReqDesc* __restrict__ reqs, const uint2* __restrict__ items, int nitems) {
     for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
         const uint2 w = items[it];
-        const ReqDesc& rd = reqs[w.x];
+        const ReqDesc& rd = reqs[w.x & 0xFFFFu];
         const DevStatus* st = rd.sw.st;
         if (st->done) continue;
         if (rd.sw.chunk > 1)
             sweep_chunk<ST, MT, AT, GRAM_F32, D, SER, 2>(rd.sw, (int)(w.y >> 16), (int)(w.y & 0xFFFFu), st->t % rd.sw.R);
         else
-            sweep_tile<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, false, SER>(rd.sw, (int64_t)w.y, st->t % rd.sw.R);
+            sweep_tile<ST, MT, AT, KSRC_PLANE, GRAM_F32, D, false, SER>(rd.sw, (int64_t)w.y, st->t % rd.sw.R, nullptr,
+                                                                        rd.sw.split, (int)(w.x >> 16));
         __syncthreads();
     }
 }
@@ -1551,7 +1580,7 @@ inline void launch_ev(K kern, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipE
 
 template <class ST, class MT, class AT, int KSRC, int GK, int D, int SER>
 inline hipError_t sweep_d(bool first, const SweepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    const dim3 g((unsigned)a.ntiles), blk(WG);
+    const dim3 g((unsigned)(a.ntiles * a.split)), blk(WG);
     if (a.chunk > 1) {
         if constexpr (chunk_sweep_ok<ST, MT, AT, KSRC, D, SER>()) {
             if (a.chunk != 2 || a.chunks == nullptr || a.nchunks <= 0) return hipErrorInvalidValue;
@@ -1596,7 +1625,7 @@ inline hipError_t sweep_depth(int levels, bool first, int ser, const SweepArgs& 
 template <class ST, class MT, class AT, int KSRC, int GK, int D, int SER>
 inline void grouped_d(const SweepArgs& a, const uint32_t* list, int n, int t, hipStream_t s) {
     if (n > 0)
-        hipLaunchKernelGGL((k_sweep_dir<ST, MT, AT, KSRC, GK, D, SER>), dim3((unsigned)n), dim3(WG), 0, s, a, list, t);
+        hipLaunchKernelGGL((k_sweep_dir<ST, MT, AT, KSRC, GK, D, SER>), dim3((unsigned)(n * a.split)), dim3(WG), 0, s, a, list, t);
 }
 
 // Stored records (levels 0): the tiles inside the group in `within` (both
@@ -1606,7 +1635,7 @@ inline hipError_t sweep_grouped(int levels, int ser, const SweepArgs& a, const u
                                 const uint32_t* dir, int ndir, int t, hipStream_t s) {
     if (levels == 0) {
         if (nwithin > 0)
-            hipLaunchKernelGGL((k_sweep_listed<ST, MT, AT, KSRC, GK>), dim3((unsigned)nwithin), dim3(WG), 0, s, a,
+            hipLaunchKernelGGL((k_sweep_listed<ST, MT, AT, KSRC, GK>), dim3((unsigned)(nwithin * a.split)), dim3(WG), 0, s, a,
                                within);
         grouped_d<ST, MT, AT, KSRC, GK, 0, 0>(a, dir, ndir, t, s);
         return hipGetLastError();

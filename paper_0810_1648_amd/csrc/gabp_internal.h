@@ -133,6 +133,30 @@ inline bool chunk_sweep(bool fp32_partials, int levels, int ser, int NB, int mod
     if (mode == 1 || !chunk_plan(fp32_partials, levels, ser)) return false;
     return mode == 2 || nbc * (nbc + 1) / 2 >= kChunkMin;
 }
+// Row parts per tile of a sweep over whole tiles (1, 2, 4 or 8 workgroups per
+// tile, each with 256 / split of its rows), for a launch of `items` tiles or
+// single-direction entries: the fewest that give two workgroups per CU.  A
+// tile's 64 row steps are one serial chain per wave, so a launch of fewer
+// tiles than that takes the chain's time whatever its size: N = 500 in FP64
+// (3 tiles) 13.4 -> 3.8 ms per solve with eight parts, N = 3,001 in FP32 (78
+// tiles) 4.5 -> 2.8 ms.  Beyond it the parts' prologues and column partials
+// cost more than they fill: visits of 1,550 entries (N = 40,009, 16 groups) 11.4
+// ms at 512, 12.1 at 2,048 and 15.6 at 8,192, 3,160 tiles (N = 20,000) 20.1,
+// 20.2 and 21.8 ms, a burst of 48 served solves 54, 57 and 61 ms.
+inline int tile_split(int64_t items) {
+    for (int sp = 1; sp < 8; sp *= 2)
+        if (items * sp >= 512) return sp;
+    return 8;
+}
+// Partial-sum slots of node block K when every tile is split into `split` row
+// parts (a tile's column sums then take one slot per part, its row sums one
+// slot, each part storing its own rows): the column sums of part s of tile
+// (I, K), I < K, in slot I split + s; the row sums of tile (K, J) in slot
+// K split + J - K; the column sums of part s of the diagonal tile in slot
+// K split + NB - K + s.  part_stride slots are set aside per block;
+// part_slots(K) of them are in use.
+__host__ __device__ inline int part_stride(int NB, int split) { return NB * split + 1; }
+__host__ __device__ inline int part_slots(int K, int NB, int split) { return split * (K + 1) + NB - K; }
 // Storage index of tile (I, J), I <= J: row-major over the upper triangle.
 __host__ __device__ inline int64_t tile_index(int I, int J, int NB) {
     return (int64_t)I * NB - (int64_t)I * (I - 1) / 2 + (J - I);
@@ -183,11 +207,12 @@ struct SweepArgs {
     int64_t NPAD;
     int R, slot_top, levels;      // ring depth, top slot, stateless levels in use
     int part32;                   // 1: partial sums stored in FP32 (FP32-message plans)
-    void *partP, *partE;          // [NB][NB+1][TILE] partial sums (aggregate type, or FP32); chunked
-                                  // sweeps: [NB][NBc+1][TILE], NBc = ceil(NB / chunk)
+    void *partP, *partE;          // [NB][part_stride][TILE] partial sums (aggregate type, or FP32);
+                                  // chunked sweeps: [NB][NBc+1][TILE], NBc = ceil(NB / chunk)
     const uint32_t* chunks;       // chunked synchronous sweep: Ic << 16 | Jc, Ic <= Jc < NBc (row-major)
     int64_t nchunks;
     int chunk;                    // tiles per chunk side (0 or 1: one tile per workgroup)
+    int split;                    // row parts per tile (1 with chunks)
     DevStatus* st;
     Features F;                   // KSRC_RECOMPUTE
     KernelParams kp;
@@ -253,7 +278,7 @@ hipError_t launch_sweep_f64(int ksrc, int gram, int levels, bool first, int ser,
 // visits of all groups but the last).
 struct FinalizeArgs {
     int64_t N;
-    int NB;                       // slots per block - 1
+    int stride, split, NB;        // slots set aside per block; part_slots(K, NB, split) in use (split = 1: all)
     const void *partP, *partE;
     const double* Adiag;
     const float* y;

@@ -679,7 +679,7 @@ __device__ inline void status_update(int nblk, const double* __restrict__ bd,
 // many workgroups as it has waves: with 256 nodes per workgroup and one slot
 // in flight a 158-slot group visit took 17.8 us and an 80-slot sweep 10.6 us.
 template <class AT, class PT>
-__device__ inline void finalize_block(int64_t blk, int64_t N, int NB, const PT* __restrict__ partP,
+__device__ inline void finalize_block(int64_t blk, int64_t N, int stride, int slots, const PT* __restrict__ partP,
                                       const PT* __restrict__ partE,
                                       const double* __restrict__ Adiag,
                                       const float* __restrict__ y, AT* __restrict__ Pt,
@@ -691,9 +691,9 @@ __device__ inline void finalize_block(int64_t blk, int64_t N, int NB, const PT* 
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int64_t i = blk * FB + l;
     {
-        const int S1 = NB + 1, qn = (S1 + 3) / 4;
-        const int s0 = w * qn, s1 = (s0 + qn < S1) ? s0 + qn : S1;
-        const size_t o = (size_t)(i / TILE) * S1 * TILE + (size_t)(i % TILE);
+        const int qn = (slots + 3) / 4;
+        const int s0 = w * qn, s1 = (s0 + qn < slots) ? s0 + qn : slots;
+        const size_t o = (size_t)(i / TILE) * stride * TILE + (size_t)(i % TILE);
         const PT* pp = partP + o;
         const PT* pe = partE + o;
         AT ap = 0, ae = 0;
@@ -744,7 +744,9 @@ template <class AT, class PT>
 __global__ __launch_bounds__(WG) void k_finalize(FinalizeArgs f) {
     if (f.st->done) return;
     __shared__ int last;
-    finalize_block<AT, PT>(f.b0 * (TILE / FB) + blockIdx.x, f.N, f.NB, static_cast<const PT*>(f.partP),
+    const int64_t blk = f.b0 * (TILE / FB) + blockIdx.x;
+    const int slots = f.split > 1 ? part_slots((int)(blk / (TILE / FB)), f.NB, f.split) : f.stride;
+    finalize_block<AT, PT>(blk, f.N, f.stride, slots, static_cast<const PT*>(f.partP),
                            static_cast<const PT*>(f.partE), f.Adiag, f.y, static_cast<AT*>(f.Pt),
                            static_cast<AT*>(f.S), f.alpha, f.blk_delta, f.blk_amax, f.st, f.boxC,
                            static_cast<AT*>(f.Inv), static_cast<AT*>(f.Mean));
@@ -790,14 +792,16 @@ __global__ __launch_bounds__(WG) void k_finalize_batched(const ReqDesc* __restri
         const int64_t wslot = (int64_t)((rd.sw.st->t + 1) % rd.sw.R) * rd.sw.NPAD;
         AT* const Pt = static_cast<AT*>(const_cast<void*>(rd.sw.HP)) + wslot;
         AT* const S = static_cast<AT*>(const_cast<void*>(rd.sw.HS)) + wslot;
-        // slots per block: NB + 1, or NBc + 1 after a sweep over chunks
-        const int ns = (rd.sw.chunk > 1) ? (rd.sw.NB + rd.sw.chunk - 1) / rd.sw.chunk : rd.sw.NB;
+        // NBc + 1 slots per block after a sweep over chunks
+        const int stride = (rd.sw.chunk > 1) ? (rd.sw.NB + rd.sw.chunk - 1) / rd.sw.chunk + 1
+                                             : part_stride(rd.sw.NB, rd.sw.split);
+        const int ns = (rd.sw.chunk > 1) ? stride : part_slots((int)w.y, rd.sw.NB, rd.sw.split);
         if (rd.sw.part32)
-            finalize_block<AT, float>(blk, rd.N, ns, static_cast<const float*>(rd.sw.partP),
+            finalize_block<AT, float>(blk, rd.N, stride, ns, static_cast<const float*>(rd.sw.partP),
                                       static_cast<const float*>(rd.sw.partE), rd.Adiag, rd.y, Pt, S, rd.alpha,
                                       rd.blk_delta, rd.blk_amax, rd.sw.st, 0.0, nullptr, nullptr);
         else
-            finalize_block<AT, AT>(blk, rd.N, ns, static_cast<const AT*>(rd.sw.partP),
+            finalize_block<AT, AT>(blk, rd.N, stride, ns, static_cast<const AT*>(rd.sw.partP),
                                    static_cast<const AT*>(rd.sw.partE), rd.Adiag, rd.y, Pt, S, rd.alpha,
                                    rd.blk_delta, rd.blk_amax, rd.sw.st, 0.0, nullptr, nullptr);
         __syncthreads();

@@ -141,6 +141,7 @@ struct Req {
     int32_t refused = 0; // set up but refused (gabp_status): no plan without a bound
     int levels = 0;      // 0: stored pair records; >= 1: stateless levels
     int ser = 0;         // stateless reciprocals: 0 exact, 1 / 2 series (top-level terms)
+    int split = 1;       // row parts per tile
     bool chunked = false;  // synchronous sweeps over 2 x 2 chunks of tiles
     double rho = 0.0;    // contraction bound
     // grouped schedule: G groups of whole block rows, the group the next step
@@ -158,7 +159,10 @@ constexpr int kRing = 8;   // aggregate ring slots (stateless form)
 void plan_sizes(Req& r) {
     const size_t st = (r.prec == PREC_FP64) ? 8 : 4;
     const size_t plane = (size_t)r.nt * TT * st;
-    const size_t part = (size_t)r.NB * (r.NB + 1) * TILE * 8;
+    // row parts per tile, as in a single solve
+    const int G = r.p.schedule == GABP_SCHED_GROUPED ? std::min(r.p.sched_groups > 0 ? r.p.sched_groups : 16, r.NB) : 0;
+    r.split = tile_split(G ? 2 * r.nt / G : r.nt);
+    const size_t part = (size_t)r.NB * part_stride(r.NB, r.split) * TILE * 8;
     const size_t fe = (size_t)r.NPAD * r.m_pad;
     std::vector<size_t> z(B_COUNT, 0);
     z[B_TILES] = (size_t)r.nt * 4;
@@ -386,6 +390,7 @@ hipError_t setup_request(gabp_server* S, Req& r) {
     d.sw.chunk = (!r.grouped && stateless && chunk_sweep(r.prec == PREC_FP32 || d.sw.part32, r.levels, r.ser, r.NB,
                                                                r.p.tile_chunk)) ? 2 : 1;
     r.chunked = d.sw.chunk > 1;
+    d.sw.split = r.chunked ? 1 : r.split;
     d.sw.partP = P(B_PARTP); d.sw.partE = P(B_PARTE);
     d.sw.st = (DevStatus*)P(B_STATUS);
     d.sw.F = F;
@@ -404,6 +409,9 @@ hipError_t setup_request(gabp_server* S, Req& r) {
 #undef CK
     return hipSuccess;
 }
+
+// Sweep item: the request's slot and the row part of the tile or entry.
+inline uint2 part_item(int slot, int part, unsigned tile) { return make_uint2((unsigned)slot | (unsigned)part << 16, tile); }
 
 inline int group_key(const Req& r) { return (r.grouped ? 1000 : 0) + r.prec * 100 + r.ser * 10 + r.levels; }
 
@@ -434,11 +442,11 @@ hipError_t rebuild_lists(gabp_server* S) {
         for (int k : G.slot_list) S->h_slots[na++] = k;
         G.ntiles = 0;
         if (G.grouped) continue;   // per-step items (build_step)
-        // items: (request, tile), or (request, Ic << 16 | Jc) for a request
+        // items: (request and row part, tile), or (request, Ic << 16 | Jc) for a request
         // whose sweeps run over 2 x 2 chunks of tiles
         auto nitems = [](const Req* r) {
             const int64_t nbc = (r->NB + 1) / 2;
-            return r->chunked ? nbc * (nbc + 1) / 2 : r->nt;
+            return r->chunked ? nbc * (nbc + 1) / 2 : r->nt * r->split;
         };
         size_t nt = 0;
         for (int k : G.slot_list) nt += (size_t)nitems(S->slots[k]);
@@ -452,7 +460,8 @@ hipError_t rebuild_lists(gabp_server* S) {
                     for (int jc = ic; jc < nbc; ++jc)
                         G.h_tiles[it++] = make_uint2((unsigned)k, ((unsigned)ic << 16) | (unsigned)jc);
             } else {
-                for (int64_t t = 0; t < r->nt; ++t) G.h_tiles[it++] = make_uint2((unsigned)k, (unsigned)t);
+                for (int64_t t = 0; t < r->nt; ++t)
+                    for (int u = 0; u < r->split; ++u) G.h_tiles[it++] = part_item(k, u, (unsigned)t);
             }
         }
         G.ntiles = (int)it;
@@ -491,8 +500,8 @@ hipError_t build_step(gabp_server* S, int k, StepPlan& P) {
         if (kv.second.grouped)
             for (int q : kv.second.slot_list) {
                 const Req* r = S->slots[q];
-                n += (size_t)(r->goff[r->gcur + 1] - r->goff[r->gcur]);
-                n += (size_t)(r->gwoff[r->gcur + 1] - r->gwoff[r->gcur]);
+                n += (size_t)(r->goff[r->gcur + 1] - r->goff[r->gcur]) * r->split;
+                n += (size_t)(r->gwoff[r->gcur + 1] - r->gwoff[r->gcur]) * r->split;
             }
     for (int q = 0; q < S->nactive; ++q) {
         int64_t b0, b1;
@@ -509,7 +518,7 @@ hipError_t build_step(gabp_server* S, int k, StepPlan& P) {
             for (int q : kv.second.slot_list) {
                 const Req* r = S->slots[q];
                 for (int64_t u = r->goff[r->gcur]; u < r->goff[r->gcur + 1]; ++u)
-                    L.h[it++] = make_uint2((unsigned)q, r->gent[(size_t)u]);
+                    for (int v = 0; v < r->split; ++v) L.h[it++] = part_item(q, v, r->gent[(size_t)u]);
             }
         P.dir.emplace_back((int64_t)start, (int)(it - start));
         start = it;
@@ -517,7 +526,7 @@ hipError_t build_step(gabp_server* S, int k, StepPlan& P) {
             for (int q : kv.second.slot_list) {
                 const Req* r = S->slots[q];
                 for (int64_t u = r->gwoff[r->gcur]; u < r->gwoff[r->gcur + 1]; ++u)
-                    L.h[it++] = make_uint2((unsigned)q, r->gwin[(size_t)u]);
+                    for (int v = 0; v < r->split; ++v) L.h[it++] = part_item(q, v, r->gwin[(size_t)u]);
             }
         P.win.emplace_back((int64_t)start, (int)(it - start));
     }

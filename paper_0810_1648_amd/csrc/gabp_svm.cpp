@@ -212,7 +212,11 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     const int m_pad = rbf ? (int)((m + 15) / 16 * 16) : 16;
     const size_t st_bytes = (prec == PREC_FP64) ? 8 : 4;
     const size_t plane = (size_t)nt * TT * st_bytes;
-    const size_t part = (size_t)NB * (NB + 1) * TILE * sizeof(double);
+    // row parts per tile of the sweeps over whole tiles
+    const bool grouped = p.schedule == GABP_SCHED_GROUPED;
+    const int G = grouped ? std::min(p.sched_groups > 0 ? p.sched_groups : 16, NB) : 1;
+    const int split = tile_split(grouped ? 2 * nt / G : nt);
+    const size_t part = (size_t)NB * part_stride(NB, split) * TILE * sizeof(double);
     size_t feat = 0;
     if (rbf) {
         switch (gram) {
@@ -534,7 +538,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     sa.chunks = h->chunks.as<uint32_t>();
     sa.nchunks = nchunks;
     sa.chunk = chunked ? 2 : 1;
-    const int nslot = chunked ? NBc : NB;
+    sa.split = chunked ? 1 : split;
     sa.st = st;
     sa.F = F;
     sa.kp = kp;
@@ -544,8 +548,6 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     // per group the single-direction entries (stateless: every message into
     // the group; stored: the tiles crossing the group boundary) and, for
     // stored records, the tiles inside the group
-    const bool grouped = p.schedule == GABP_SCHED_GROUPED;
-    const int G = grouped ? std::min(p.sched_groups > 0 ? p.sched_groups : 16, NB) : 1;
     std::vector<int64_t> g_within_off(G + 1, 0), g_dir_off(G + 1, 0), g_b0(G + 1, 0);
     if (grouped) {
         auto grp = [&](int I) { return (int)((int64_t)I * G / NB); };
@@ -594,7 +596,9 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     }
     FinalizeArgs fa{};
     fa.N = N;
-    fa.NB = nslot;
+    fa.stride = chunked ? NBc + 1 : part_stride(NB, split);
+    fa.split = sa.split;
+    fa.NB = NB;
     fa.partP = h->partP.p; fa.partE = h->partE.p;
     fa.Adiag = h->Adiag.as<double>();
     fa.y = h->yd.as<float>();
@@ -1035,6 +1039,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     // ---- sweeps: edge update + per-node gather, finalize, stop rule
     FinalizeArgs fa{};
     fa.N = N;
+    fa.stride = fa.split = 1;       // one partial per node
     fa.partP = h->partP.p; fa.partE = h->partE.p;
     fa.Adiag = h->Adiag.as<double>();
     fa.y = h->yd.as<float>();
