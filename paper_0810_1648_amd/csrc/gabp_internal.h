@@ -386,8 +386,9 @@ int64_t predict_query_pad(int64_t nq);
 constexpr size_t PREDICT_SCRATCH_BYTES = size_t(64) << 20;
 hipError_t predict_scratch(void** ptr);
 void predict_chunks(int64_t NPAD, int64_t NQPAD, int* nchunk, int* bpc);
+// w and its sums over blocks of WG rows (ceil(NPAD / WG) of them).
 hipError_t launch_predict_weights(const double* alpha, const float* y, int64_t N, int64_t NPAD, bool box,
-                                  double C, double* w, double* blk, double* wsum, hipStream_t s);
+                                  double C, double* w, double* blk, hipStream_t s);
 hipError_t launch_predict_direct(const float* Xtr, const double* w, int64_t N, int64_t m, const float* Xq,
                                  int64_t nq, double gamma, double* part, hipStream_t s);
 hipError_t launch_predict_mfma(const Features& Ft, const Features& Fq, const double* w, int64_t NPAD,
@@ -405,7 +406,15 @@ hipError_t launch_stage_aug(const float* X, const double* mean, int64_t n, int64
 hipError_t launch_predict_aug(int kind, int mp, const uint16_t* Bt, int64_t NPAD, const uint16_t* Aq, int64_t NQPAD,
                               const double* w, int nchunk, int bpc, double* part, hipStream_t s,
                               hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-hipError_t launch_predict_reduce(const double* part, int nchunk, int64_t stride, int64_t nq, const double* wsum,
+// Few queries (augmented rows): queries read and augmented by the kernel
+// itself, weights formed from alpha and y; part[nchunk][NQPAD], wpart[nchunk].
+int64_t predict_query_pad_small(int64_t nq);
+void predict_chunks_small(int64_t NPAD, int64_t NQPAD, int* nchunk, int* bpc);
+hipError_t launch_predict_small(int kind, int mp, const uint16_t* Bt, int64_t NPAD, const float* Xq, const double* mean,
+                                int64_t nq, int64_t m, const double* alpha, const float* y, int64_t N, bool box,
+                                double C, int64_t NQPAD, int nchunk, int bpc, double* part, double* wpart,
+                                hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+hipError_t launch_predict_reduce(const double* part, int nchunk, int64_t stride, int64_t nq, const double* wpart, int nw,
                                  double lam2, double* f, hipStream_t s);
 hipError_t launch_convert_agg(int prec, const void* src, double* dst, int64_t n, hipStream_t s);
 

@@ -50,8 +50,15 @@ constexpr int QB = 128;   // queries per workgroup: four waves of 32
 constexpr int AUG_FR = 2;                // augmented form: 32-query A fragments per wave
 constexpr int QBA = 4 * 32 * AUG_FR;      // augmented form: queries per workgroup
 
-// w_i = alpha_i y_i (alpha clipped to [0, C] with the box option), zero on
-// padded rows; per-block sums of w in a fixed tree order.
+// w_i = alpha_i y_i (alpha clipped to [0, C] with the box option).
+__device__ inline double weight_of(const double* __restrict__ alpha, const float* __restrict__ y, int64_t i, int box,
+                                   double C) {
+    double a = alpha[i];
+    if (box) a = fmin(fmax(a, 0.0), C);
+    return a * (double)y[i];
+}
+
+// w, zero on padded rows, and per-block sums of w in a fixed tree order.
 __global__ __launch_bounds__(WG) void k_predict_weights(const double* __restrict__ alpha,
                                                         const float* __restrict__ y, int64_t N,
                                                         int64_t NPAD, int box, double C,
@@ -59,11 +66,7 @@ __global__ __launch_bounds__(WG) void k_predict_weights(const double* __restrict
     __shared__ double sh[WG];
     const int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x;
     double v = 0.0;
-    if (i < N) {
-        double a = alpha[i];
-        if (box) a = fmin(fmax(a, 0.0), C);
-        v = a * (double)y[i];
-    }
+    if (i < N) v = weight_of(alpha, y, i, box, C);
     if (i < NPAD) w[i] = v;
     sh[threadIdx.x] = v;
     __syncthreads();
@@ -72,21 +75,6 @@ __global__ __launch_bounds__(WG) void k_predict_weights(const double* __restrict
         __syncthreads();
     }
     if (threadIdx.x == 0) blk[blockIdx.x] = sh[0];
-}
-
-// One workgroup: out[0] = sum of v[0 .. n) in a fixed order.
-__global__ __launch_bounds__(WG) void k_sum_fixed(const double* __restrict__ v, int64_t n,
-                                                  double* __restrict__ out) {
-    __shared__ double sh[WG];
-    double acc = 0.0;
-    for (int64_t k = threadIdx.x; k < n; k += WG) acc += v[k];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int o = WG / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = sh[0];
 }
 
 // FP64: one workgroup per query, direct differences of the raw features.
@@ -266,42 +254,154 @@ __global__ __launch_bounds__(WG) void k_predict_lds(Features Ft, Features Fq, co
 // (distances unchanged), and each entry is split into one, two or three
 // BF16 terms (the Gram kind's planes); n is the squared norm of the split
 // representation.  Columns past m + 1 and rows past n are zero.
-__global__ void k_stage_aug(const float* __restrict__ X, const double* __restrict__ mean, int64_t n, int64_t m,
-                            int64_t NPAD, int mp, int np, int side, float c, uint16_t* __restrict__ out,
-                            int64_t plane) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= NPAD) return;
-    uint16_t* o0 = out + i * mp;
-    uint16_t* o1 = o0 + plane;
-    uint16_t* o2 = o1 + plane;
-    auto put = [&](int k, float v) {
+//
+// One row on eight lanes (lane e of the row: columns [e mp/8, (e + 1) mp/8)):
+// the split values go to o0, o1, o2 (16 bytes of each plane at a time).  The
+// norm is one FMA chain in column order handed from lane to lane: its rounding
+// leans the way the MFMA's own accumulation of x . x does, and the two cancel
+// in d^2 (a tree of the lanes' sums, closer to the exact norm, gives f twice
+// the error: 6.8e-7 instead of 2.8e-7 at 100,000 x 100,000).
+template <int MP>
+__device__ inline void aug_row(const float* __restrict__ x, const double* __restrict__ mean, bool live, int m, int e,
+                               int np, int side, float c, uint16_t* o0, uint16_t* o1, uint16_t* o2) {
+    constexpr int CW = MP / 8;
+    float xc[CW], sv[CW];
+#pragma unroll
+    for (int j = 0; j < CW; ++j) {
+        const int k = CW * e + j;
+        xc[j] = (live && k < m) ? (float)((double)x[k] - mean[k]) : 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < CW; ++j) {
+        uint16_t h, l, l2;
+        split3(xc[j], h, l, l2);
+        sv[j] = bf2f(h) + (np >= 2 ? bf2f(l) : 0.0f) + (np >= 3 ? bf2f(l2) : 0.0f);
+    }
+    float nrm = 0.0f;
+    for (int u = 0; u < 8; ++u) {
+        float t = nrm;
+#pragma unroll
+        for (int j = 0; j < CW; ++j) t = fmaf(sv[j], sv[j], t);
+        nrm = __shfl(t, u, 8);
+    }
+    uint32_t p0[CW / 2], p1[CW / 2], p2[CW / 2];
+#pragma unroll
+    for (int j = 0; j < CW; ++j) {
+        const int k = CW * e + j;
+        float v = (side == 0) ? xc[j] : c * xc[j];
+        if (k == m) v = (side == 0) ? nrm : (live ? -0.5f * c : 0.0f);
+        if (k == m + 1) v = (side == 0) ? (live ? 1.0f : 0.0f) : -0.5f * c * nrm;
         uint16_t h, l, l2;
         split3(v, h, l, l2);
-        o0[k] = h;
-        if (np >= 2) o1[k] = l;
-        if (np >= 3) o2[k] = l2;
-    };
-    float nrm = 0.0f;
-    for (int k = 0; k < mp; ++k) {
-        const bool in = (i < n) && (k < m);
-        const float xc = in ? (float)((double)X[i * m + k] - mean[k]) : 0.0f;
-        if (k < m) {
-            uint16_t h, l, l2;
-            split3(xc, h, l, l2);
-            const float v = bf2f(h) + (np >= 2 ? bf2f(l) : 0.0f) + (np >= 3 ? bf2f(l2) : 0.0f);
-            nrm = fmaf(v, v, nrm);
+        if (j & 1) { p0[j / 2] |= (uint32_t)h << 16; p1[j / 2] |= (uint32_t)l << 16; p2[j / 2] |= (uint32_t)l2 << 16; }
+        else { p0[j / 2] = h; p1[j / 2] = l; p2[j / 2] = l2; }
+    }
+#pragma unroll
+    for (int j = 0; j < CW / 2; ++j) {
+        reinterpret_cast<uint32_t*>(o0 + CW * e)[j] = p0[j];
+        if (np >= 2) reinterpret_cast<uint32_t*>(o1 + CW * e)[j] = p1[j];
+        if (np >= 3) reinterpret_cast<uint32_t*>(o2 + CW * e)[j] = p2[j];
+    }
+}
+
+// Staged rows, eight lanes per row (one thread per row, its columns one after
+// another, took 37 us for 256 rows and 260 us for 100k; now 5 and 30 us).
+template <int MP>
+__global__ __launch_bounds__(WG) void k_stage_aug(const float* __restrict__ X, const double* __restrict__ mean, int64_t n,
+                                                  int64_t m, int64_t NPAD, int np, int side, float c,
+                                                  uint16_t* __restrict__ out, int64_t plane) {
+    const int64_t i = (int64_t)blockIdx.x * (WG / 8) + threadIdx.x / 8;
+    if (i >= NPAD) return;
+    uint16_t* o = out + i * MP;
+    aug_row<MP>(X + i * m, mean, i < n, (int)m, threadIdx.x & 7, np, side, c, o, o + plane, o + 2 * plane);
+}
+
+// Few queries: workgroup (x, y) takes the queries [32 x, 32 x + 32) and the
+// training blocks of 32 rows [bpc y, bpc (y + 1)), its four waves every fourth
+// block.  The 32 query rows are augmented straight into LDS and held as one A
+// fragment by every wave; B fragments come from memory (each is used once per
+// workgroup).  Weights are formed on the way, the chunk's sum of weights by
+// the first query block, so a call is this kernel and the reduction.  Each
+// lane adds at most 32 terms per query in FP32, then lanes and waves in FP64
+// in a fixed order.  Bound by launch and load latency: 33 queries on 20,000
+// points (7.7 MB of training rows) 10.6 us, a call 13 us (195 us as five
+// launches of the bulk form with a serial reduction).
+template <int KIND, int MP>
+__global__ __launch_bounds__(WG) void k_predict_small(const uint16_t* __restrict__ Bt, int64_t bplane,
+                                                      const float* __restrict__ Xq, const double* __restrict__ mean,
+                                                      int64_t nq, int64_t m, const double* __restrict__ alpha,
+                                                      const float* __restrict__ y, int64_t N, int box, double C,
+                                                      int64_t nblk32, int bpc, int64_t NQPAD,
+                                                      double* __restrict__ part, double* __restrict__ wpart) {
+    constexpr int NP = (KIND == GRAM_BF16X6) ? 3 : (KIND == GRAM_BF16X3) ? 2 : 1;
+    constexpr int NS = MP / 16;
+    constexpr int LD = MP + 8;                  // row pitch: the 16-byte reads of 8 rows take all banks
+    __shared__ __attribute__((aligned(16))) uint16_t sq[NP][32][LD];
+    __shared__ double sacc[4][32];
+    __shared__ double sw[4];
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, h = l >> 5, l32 = l & 31;
+    {
+        const int r = tid >> 3;
+        const int64_t q = (int64_t)blockIdx.x * 32 + r;
+        aug_row<MP>(Xq + q * m, mean, q < nq, (int)m, tid & 7, NP, 0, 0.0f, &sq[0][r][0], &sq[NP > 1 ? 1 : 0][r][0],
+                    &sq[NP > 2 ? 2 : 0][r][0]);
+    }
+    __syncthreads();
+    bf16x8 a[NP][NS];
+#pragma unroll
+    for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+        for (int st = 0; st < NS; ++st) a[pl][st] = *reinterpret_cast<const bf16x8*>(&sq[pl][l32][16 * st + 8 * h]);
+    float accf[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) accf[r] = 0.0f;
+    double ws = 0.0;
+    const int64_t b0 = (int64_t)blockIdx.y * bpc;
+    const int64_t b1 = (b0 + bpc < nblk32) ? b0 + bpc : nblk32;
+    for (int64_t b = b0 + wv; b < b1; b += 4) {
+        const int64_t row = b * 32 + l32;
+        bf16x8 bf[NP][NS];
+#pragma unroll
+        for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+            for (int st = 0; st < NS; ++st)
+                bf[pl][st] = *reinterpret_cast<const bf16x8*>(Bt + pl * bplane + row * MP + 16 * st + 8 * h);
+        const double wd = (row < N) ? weight_of(alpha, y, row, box, C) : 0.0;
+        ws += wd;
+        f32x16 g = {};
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            if constexpr (NP >= 3) {
+                g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][st], bf[2][st], g, 0, 0, 0);
+                g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2][st], bf[0][st], g, 0, 0, 0);
+                g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][st], bf[1][st], g, 0, 0, 0);
+            }
+            if constexpr (NP >= 2) {
+                g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][st], bf[1][st], g, 0, 0, 0);
+                g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][st], bf[0][st], g, 0, 0, 0);
+            }
+            g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][st], bf[0][st], g, 0, 0, 0);
         }
-        if (k < m || k >= m + 2) put(k, side == 0 ? xc : c * xc);
+        const float wj = (float)wd;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            accf[r] = fmaf(__builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(g[r]), 0.0f, 1.0f), wj, accf[r]);
     }
-    if (i >= n) nrm = 0.0f;
-    const bool live = i < n;
-    if (side == 0) {
-        put((int)m, nrm);
-        put((int)m + 1, live ? 1.0f : 0.0f);
-    } else {
-        put((int)m, live ? -0.5f * c : 0.0f);
-        put((int)m + 1, -0.5f * c * nrm);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        double v = sum16((double)accf[r]);
+        v = v + __shfl_xor(v, 16);
+        if (l32 == 0) sacc[wv][8 * (r >> 2) + 4 * h + (r & 3)] = v;
     }
+    // the 32 training rows of a block are held twice (lane halves)
+    ws = sum16(ws);
+    ws = ws + __shfl_xor(ws, 16);
+    if (l == 0) sw[wv] = ws;
+    __syncthreads();
+    if (tid < 32)
+        part[(int64_t)blockIdx.y * NQPAD + (int64_t)blockIdx.x * 32 + tid] =
+            (sacc[0][tid] + sacc[1][tid]) + (sacc[2][tid] + sacc[3][tid]);
+    if (blockIdx.x == 0 && tid == 0) wpart[blockIdx.y] = (sw[0] + sw[1]) + (sw[2] + sw[3]);
 }
 
 // Workgroup (x, y): queries [256 x, 256 x + 256), training blocks of 32 rows
@@ -445,14 +545,42 @@ __global__ __launch_bounds__(WG) void k_predict_aug(const uint16_t* __restrict__
         }
 }
 
-// f_q = sum over chunks (in order) of part[c][q] + lambda^2 sum_i w_i.
-__global__ void k_predict_reduce(const double* __restrict__ part, int nchunk, int64_t stride, int64_t nq,
-                                 const double* __restrict__ wsum, double lam2, double* __restrict__ f) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nq) return;
+// f_q = sum over chunks of part[c][q] + lambda^2 sum_i w_i (the sum of the nw
+// partial sums wpart), all in a fixed order.  Eight queries per workgroup, 32
+// lanes per query over its chunks, eight loads in flight (one thread per
+// query walking its chunks took 145 us for 33 queries of 625 chunks, now
+// 4 us).
+__global__ __launch_bounds__(WG) void k_predict_reduce(const double* __restrict__ part, int nchunk, int64_t stride,
+                                                       int64_t nq, const double* __restrict__ wpart, int nw, double lam2,
+                                                       double* __restrict__ f) {
+    __shared__ double sh[WG], sw[WG];
+    const int tid = threadIdx.x, qi = tid & 7, j = tid >> 3;
+    const int64_t q = (int64_t)blockIdx.x * 8 + qi;
+    double ws = 0.0;
+    for (int k = tid; k < nw; k += WG) ws += wpart[k];
     double acc = 0.0;
-    for (int c = 0; c < nchunk; ++c) acc += part[(int64_t)c * stride + q];
-    f[q] = acc + lam2 * wsum[0];
+    if (q < nq) {
+        int c = j;
+        for (; c + 7 * 32 < nchunk; c += 8 * 32) {
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = part[(int64_t)(c + 32 * k) * stride + q];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc += v[k];
+        }
+        for (; c < nchunk; c += 32) acc += part[(int64_t)c * stride + q];
+    }
+    sh[tid] = acc;
+    sw[tid] = ws;
+    __syncthreads();
+    for (int o = WG / 2; o > 0; o >>= 1) {
+        if (tid < o) {
+            if (o >= 8) sh[tid] += sh[tid + o];
+            sw[tid] += sw[tid + o];
+        }
+        __syncthreads();
+    }
+    if (tid < 8 && q < nq) f[q] = sh[tid] + lam2 * sw[0];
 }
 
 template <int KIND>
@@ -499,10 +627,9 @@ void predict_chunks(int64_t NPAD, int64_t NQPAD, int* nchunk, int* bpc) {
 }
 
 hipError_t launch_predict_weights(const double* alpha, const float* y, int64_t N, int64_t NPAD, bool box,
-                                  double C, double* w, double* blk, double* wsum, hipStream_t s) {
-    const unsigned nb = blocks_of(NPAD);
-    hipLaunchKernelGGL(k_predict_weights, dim3(nb), dim3(WG), 0, s, alpha, y, N, NPAD, box ? 1 : 0, C, w, blk);
-    hipLaunchKernelGGL(k_sum_fixed, dim3(1), dim3(WG), 0, s, blk, (int64_t)nb, wsum);
+                                  double C, double* w, double* blk, hipStream_t s) {
+    hipLaunchKernelGGL(k_predict_weights, dim3(blocks_of(NPAD)), dim3(WG), 0, s, alpha, y, N, NPAD, box ? 1 : 0, C, w,
+                       blk);
     return hipGetLastError();
 }
 
@@ -548,8 +675,44 @@ hipError_t launch_stage_aug(const float* X, const double* mean, int64_t n, int64
     const int np = (kind == GRAM_BF16X6) ? 3 : (kind == GRAM_BF16X3) ? 2 : 1;
     if (m + 2 > mp || (mp != 32 && mp != 64) || (kind != GRAM_BF16 && kind != GRAM_BF16X3 && kind != GRAM_BF16X6))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_stage_aug, dim3(blocks_of(NPAD)), dim3(WG), 0, s, X, mean, n, m, NPAD, mp, np, side, c, out,
-                       NPAD * mp);
+    const dim3 g((unsigned)((NPAD + WG / 8 - 1) / (WG / 8)));
+    if (mp == 32)
+        hipLaunchKernelGGL(k_stage_aug<32>, g, dim3(WG), 0, s, X, mean, n, m, NPAD, np, side, c, out, NPAD * mp);
+    else
+        hipLaunchKernelGGL(k_stage_aug<64>, g, dim3(WG), 0, s, X, mean, n, m, NPAD, np, side, c, out, NPAD * mp);
+    return hipGetLastError();
+}
+
+int64_t predict_query_pad_small(int64_t nq) { return (nq + 31) / 32 * 32; }
+
+void predict_chunks_small(int64_t NPAD, int64_t NQPAD, int* nchunk, int* bpc) {
+    // four blocks (one per wave) or a multiple of it, about 512 workgroups,
+    // and at most 32 blocks per wave (FP32 partial sums)
+    const int64_t nblk32 = NPAD / 32, nqb = NQPAD / 32;
+    int64_t per = (nblk32 * nqb + 4 * 512 - 1) / (4 * 512);
+    per = 4 * std::max<int64_t>(1, std::min<int64_t>(per, 32));
+    *bpc = (int)per;
+    *nchunk = (int)((nblk32 + per - 1) / per);
+}
+
+hipError_t launch_predict_small(int kind, int mp, const uint16_t* Bt, int64_t NPAD, const float* Xq, const double* mean,
+                                int64_t nq, int64_t m, const double* alpha, const float* y, int64_t N, bool box,
+                                double C, int64_t NQPAD, int nchunk, int bpc, double* part, double* wpart,
+                                hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (NQPAD % 32 != 0 || NPAD % 32 != 0 || m + 2 > mp) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(NQPAD / 32), (unsigned)nchunk);
+    const int64_t nblk32 = NPAD / 32, bp = NPAD * mp;
+#define GABP_SMALL(K, M) launch_ev(k_predict_small<K, M>, grid, dim3(WG), s, e0, e1, Bt, bp, Xq, mean, nq, m, alpha, y, N, box ? 1 : 0, C, nblk32, bpc, NQPAD, part, wpart)
+    switch (mp * 8 + kind) {
+        case 32 * 8 + GRAM_BF16: GABP_SMALL(GRAM_BF16, 32); break;
+        case 32 * 8 + GRAM_BF16X3: GABP_SMALL(GRAM_BF16X3, 32); break;
+        case 32 * 8 + GRAM_BF16X6: GABP_SMALL(GRAM_BF16X6, 32); break;
+        case 64 * 8 + GRAM_BF16: GABP_SMALL(GRAM_BF16, 64); break;
+        case 64 * 8 + GRAM_BF16X3: GABP_SMALL(GRAM_BF16X3, 64); break;
+        case 64 * 8 + GRAM_BF16X6: GABP_SMALL(GRAM_BF16X6, 64); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef GABP_SMALL
     return hipGetLastError();
 }
 
@@ -581,10 +744,10 @@ hipError_t launch_predict_aug(int kind, int mp, const uint16_t* Bt, int64_t NPAD
     return hipGetLastError();
 }
 
-hipError_t launch_predict_reduce(const double* part, int nchunk, int64_t stride, int64_t nq, const double* wsum,
+hipError_t launch_predict_reduce(const double* part, int nchunk, int64_t stride, int64_t nq, const double* wpart, int nw,
                                  double lam2, double* f, hipStream_t s) {
-    hipLaunchKernelGGL(k_predict_reduce, dim3(blocks_of(nq)), dim3(WG), 0, s, part, nchunk, stride, nq, wsum,
-                       lam2, f);
+    hipLaunchKernelGGL(k_predict_reduce, dim3((unsigned)((nq + 7) / 8)), dim3(WG), 0, s, part, nchunk, stride, nq, wpart,
+                       nw, lam2, f);
     return hipGetLastError();
 }
 

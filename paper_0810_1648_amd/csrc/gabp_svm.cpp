@@ -1360,11 +1360,19 @@ namespace {
 // uses (FP64 direct differences; augmented BF16 rows; FP32 or BF16 rows
 // with norms).
 struct PredictPlan {
-    int form = 0;                 // 0 direct FP64, 1 augmented rows, 2 rows + norms
+    int form = 0;                 // 0 direct FP64, 1 augmented rows, 2 rows + norms, 3 augmented rows, few queries
     int kind = 0, mp = 0, np = 0, nc = 1, bp = 1;
     int64_t qpad = 0;
-    size_t o_w = 0, o_blk = 0, o_ws = 0, o_part = 0, o_nrm = 0, o_q0 = 0, o_q1 = 0, o_q2 = 0, bytes = 0;
+    size_t o_w = 0, o_blk = 0, o_part = 0, o_nrm = 0, o_q0 = 0, o_q1 = 0, o_q2 = 0, bytes = 0;
 };
+
+// Few queries (form 3): one launch re-reads the staged training rows for
+// every 32 queries, the bulk form for every 256 but with two more launches
+// and a start of its own.  Measured on 60,000 points: 33 queries 19 against
+// 49 us, 512 53 against 81, 768 75 against 78, 1,024 94 both, 2,048 194
+// against 129; on 20,000 points 2,048 queries 66 against 68, on 4,000 21
+// against 31.  Up to 32 queries the rows are read once in either form.
+bool few_queries(int64_t nb, int64_t NPAD) { return nb <= 32 || nb * NPAD <= 45000000; }
 
 PredictPlan predict_plan(const gabp_svm* h, int64_t nb) {
     PredictPlan P;
@@ -1373,7 +1381,6 @@ PredictPlan predict_plan(const gabp_svm* h, int64_t nb) {
     const int64_t NPAD = h->NPAD;
     P.o_w = seg((size_t)NPAD * 8);
     P.o_blk = seg((size_t)(NPAD / WG + 1) * 8);
-    P.o_ws = seg(64);
     if (h->prec == PREC_FP64) {
         P.form = 0;
         P.qpad = nb;
@@ -1383,6 +1390,15 @@ PredictPlan predict_plan(const gabp_svm* h, int64_t nb) {
         P.kind = h->aug_kind;
         P.mp = h->aug_mp;
         P.np = (P.kind == GRAM_BF16X6) ? 3 : (P.kind == GRAM_BF16X3) ? 2 : 1;
+        if (few_queries(nb, NPAD)) {
+            P.form = 3;
+            P.qpad = predict_query_pad_small(nb);
+            predict_chunks_small(NPAD, P.qpad, &P.nc, &P.bp);
+            // (the chunks' sums of weights take the place of the block sums)
+            P.o_part = seg((size_t)P.nc * (P.qpad + 1) * 8);
+            P.bytes = off;
+            return P;
+        }
         P.qpad = predict_query_pad_aug(nb);
         predict_chunks_aug(NPAD, P.qpad, &P.nc, &P.bp);
         P.o_part = seg((size_t)P.nc * P.qpad * 8);
@@ -1406,10 +1422,11 @@ PredictPlan predict_plan(const gabp_svm* h, int64_t nb) {
 }
 
 gabp_status predict_weights(gabp_svm* h, char* base, const PredictPlan& P, hipStream_t s) {
+    if (P.form == 3) return GABP_OK;    // the kernel forms them
     HIPCHK(h, launch_predict_weights(h->alpha_d.as<double>(), h->yd.as<float>(), h->N, h->NPAD,
                                      h->p.box_mode == GABP_BOX_CLIP_OUTPUT, h->p.C,
                                      reinterpret_cast<double*>(base + P.o_w), reinterpret_cast<double*>(base + P.o_blk),
-                                     reinterpret_cast<double*>(base + P.o_ws), s));
+                                     s));
     return GABP_OK;
 }
 
@@ -1418,14 +1435,24 @@ gabp_status predict_weights(gabp_svm* h, char* base, const PredictPlan& P, hipSt
 gabp_status predict_batch(gabp_svm* h, const PredictPlan& P, char* base, const float* xqd, int64_t nb, double* fd,
                           hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const double* w = reinterpret_cast<const double*>(base + P.o_w);
-    const double* wsum = reinterpret_cast<const double*>(base + P.o_ws);
+    const double* wblk = reinterpret_cast<const double*>(base + P.o_blk);
+    const int nw = (int)((h->NPAD + WG - 1) / WG);
     double* part = reinterpret_cast<double*>(base + P.o_part);
     const double lam2 = h->lam * h->lam;
     if (P.form == 0) {
         if (e0) HIPCHK(h, hipEventRecord(e0, s));
         HIPCHK(h, launch_predict_direct(h->Xin.as<float>(), w, h->N, h->m, xqd, nb, h->p.gamma, part, s));
         if (e1) HIPCHK(h, hipEventRecord(e1, s));
-        HIPCHK(h, launch_predict_reduce(part, 1, nb, nb, wsum, lam2, fd, s));
+        HIPCHK(h, launch_predict_reduce(part, 1, nb, nb, wblk, nw, lam2, fd, s));
+        return GABP_OK;
+    }
+    if (P.form == 3) {
+        double* wpart = part + (size_t)P.nc * P.qpad;
+        HIPCHK(h, launch_predict_small(P.kind, P.mp, h->xaug.as<uint16_t>(), h->NPAD, xqd, h->mean.as<double>(), nb, h->m,
+                                       h->alpha_d.as<double>(), h->yd.as<float>(), h->N,
+                                       h->p.box_mode == GABP_BOX_CLIP_OUTPUT, h->p.C, P.qpad, P.nc, P.bp, part, wpart, s,
+                                       e0, e1));
+        HIPCHK(h, launch_predict_reduce(part, P.nc, P.qpad, nb, wpart, P.nc, lam2, fd, s));
         return GABP_OK;
     }
     if (P.form == 1) {
@@ -1434,7 +1461,7 @@ gabp_status predict_batch(gabp_svm* h, const PredictPlan& P, char* base, const f
         // the events take the kernel dispatch's own timestamps
         HIPCHK(h, launch_predict_aug(P.kind, P.mp, h->xaug.as<uint16_t>(), h->NPAD, q, P.qpad, w, P.nc, P.bp, part, s,
                                      e0, e1));
-        HIPCHK(h, launch_predict_reduce(part, P.nc, P.qpad, nb, wsum, lam2, fd, s));
+        HIPCHK(h, launch_predict_reduce(part, P.nc, P.qpad, nb, wblk, nw, lam2, fd, s));
         return GABP_OK;
     }
     Features Ft{}, Fq{};
@@ -1452,7 +1479,7 @@ gabp_status predict_batch(gabp_svm* h, const PredictPlan& P, char* base, const f
     if (e0) HIPCHK(h, hipEventRecord(e0, s));
     HIPCHK(h, launch_predict_mfma(Ft, Fq, w, h->NPAD, P.qpad, c, P.nc, P.bp, part, s));
     if (e1) HIPCHK(h, hipEventRecord(e1, s));
-    HIPCHK(h, launch_predict_reduce(part, P.nc, P.qpad, nb, wsum, lam2, fd, s));
+    HIPCHK(h, launch_predict_reduce(part, P.nc, P.qpad, nb, wblk, nw, lam2, fd, s));
     return GABP_OK;
 }
 
