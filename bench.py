@@ -377,7 +377,7 @@ def sparse_bench(torch, gabp, inputs, n, tau, steps=2, warmup=1):
             "edges": E, "mean_degree": 2.0 * E / n, "sweeps_per_s": sweeps / wall, "solves_per_s": steps / wall,
             "sweeps_per_solve": info["sweeps_per_solve"], "reason": info["reason"],
             "graph_build_ms": tm["kbuild_ms"], "sweep_loop_ms": tm["sweep_loop_ms"],
-            "roofline": {"bound": "hbm", "kernel": "k_sp_sweep + k_sp_gather", "achieved": ach,
+            "roofline": {"bound": "hbm", "kernel": "k_sp_sweep + k_sp_join", "achieved": ach,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS if ach else None,
                          "avg_launch_ms": avg, "alg_bytes_per_edge": plan["alg_bytes_per_pair"],
                          "alg_bytes_per_launch": plan["alg_bytes_per_sweep"]}}

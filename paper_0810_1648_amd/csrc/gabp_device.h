@@ -157,6 +157,40 @@ __device__ inline double block_max(double v, double* sh4) {
     return v;
 }
 
+// Stop rule (Algorithm 2 step "Check", tested on alpha).
+__device__ inline void status_update(int nblk, const double* __restrict__ bd,
+                                     const double* __restrict__ ba, DevStatus* st,
+                                     double* __restrict__ trace, const StopRule& rule) {
+    __shared__ double sh4[4];
+    double d = 0.0, a = 0.0;
+    for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
+        d = fmax(d, load_agent(bd + k));
+        a = fmax(a, load_agent(ba + k));
+    }
+    d = block_max(d, sh4);
+    a = block_max(a, sh4);
+    if (threadIdx.x == 0) {
+        const int t = st->t + 1;
+        st->t = t;
+        st->delta = d;
+        st->amax = a;
+        trace[t - 1] = d;
+        if (load_agent(&st->bad)) {
+            st->done = 1; st->reason = R_DIVERGED;
+        } else if (d <= rule.tol_abs + rule.tol_rel * a) {
+            st->done = 1; st->reason = R_CONVERGED;
+        } else {
+            if (d < st->best_delta) { st->best_delta = d; st->since_best = 0; }
+            else st->since_best = st->since_best + 1;
+            if (rule.stag_window > 0 && st->since_best >= rule.stag_window && d <= rule.stag_rel * a) {
+                st->done = 1; st->reason = R_STAGNATED;
+            } else if (t >= rule.max_sweeps) {
+                st->done = 1; st->reason = R_MAX_SWEEPS;
+            }
+        }
+    }
+}
+
 __device__ inline uint16_t f2bf(float f) {  // round to nearest even
     uint32_t u = __float_as_uint(f);
     u += 0x7FFFu + ((u >> 16) & 1u);
@@ -183,6 +217,14 @@ __device__ inline double rcp_fast(double x) {
     e = fma(-x, r, 1.0);
     r = fma(r, e, r);
     return __builtin_isinf(x) ? 0.0 : r;    // 1/inf = 0 (Newton would give NaN)
+}
+
+// ... of a finite positive argument.
+__device__ inline float rcp_pos(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ inline double rcp_pos(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
 }
 
 // Workgroups go to the eight XCDs in turn (workgroup b to XCD b mod 8).

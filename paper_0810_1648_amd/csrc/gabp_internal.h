@@ -315,13 +315,13 @@ hipError_t launch_sweep_grouped_f64(int ksrc, int gram, int levels, int ser, con
 // sweep (edge update + per-node gather into one partial per node).
 // count: kept pairs of tiles[0], tiles[stride], ... (ntiles launched);
 // fill: every listed tile's kept pairs appended at *cursor (slots >= cap
-// counted, not written).
+// counted, not written), keys i << sh | j.
 // FA, FB: the augmented A and B rows (launch_sp_augment), whose Gram is
 // -d^2 / 2.
 hipError_t launch_sp_count(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles,
                            int64_t stride, int64_t N, float cut, int32_t* counts, hipStream_t s);
 hipError_t launch_sp_fill(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles, int64_t N,
-                          float cut, float neg_gamma_log2e, float lam2, int64_t cap, unsigned long long* cursor,
+                          float cut, float neg_gamma_log2e, float lam2, int64_t cap, unsigned long long* cursor, int sh,
                           uint64_t* keys, float* kv, hipStream_t s);
 // Columns m, m + 1 (< m_pad) of the staged rows: A planes (n_i, 1), B planes
 // the first m columns of A and (-1/2, -n_i/2); NPAD rows.
@@ -347,19 +347,46 @@ hipError_t sp_select(void* tmp, size_t* bytes, const uint32_t* in, const uint8_t
                      int64_t* nsel, int64_t n, hipStream_t s);
 hipError_t launch_sp_unpermute(const double* in, const int32_t* order, int64_t N, double* out, hipStream_t s);
 hipError_t sp_sort_keys(void* tmp, size_t* bytes, const uint64_t* kin, uint64_t* kout, const float* vin,
-                        float* vout, int64_t n, hipStream_t s);
+                        float* vout, int64_t n, int bits, hipStream_t s);
 hipError_t sp_sort_ids(void* tmp, size_t* bytes, const uint64_t* kin, uint64_t* kout, const int32_t* vin,
                        int32_t* vout, int64_t n, hipStream_t s);
-hipError_t launch_sp_unpack(const uint64_t* keys, int64_t E, int32_t* ei, int32_t* ej, int32_t* deg_i,
-                            int32_t* deg_j, uint64_t* keys_t, int32_t* ids, hipStream_t s);
-hipError_t launch_sp_rowsum(int64_t N, const int64_t* off_i, const int64_t* off_j, const int32_t* perm,
-                            const float* kv, double* psum, double* pmax, hipStream_t s);
-// PS: 2 N aggregates packed (P~, S); RF / RB: 2 E records packed (P, E) of
-// the messages i -> j / j -> i of every edge.
-hipError_t launch_sp_sweep(int prec, int64_t E, int64_t N, const int32_t* ei, const int32_t* ej, const float* kv,
-                           const void* Pt, const void* S, void* PS, void* RF, void* RB, const int64_t* off_i,
-                           const int64_t* off_j, const int32_t* perm, void* partP, void* partE, DevStatus* st,
-                           hipStream_t s);
+hipError_t launch_sp_unpack(const uint64_t* keys, int64_t E, int sh, int32_t* ei, int32_t* ej, uint64_t* keys_t,
+                            hipStream_t s);
+// First position of every node in sorted keys (node = key >> sh; N + 1 values).
+hipError_t launch_sp_offsets(const uint64_t* keys, int64_t E, int sh, int64_t N, int64_t* off, hipStream_t s);
+// Row lengths (N + 1 values, the last 0) in whole quads, at least one, and
+// the rows of all nodes (neighbour, K') from row[k] (the exclusive sums of the
+// lengths), a node's i-end edges first; at most 2 E + 4 N entries.  qrow: the
+// node of every quad.
+hipError_t launch_sp_rowlen(int64_t N, const int64_t* off_i, const int64_t* off_j, int32_t* len, hipStream_t s);
+hipError_t launch_sp_rows(int64_t E, int64_t N, int sh, const int32_t* ei, const int32_t* ej, const float* kv,
+                          const uint64_t* keys_t, const float* kv_t, const int64_t* off_i, const int64_t* off_j,
+                          const int64_t* row, int32_t* col, float* rkv, int32_t* qrow, hipStream_t s);
+hipError_t launch_sp_rowsum(int64_t N, const int64_t* row, const float* kv, double* psum, double* pmax, hipStream_t s);
+// (P~, S) pairs from the separate aggregates, and P~ back out of the pairs.
+hipError_t launch_sp_pack(int prec, int64_t N, const void* Pt, const void* S, void* PS, hipStream_t s);
+hipError_t launch_sp_unpack_p(int prec, int64_t N, const void* PS, double* P, hipStream_t s);
+// Sweep t = 1, 2, ... over the rows with its stop rule: rec[t & 1] holds the
+// packed (P, E) messages into every node of sweep t - 2 and takes sweep t's,
+// PS[t & 1] the packed aggregates likewise; PS[(t - 1) & 1] those of sweep
+// t - 1.  dmax / amax: 256 doubles each, zero before the first sweep; edge:
+// four aggregates per 256 quads.
+struct SparseSweep {
+    int64_t nq;                  // quads of all rows
+    const int64_t* row;
+    const int32_t *qrow, *col;
+    void* edge;
+    const float* kv;
+    void* rec[2];
+    void* PS[2];
+    const double* Adiag;
+    const float* y;
+    double *alpha, *dmax, *amax, *trace;
+    DevStatus* st;
+    double boxC;
+    StopRule rule;
+};
+hipError_t launch_sp_sweep(int prec, const SparseSweep& a, int t, hipStream_t s);
 // A-priori contraction bound: one[0] = -m* (minus the aggregate lower
 // bound), one[1] = rho (+inf when no bound exists).
 hipError_t launch_rho_bound(int64_t N, const double* Adiag, const double* rowmax, const double* rsum,

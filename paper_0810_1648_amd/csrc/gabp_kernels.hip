@@ -634,40 +634,6 @@ __global__ void k_init(int64_t N, int64_t NPAD, int R, const double* __restrict_
     }
 }
 
-// Stop rule (Algorithm 2 step "Check", tested on alpha).
-__device__ inline void status_update(int nblk, const double* __restrict__ bd,
-                                     const double* __restrict__ ba, DevStatus* st,
-                                     double* __restrict__ trace, const StopRule& rule) {
-    __shared__ double sh4[4];
-    double d = 0.0, a = 0.0;
-    for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
-        d = fmax(d, load_agent(bd + k));
-        a = fmax(a, load_agent(ba + k));
-    }
-    d = block_max(d, sh4);
-    a = block_max(a, sh4);
-    if (threadIdx.x == 0) {
-        const int t = st->t + 1;
-        st->t = t;
-        st->delta = d;
-        st->amax = a;
-        trace[t - 1] = d;
-        if (load_agent(&st->bad)) {
-            st->done = 1; st->reason = R_DIVERGED;
-        } else if (d <= rule.tol_abs + rule.tol_rel * a) {
-            st->done = 1; st->reason = R_CONVERGED;
-        } else {
-            if (d < st->best_delta) { st->best_delta = d; st->since_best = 0; }
-            else st->since_best = st->since_best + 1;
-            if (rule.stag_window > 0 && st->since_best >= rule.stag_window && d <= rule.stag_rel * a) {
-                st->done = 1; st->reason = R_STAGNATED;
-            } else if (t >= rule.max_sweeps) {
-                st->done = 1; st->reason = R_MAX_SWEEPS;
-            }
-        }
-    }
-}
-
 // Aggregates of the FB nodes of finalize block `blk` from the partial sums
 // (fixed order), the new alpha and the block's change / magnitude maxima.
 // boxC > 0: the belief mean is clipped to [0, boxC] (alpha space) and S is

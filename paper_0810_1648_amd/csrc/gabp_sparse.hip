@@ -9,16 +9,16 @@
 //   k_sp_augment the A and B rows of the build;
 //   k_sp_count  kept pairs i < j of every 32nd tile: an estimate that sizes
 //               the fill's output;
-//   k_sp_fill   per tile: 64-bit keys (i << 32 | j) and K' appended at a
-//               global cursor (arbitrary order); a second pass runs only if
-//               the estimate fell short;
+//   k_sp_fill   per tile: keys (i << sh | j) and K' appended at a global
+//               cursor (arbitrary order); a second pass runs only if the
+//               estimate fell short;
 //   radix sort of the keys: edges in (i, j) order, so every node's edges
-//   with the node as i-end are contiguous; a second sort by (j, i) gives
-//   the permutation listing each node's edges as j-end.
-// Sweep (Algorithm 2, synchronous, information form): one thread per edge
-// updates both directions from the previous records and aggregates;
-// sixteen lanes per node add its incoming messages in a fixed order (its
-// i-end edges, then its j-end edges), so every result is reproducible.
+//   with the node as i-end are contiguous; a second sort by (j, i) lists
+//   each node's edges as j-end; k_sp_rows puts both ends of every node
+//   together as its row (neighbour, K'), j-ends after i-ends.
+// Sweep (Algorithm 2, synchronous, information form), by rows: a row's
+// records are the messages INTO its node, so everything a node needs lies in
+// its row except its neighbours' aggregates (k_sp_sweep).
 #include "gabp_device.h"
 
 #include <hipcub/hipcub.hpp>
@@ -145,7 +145,7 @@ template <int KIND, int MP>
 __global__ __launch_bounds__(WG) void k_sp_fill(Features FA, Features FB, const uint32_t* __restrict__ tiles,
                                                 int64_t ntiles, int64_t N,
                                                 float cut, float neg_gamma_log2e, float lam2, int64_t cap,
-                                                unsigned long long* __restrict__ cursor,
+                                                unsigned long long* __restrict__ cursor, int sh,
                                                 uint64_t* __restrict__ keys, float* __restrict__ kv) {
     constexpr int BW = 512;   // entries buffered per wave
     __shared__ uint64_t bkey[4][BW];
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(WG) void k_sp_fill(Features FA, Features FB, const 
                 if ((mask >> l) & 1ull) {
                     const int k = n + __popcll(mask & below);
                     const int64_t i = ib + 128 * half + 8 * (r >> 2) + 4 * h + (r & 3);
-                    bkey[w][k] = ((uint64_t)i << 32) | (uint64_t)j;
+                    bkey[w][k] = ((uint64_t)i << sh) | (uint64_t)j;
                     bval[w][k] = __builtin_amdgcn_exp2f(neg_gamma_log2e * fmaxf(-2.0f * gv, 0.0f)) + lam2;
                 }
                 n += __popcll(mask);
@@ -211,40 +211,80 @@ __global__ __launch_bounds__(WG) void k_sp_fill(Features FA, Features FB, const 
     drain(wbase[w]);
 }
 
-// i, j of every sorted edge; node degrees as i-end and as j-end.
-__global__ void k_sp_unpack(const uint64_t* __restrict__ keys, int64_t E, int32_t* __restrict__ ei,
-                            int32_t* __restrict__ ej, int32_t* __restrict__ deg_i, int32_t* __restrict__ deg_j,
-                            uint64_t* __restrict__ keys_t, int32_t* __restrict__ ids) {
+// Ends of every edge in (i, j) order, and the keys of the (j, i) order.
+__global__ void k_sp_unpack(const uint64_t* __restrict__ keys, int64_t E, int sh, int32_t* __restrict__ ei,
+                            int32_t* __restrict__ ej, uint64_t* __restrict__ keys_t) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= E) return;
     const uint64_t k = keys[e];
-    const int32_t i = (int32_t)(k >> 32), j = (int32_t)(k & 0xFFFFFFFFull);
+    const int32_t i = (int32_t)(k >> sh), j = (int32_t)(k & ((1ull << sh) - 1ull));
     ei[e] = i;
     ej[e] = j;
-    atomicAdd(&deg_i[i], 1);
-    atomicAdd(&deg_j[j], 1);
-    keys_t[e] = ((uint64_t)j << 32) | (uint64_t)i;
-    ids[e] = (int32_t)e;
+    keys_t[e] = ((uint64_t)j << sh) | (uint64_t)i;
 }
 
-// Row sums and maxima of K' over each node's edges (the sparse r_i), written
+// off[k] = first position whose key's node (key >> sh) is >= k, k = 0 .. N:
+// every position fills the nodes that begin at it.
+__global__ void k_sp_offsets(const uint64_t* __restrict__ keys, int64_t E, int sh, int64_t N, int64_t* __restrict__ off) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e > E) return;
+    const int64_t lo = (e > 0) ? (int64_t)(keys[e - 1] >> sh) + 1 : 0;
+    const int64_t hi = (e < E) ? (int64_t)(keys[e] >> sh) : N;
+    for (int64_t k = lo; k <= hi; ++k) off[k] = e;
+}
+
+// Row lengths: a node's edges of both ends in whole quads, at least one.
+__global__ void k_sp_rowlen(int64_t N, const int64_t* __restrict__ off_i, const int64_t* __restrict__ off_j,
+                            int32_t* __restrict__ len) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k > N) return;
+    const int64_t d = (k < N) ? (off_i[k + 1] - off_i[k]) + (off_j[k + 1] - off_j[k]) : 0;
+    len[k] = (k < N) ? (d > 0 ? (int32_t)((d + 3) / 4 * 4) : 4) : 0;
+}
+
+// Rows (neighbour, K'): node k's row begins at row[k] with its i-end edges,
+// then its j-end edges; its last quad is filled up with the node itself and
+// K' = 0, whose messages are zero.  qrow names the node of every quad.
+// Thread e places edge e of both orders; thread k < N fills row k's end and
+// names its quads.
+__global__ void k_sp_rows(int64_t E, int64_t N, int sh, const int32_t* __restrict__ ei, const int32_t* __restrict__ ej,
+                          const float* __restrict__ kv, const uint64_t* __restrict__ keys_t,
+                          const float* __restrict__ kv_t, const int64_t* __restrict__ off_i,
+                          const int64_t* __restrict__ off_j, const int64_t* __restrict__ row, int32_t* __restrict__ col,
+                          float* __restrict__ rkv, int32_t* __restrict__ qrow) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < E) {
+        const int64_t i = ei[e], a = row[i] + (e - off_i[i]);
+        col[a] = ej[e];
+        rkv[a] = kv[e];
+        const uint64_t k = keys_t[e];
+        const int64_t j = (int64_t)(k >> sh), b = row[j] + (off_i[j + 1] - off_i[j]) + (e - off_j[j]);
+        col[b] = (int32_t)(k & ((1ull << sh) - 1ull));
+        rkv[b] = kv_t[e];
+    }
+    if (e < N) {
+        for (int64_t a = row[e] / 4; a < row[e + 1] / 4; ++a) qrow[a] = (int32_t)e;
+        for (int64_t a = row[e] + (off_i[e + 1] - off_i[e]) + (off_j[e + 1] - off_j[e]); a < row[e + 1]; ++a) {
+            col[a] = (int32_t)e;
+            rkv[a] = 0.0f;
+        }
+    }
+}
+
+// Row sums and maxima of K' over each node's row (the sparse r_i), written
 // as one partial per node (the dense layout with a single slot); sixteen
-// lanes per node as in k_sp_gather.
-__global__ __launch_bounds__(WG) void k_sp_rowsum(int64_t N, const int64_t* __restrict__ off_i,
-                                                  const int64_t* __restrict__ off_j,
-                                                  const int32_t* __restrict__ perm, const float* __restrict__ kv,
-                                                  double* __restrict__ psum, double* __restrict__ pmax) {
+// lanes per node as in k_sp_sweep.
+__global__ __launch_bounds__(WG) void k_sp_rowsum(int64_t N, const int64_t* __restrict__ row,
+                                                  const float* __restrict__ kv, double* __restrict__ psum,
+                                                  double* __restrict__ pmax) {
     const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
     const int q = threadIdx.x & 15;
     double s = 0.0, m = 0.0;
-    if (k < N) {
-        for (int64_t e = off_i[k] + q; e < off_i[k + 1]; e += 16) { s += (double)kv[e]; m = fmax(m, (double)kv[e]); }
-        for (int64_t t = off_j[k] + q; t < off_j[k + 1]; t += 16) {
-            const double v = (double)kv[perm[t]];
-            s += v;
-            m = fmax(m, v);
+    if (k < N)
+        for (int64_t e = row[k] + q, r1 = row[k + 1]; e < r1; e += 16) {
+            s += (double)kv[e];
+            m = fmax(m, (double)kv[e]);
         }
-    }
     s = sum16(s);
     m = fmax(m, dpp<0xB1>(m));
     m = fmax(m, dpp<0x4E>(m));
@@ -254,95 +294,204 @@ __global__ __launch_bounds__(WG) void k_sp_rowsum(int64_t N, const int64_t* __re
 }
 
 // Aggregates of every node packed as (P~, S) pairs, so that the sweep's
-// reads of a random neighbour fetch one 8- or 16-byte item.
+// reads of a random neighbour fetch one 8- or 16-byte item (the start of the
+// solve; the sweeps write them packed).
 template <class AT>
-__global__ void k_sp_pack(int64_t N, const AT* __restrict__ Pt, const AT* __restrict__ S, AT* __restrict__ PS,
-                          const DevStatus* st) {
-    if (st->done) return;
+__global__ void k_sp_pack(int64_t N, const AT* __restrict__ Pt, const AT* __restrict__ S, AT* __restrict__ PS) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < N) { PS[2 * k] = Pt[k]; PS[2 * k + 1] = S[k]; }
 }
+template <class AT>
+__global__ void k_sp_unpack_p(int64_t N, const AT* __restrict__ PS, double* __restrict__ P) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < N) P[k] = (double)PS[2 * k];
+}
 
-// One synchronous sweep over the edges: both directions of edge (i, j) from
-// the previous records and aggregates.  Records are (P, E) pairs: RF[e] the
-// message i -> j, RB[e] the message j -> i (ST), aggregates (P~, S) pairs
-// (AT), arithmetic in MT.
-template <class ST, class MT, class AT>
-__global__ __launch_bounds__(WG) void k_sp_sweep(int64_t E, const int32_t* __restrict__ ei,
-                                                 const int32_t* __restrict__ ej, const float* __restrict__ kv,
-                                                 const AT* __restrict__ PS, ST* __restrict__ RF,
-                                                 ST* __restrict__ RB, DevStatus* st) {
-    if (st->done) return;
-    const int64_t e = xcd_contiguous(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+constexpr int SP_MAXS = 256;   // slots of the sweep's change / magnitude maxima
+
+// New aggregates and alpha of node k from the sums of its messages; d and am
+// take its change and magnitude.  Returns false when the node diverged.
+template <class AT>
+__device__ inline bool sp_node(int64_t k, AT sp, AT se, const SparseSweep& a, AT* __restrict__ PS, double& d, double& am) {
+    const double yk = (double)a.y[k];
+    const AT p = (AT)a.Adiag[k] + sp;
+    AT s = (AT)a.y[k] + se;
+    double an = (double)(s / p) * yk;
+    const bool ok = p > (AT)0 && isfinite((double)p) && isfinite((double)s);
+    if (a.boxC > 0.0) {
+        an = fmin(fmax(an, 0.0), a.boxC);
+        s = p * (AT)(an * yk);
+    }
+    PS[2 * k] = p;
+    PS[2 * k + 1] = s;
+    d = fmax(d, fabs(an - a.alpha[k]));
+    am = fmax(am, fabs(an));
+    a.alpha[k] = an;
+    return ok;
+}
+
+// Change and magnitude maxima of a workgroup into the sweep's slots by
+// integer maximum (non-negative doubles order as their bits), which no order
+// of arrival changes.
+__device__ inline void sp_maxima(double d, double am, const SparseSweep& a) {
+    __shared__ double sh4[4];
+    d = block_max(d, sh4);
+    am = block_max(am, sh4);
+    if (threadIdx.x == 0) {
+        atomicMax(reinterpret_cast<unsigned long long*>(a.dmax) + blockIdx.x % SP_MAXS,
+                  (unsigned long long)__double_as_longlong(d));
+        atomicMax(reinterpret_cast<unsigned long long*>(a.amax) + blockIdx.x % SP_MAXS,
+                  (unsigned long long)__double_as_longlong(am));
+    }
+}
+
+// Sweep t (1, 2, ...): workgroup w takes the quads [256 w, 256 w + 256) of
+// the rows, one per thread, whatever rows they belong to (degrees spread over
+// three decades, and sixteen lanes per row left most of them waiting for the
+// longest row: 2.3 ms per sweep at 90.8 M edges).
+//
+// The message j -> k of sweep t needs the reverse message k -> j of sweep
+// t - 1, which lies in the row of j; but k -> j of sweep t - 1 follows from
+// node k's own aggregates of sweep t - 2 and the message j -> k of sweep
+// t - 2, which lies here.  So each row keeps the messages into its node by
+// the parity of the sweep (rec: those of sweep t - 2, overwritten with sweep
+// t's), and nothing is scattered or gathered but the neighbours' packed
+// aggregates: 25 bytes per directed edge in row order and one 16-byte read
+// that the locality order keeps in L2.  With q = P~_k - P_jk of the older
+// pair, P_kj = -a^2 / q and E_kj = -a (S_k - E_jk) / q, both new messages
+// follow from one reciprocal:
+//   P_jk = -a^2 q / D,  E_jk = -a (S_j q + a (S_k - E_jk)) / D,  D = P~_j q + a^2
+// (q > 0 was checked as the reverse message's own cavity one sweep earlier,
+// so the cavity P~_j - P_kj = D / q is positive where D is).
+// (Records per edge updated by one thread and gathered by node through a
+// permutation moved 12.1 GB per sweep at 90.8 M edges, 2.63 ms with their five
+// launches; this is 4.5 GB and 1.75 ms, 0.65 of them the neighbours' reads.
+// At 3.65 M edges 101 -> 69 us.)
+// FIRST: sweep 1, whose reverse messages are zero.  Sweep 2's older messages
+// are those of sweep 0, zero too.
+//
+// The quads' sums meet in LDS: sixteen lanes add a row's quads in a fixed
+// tree, one thread per row forms its node.  A row that leaves the workgroup's
+// range puts its sum into the workgroup's head (begun earlier) or tail slot
+// of `edge` for k_sp_join.
+template <class ST, class MT, class AT, bool FIRST>
+__global__ __launch_bounds__(WG) void k_sp_sweep(SparseSweep a, int t) {
+    if (a.st->done) return;
+    typedef ST Rec2 __attribute__((ext_vector_type(4)));          // two records
+    typedef int32_t Int4 __attribute__((ext_vector_type(4)));
+    typedef AT AggT __attribute__((ext_vector_type(2)));
+    __shared__ AT qP[WG], qE[WG], rowP[WG], rowE[WG];
+    const int par = t & 1, tid = threadIdx.x;
+    const AggT* const A1 = static_cast<const AggT*>(a.PS[par ^ 1]);
+    AT* const PS2 = static_cast<AT*>(a.PS[par]);
+    const int64_t w = xcd_contiguous(blockIdx.x, gridDim.x), q0 = w * WG;
+    const int nq = (int)(a.nq - q0 < WG ? a.nq - q0 : WG);
+    const int ra = a.qrow[q0], rb = a.qrow[q0 + nq - 1];          // first and last row here
     bool bad = false;
-    if (e < E) {
-        const int32_t i = ei[e], j = ej[e];
-        const MT a = (MT)kv[e];
-        const MT pf = (MT)RF[2 * e], ef = (MT)RF[2 * e + 1], pb = (MT)RB[2 * e], eb = (MT)RB[2 * e + 1];
-        const MT Pi = (MT)PS[2 * (int64_t)i], Si = (MT)PS[2 * (int64_t)i + 1];
-        const MT Pj = (MT)PS[2 * (int64_t)j], Sj = (MT)PS[2 * (int64_t)j + 1];
-        const MT qf = Pi - pb;      // P~_i - P_ji
-        const MT qb = Pj - pf;      // P~_j - P_ij
-        bad = !(qf > (MT)0) || !(qb > (MT)0);
-        const MT rf = rcp_fast(qf), rb = rcp_fast(qb);
-        const MT a2 = a * a;
-        RF[2 * e] = (ST)(-a2 * rf);
-        RF[2 * e + 1] = (ST)(-a * (Si - eb) * rf);
-        RB[2 * e] = (ST)(-a2 * rb);
-        RB[2 * e + 1] = (ST)(-a * (Sj - ef) * rb);
+    if (tid < nq) {
+        const int64_t e = q0 + tid;
+        const int k = a.qrow[e];
+        const Int4 c = reinterpret_cast<const Int4*>(a.col)[e];
+        const f32x4v kk = reinterpret_cast<const f32x4v*>(a.kv)[e];
+        Rec2* const R = static_cast<Rec2*>(a.rec[par]) + 2 * e;
+        Rec2 old[2] = {Rec2{0, 0, 0, 0}, Rec2{0, 0, 0, 0}}, m[2];
+        MT Pk = 1, Sk = 0;
+        if (!FIRST) {
+            // the node's own aggregates of sweep t - 2
+            const AggT own = *reinterpret_cast<const AggT*>(PS2 + 2 * (int64_t)k);
+            Pk = (MT)own[0];
+            Sk = (MT)own[1];
+            if (t > 2) { old[0] = R[0]; old[1] = R[1]; }
+        }
+        AggT g[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) g[u] = A1[c[u]];
+        AT sp = 0, se = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const MT av = (MT)kk[u], a2 = av * av;
+            MT qk = 1, d = (MT)g[u][0], x = (MT)g[u][1];
+            if (!FIRST) {
+                qk = Pk - (MT)old[u / 2][2 * (u & 1)];
+                d = fma(d, qk, a2);
+                x = fma(x, qk, av * (Sk - (MT)old[u / 2][2 * (u & 1) + 1]));
+            }
+            bad |= !(d > (MT)0);
+            const MT r = rcp_pos(d);
+            const ST mp = (ST)(-(a2 * qk) * r), me = (ST)(-(av * x) * r);
+            m[u / 2][2 * (u & 1)] = mp;
+            m[u / 2][2 * (u & 1) + 1] = me;
+            sp += (AT)mp;
+            se += (AT)me;
+        }
+        R[0] = m[0];
+        R[1] = m[1];
+        qP[tid] = sp;
+        qE[tid] = se;
     }
-    if (__any(bad) && (threadIdx.x & 63) == 0) st->bad = 1;
+    __syncthreads();
+    const int q = tid & 15;
+    for (int r = ra + (tid >> 4); r <= rb; r += WG / 16) {
+        const int64_t b = a.row[r] / 4 - q0, e = a.row[r + 1] / 4 - q0;
+        const int lo = b > 0 ? (int)b : 0, hi = e < nq ? (int)e : nq;
+        AT sp = 0, se = 0;
+        for (int x = lo + q; x < hi; x += 16) { sp += qP[x]; se += qE[x]; }
+        sp = sum16(sp);
+        se = sum16(se);
+        if (q == 0) { rowP[r - ra] = sp; rowE[r - ra] = se; }
+    }
+    __syncthreads();
+    double d = 0.0, am = 0.0;
+    if (tid <= rb - ra) {
+        const int r = ra + tid;
+        const bool head = a.row[r] / 4 < q0, tail = a.row[r + 1] / 4 > q0 + nq;
+        if (head || tail) {
+            AT* const o = static_cast<AT*>(a.edge) + 4 * w + (head ? 0 : 2);
+            o[0] = rowP[tid];
+            o[1] = rowE[tid];
+        } else {
+            bad |= !sp_node<AT>(r, rowP[tid], rowE[tid], a, PS2, d, am);
+        }
+    }
+    if (__any(bad) && (tid & 63) == 0) a.st->bad = 1;
+    sp_maxima(d, am, a);
 }
 
-// Incoming messages of every node: sixteen lanes (one DPP row) per node
-// stride over its i-end edges (the reverse records j -> i) and its j-end
-// edges (the records i -> j), then add their partial sums in a fixed tree,
-// so every result is reproducible and the reads of a segment coalesce.
-template <class ST, class AT>
-__global__ __launch_bounds__(WG) void k_sp_gather(int64_t N, const int64_t* __restrict__ off_i,
-                                                  const int64_t* __restrict__ off_j,
-                                                  const int32_t* __restrict__ perm, const ST* __restrict__ RF,
-                                                  const ST* __restrict__ RB, AT* __restrict__ partP,
-                                                  AT* __restrict__ partE, const DevStatus* st) {
-    if (st->done) return;
-    const int64_t k = (xcd_contiguous(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 4;
-    const int q = threadIdx.x & 15;
-    AT p = 0, e = 0;
-    if (k < N) {
-        const int64_t a0 = off_i[k], a1 = off_i[k + 1];
-        int64_t u = a0 + q;
-        for (; u + 48 < a1; u += 64) {
-            const ST p0 = RB[2 * u], e0 = RB[2 * u + 1], p1 = RB[2 * u + 32], e1 = RB[2 * u + 33];
-            const ST p2 = RB[2 * u + 64], e2 = RB[2 * u + 65], p3 = RB[2 * u + 96], e3 = RB[2 * u + 97];
-            p += (AT)p0; e += (AT)e0;
-            p += (AT)p1; e += (AT)e1;
-            p += (AT)p2; e += (AT)e2;
-            p += (AT)p3; e += (AT)e3;
-        }
-        for (; u < a1; u += 16) { p += (AT)RB[2 * u]; e += (AT)RB[2 * u + 1]; }
-        const int64_t b0 = off_j[k], b1 = off_j[k + 1];
-        // four edge ids, then their four records, in flight at once; the
-        // additions keep the edge order
-        int64_t t = b0 + q;
-        for (; t + 48 < b1; t += 64) {
-            const int64_t x0 = perm[t], x1 = perm[t + 16], x2 = perm[t + 32], x3 = perm[t + 48];
-            const ST p0 = RF[2 * x0], e0 = RF[2 * x0 + 1], p1 = RF[2 * x1], e1 = RF[2 * x1 + 1];
-            const ST p2 = RF[2 * x2], e2 = RF[2 * x2 + 1], p3 = RF[2 * x3], e3 = RF[2 * x3 + 1];
-            p += (AT)p0; e += (AT)e0;
-            p += (AT)p1; e += (AT)e1;
-            p += (AT)p2; e += (AT)e2;
-            p += (AT)p3; e += (AT)e3;
-        }
-        for (; t < b1; t += 16) {
-            const int64_t x = perm[t];
-            p += (AT)RF[2 * x];
-            e += (AT)RF[2 * x + 1];
+// The rows that cross workgroup ranges of k_sp_sweep: thread w takes the row
+// that begins in range w and leaves it, adding the tail of w and the heads of
+// the ranges after it in order.  The workgroup that takes the last ticket
+// applies the stop rule (as in k_finalize) and clears the maxima for the
+// next sweep.
+template <class AT>
+__global__ __launch_bounds__(WG) void k_sp_join(SparseSweep a, int t) {
+    if (a.st->done) return;
+    __shared__ int last;
+    const int64_t w = (int64_t)blockIdx.x * WG + threadIdx.x, nw = (a.nq + WG - 1) / WG;
+    double d = 0.0, am = 0.0;
+    bool bad = false;
+    if (w + 1 < nw) {
+        const int r = a.qrow[w * WG + WG - 1];
+        const int64_t b = a.row[r] / 4, e = a.row[r + 1] / 4;
+        if (b >= w * WG && e > (w + 1) * WG) {
+            const AT* const x = static_cast<const AT*>(a.edge);
+            AT sp = x[4 * w + 2], se = x[4 * w + 3];
+            for (int64_t v = w + 1; v * WG < e; ++v) { sp += x[4 * v]; se += x[4 * v + 1]; }
+            bad = !sp_node<AT>(r, sp, se, a, static_cast<AT*>(a.PS[t & 1]), d, am);
         }
     }
-    p = sum16(p);
-    e = sum16(e);
-    if (k < N && q == 0) { partP[k] = p; partE[k] = e; }
+    if (__any(bad) && (threadIdx.x & 63) == 0) store_agent(&a.st->bad, 1);
+    sp_maxima(d, am, a);
+    wait_vm<0>();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&a.st->ticket, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    if (threadIdx.x == 0) a.st->ticket = 0;
+    status_update(SP_MAXS, a.dmax, a.amax, a.st, a.trace, a.rule);
+    a.dmax[threadIdx.x] = 0.0;
+    a.amax[threadIdx.x] = 0.0;
 }
+static_assert(SP_MAXS == WG, "one slot per thread");
 
 // ---- locality order and tile pruning
 //
@@ -514,14 +663,14 @@ __global__ void k_sp_unpermute(const double* __restrict__ in, const int32_t* __r
 
 template <int KIND>
 void sp_build_kind(bool fill, int mp, dim3 g, const Features& FA, const Features& FB, const uint32_t* tiles, int64_t stride, int64_t N,
-                   float cut, float c, float lam2, int32_t* counts, int64_t cap, unsigned long long* cursor,
+                   float cut, float c, float lam2, int32_t* counts, int64_t cap, unsigned long long* cursor, int sh,
                    uint64_t* keys, float* kv, hipStream_t s) {
     const dim3 gf((unsigned)(((int64_t)g.x + SP_TPW - 1) / SP_TPW));
 #define GABP_SP_LAUNCH(MPV)                                                                                  \
     do {                                                                                                     \
         if (fill)                                                                                            \
             hipLaunchKernelGGL((k_sp_fill<KIND, MPV>), gf, dim3(WG), 0, s, FA, FB, tiles, (int64_t)g.x, N, cut,   \
-                               c, lam2, cap, cursor, keys, kv);                                              \
+                               c, lam2, cap, cursor, sh, keys, kv);                                          \
         else                                                                                                 \
             hipLaunchKernelGGL((k_sp_count<KIND, MPV>), g, dim3(WG), 0, s, FA, FB, tiles, stride, N, cut,     \
                                counts);                                                                      \
@@ -536,9 +685,9 @@ void sp_build_kind(bool fill, int mp, dim3 g, const Features& FA, const Features
 
 hipError_t sp_build(bool fill, const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles,
                     int64_t stride, int64_t N, float cut, float c, float lam2, int32_t* counts, int64_t cap,
-                    unsigned long long* cursor, uint64_t* keys, float* kv, hipStream_t s) {
+                    unsigned long long* cursor, int sh, uint64_t* keys, float* kv, hipStream_t s) {
     const dim3 g((unsigned)ntiles);
-#define GABP_SP_KIND(K) sp_build_kind<K>(fill, FA.m_pad, g, FA, FB, tiles, stride, N, cut, c, lam2, counts, cap, cursor, keys, kv, s)
+#define GABP_SP_KIND(K) sp_build_kind<K>(fill, FA.m_pad, g, FA, FB, tiles, stride, N, cut, c, lam2, counts, cap, cursor, sh, keys, kv, s)
     switch (FA.kind) {
         case GRAM_F32: GABP_SP_KIND(GRAM_F32); break;
         case GRAM_BF16: GABP_SP_KIND(GRAM_BF16); break;
@@ -557,15 +706,16 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + WG - 1) / WG); }
 hipError_t launch_sp_count(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles,
                            int64_t stride, int64_t N, float cut, int32_t* counts, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
-    return sp_build(false, FA, FB, tiles, ntiles, stride, N, cut, 0.0f, 0.0f, counts, 0, nullptr, nullptr, nullptr,
-                    s);
+    return sp_build(false, FA, FB, tiles, ntiles, stride, N, cut, 0.0f, 0.0f, counts, 0, nullptr, 0, nullptr,
+                    nullptr, s);
 }
 
 hipError_t launch_sp_fill(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles, int64_t N,
-                          float cut, float neg_gamma_log2e, float lam2, int64_t cap, unsigned long long* cursor,
+                          float cut, float neg_gamma_log2e, float lam2, int64_t cap, unsigned long long* cursor, int sh,
                           uint64_t* keys, float* kv, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
-    return sp_build(true, FA, FB, tiles, ntiles, 1, N, cut, neg_gamma_log2e, lam2, nullptr, cap, cursor, keys, kv, s);
+    return sp_build(true, FA, FB, tiles, ntiles, 1, N, cut, neg_gamma_log2e, lam2, nullptr, cap, cursor, sh, keys, kv,
+                    s);
 }
 
 hipError_t launch_sp_augment(int64_t NPAD, int64_t m, int m_pad, int kind, const float* nrm, float* f32a,
@@ -625,8 +775,8 @@ hipError_t sp_scan(void* tmp, size_t* bytes, const int32_t* in, int64_t* out, in
 }
 
 hipError_t sp_sort_keys(void* tmp, size_t* bytes, const uint64_t* kin, uint64_t* kout, const float* vin,
-                        float* vout, int64_t n, hipStream_t s) {
-    return hipcub::DeviceRadixSort::SortPairs(tmp, *bytes, kin, kout, vin, vout, (int)n, 0, 64, s);
+                        float* vout, int64_t n, int bits, hipStream_t s) {
+    return hipcub::DeviceRadixSort::SortPairs(tmp, *bytes, kin, kout, vin, vout, (int)n, 0, bits, s);
 }
 
 hipError_t sp_sort_ids(void* tmp, size_t* bytes, const uint64_t* kin, uint64_t* kout, const int32_t* vin,
@@ -634,43 +784,69 @@ hipError_t sp_sort_ids(void* tmp, size_t* bytes, const uint64_t* kin, uint64_t* 
     return hipcub::DeviceRadixSort::SortPairs(tmp, *bytes, kin, kout, vin, vout, (int)n, 0, 64, s);
 }
 
-hipError_t launch_sp_unpack(const uint64_t* keys, int64_t E, int32_t* ei, int32_t* ej, int32_t* deg_i,
-                            int32_t* deg_j, uint64_t* keys_t, int32_t* ids, hipStream_t s) {
-    if (E > 0)
-        hipLaunchKernelGGL(k_sp_unpack, dim3(blocks(E)), dim3(WG), 0, s, keys, E, ei, ej, deg_i, deg_j, keys_t, ids);
+hipError_t launch_sp_unpack(const uint64_t* keys, int64_t E, int sh, int32_t* ei, int32_t* ej, uint64_t* keys_t,
+                            hipStream_t s) {
+    if (E > 0) hipLaunchKernelGGL(k_sp_unpack, dim3(blocks(E)), dim3(WG), 0, s, keys, E, sh, ei, ej, keys_t);
     return hipGetLastError();
 }
 
-hipError_t launch_sp_rowsum(int64_t N, const int64_t* off_i, const int64_t* off_j, const int32_t* perm,
-                            const float* kv, double* psum, double* pmax, hipStream_t s) {
-    hipLaunchKernelGGL(k_sp_rowsum, dim3(blocks(16 * N)), dim3(WG), 0, s, N, off_i, off_j, perm, kv, psum, pmax);
+hipError_t launch_sp_offsets(const uint64_t* keys, int64_t E, int sh, int64_t N, int64_t* off, hipStream_t s) {
+    hipLaunchKernelGGL(k_sp_offsets, dim3(blocks(E + 1)), dim3(WG), 0, s, keys, E, sh, N, off);
     return hipGetLastError();
 }
 
-hipError_t launch_sp_sweep(int prec, int64_t E, int64_t N, const int32_t* ei, const int32_t* ej, const float* kv,
-                           const void* Pt, const void* S, void* PS, void* RF, void* RB, const int64_t* off_i,
-                           const int64_t* off_j, const int32_t* perm, void* partP, void* partE, DevStatus* st,
-                           hipStream_t s) {
-    const dim3 ge(blocks(std::max<int64_t>(E, 1))), gn(blocks(16 * N)), g1(blocks(N)), b(WG);
+hipError_t launch_sp_rowlen(int64_t N, const int64_t* off_i, const int64_t* off_j, int32_t* len, hipStream_t s) {
+    hipLaunchKernelGGL(k_sp_rowlen, dim3(blocks(N + 1)), dim3(WG), 0, s, N, off_i, off_j, len);
+    return hipGetLastError();
+}
+
+hipError_t launch_sp_rows(int64_t E, int64_t N, int sh, const int32_t* ei, const int32_t* ej, const float* kv,
+                          const uint64_t* keys_t, const float* kv_t, const int64_t* off_i, const int64_t* off_j,
+                          const int64_t* row, int32_t* col, float* rkv, int32_t* qrow, hipStream_t s) {
+    hipLaunchKernelGGL(k_sp_rows, dim3(blocks(std::max(E, N))), dim3(WG), 0, s, E, N, sh, ei, ej, kv, keys_t, kv_t,
+                       off_i, off_j, row, col, rkv, qrow);
+    return hipGetLastError();
+}
+
+hipError_t launch_sp_rowsum(int64_t N, const int64_t* row, const float* kv, double* psum, double* pmax, hipStream_t s) {
+    hipLaunchKernelGGL(k_sp_rowsum, dim3(blocks(16 * N)), dim3(WG), 0, s, N, row, kv, psum, pmax);
+    return hipGetLastError();
+}
+
+hipError_t launch_sp_pack(int prec, int64_t N, const void* Pt, const void* S, void* PS, hipStream_t s) {
+    if (prec == PREC_FP32)
+        hipLaunchKernelGGL(k_sp_pack<float>, dim3(blocks(N)), dim3(WG), 0, s, N, (const float*)Pt, (const float*)S,
+                           (float*)PS);
+    else
+        hipLaunchKernelGGL(k_sp_pack<double>, dim3(blocks(N)), dim3(WG), 0, s, N, (const double*)Pt, (const double*)S,
+                           (double*)PS);
+    return hipGetLastError();
+}
+
+hipError_t launch_sp_unpack_p(int prec, int64_t N, const void* PS, double* P, hipStream_t s) {
+    if (prec == PREC_FP32)
+        hipLaunchKernelGGL(k_sp_unpack_p<float>, dim3(blocks(N)), dim3(WG), 0, s, N, (const float*)PS, P);
+    else
+        hipLaunchKernelGGL(k_sp_unpack_p<double>, dim3(blocks(N)), dim3(WG), 0, s, N, (const double*)PS, P);
+    return hipGetLastError();
+}
+
+hipError_t launch_sp_sweep(int prec, const SparseSweep& a, int t, hipStream_t s) {
+    if (t < 1 || a.nq < 1) return hipErrorInvalidValue;
+    const dim3 g(blocks(a.nq)), j(blocks((a.nq + WG - 1) / WG)), b(WG);
+    auto run = [&](auto first, auto later, auto join) {
+        hipLaunchKernelGGL(t == 1 ? first : later, g, b, 0, s, a, t);
+        hipLaunchKernelGGL(join, j, b, 0, s, a, t);
+        return hipGetLastError();
+    };
     switch (prec) {
         case PREC_FP32:
-            hipLaunchKernelGGL(k_sp_pack<float>, g1, b, 0, s, N, (const float*)Pt, (const float*)S, (float*)PS, st);
-            hipLaunchKernelGGL((k_sp_sweep<float, float, float>), ge, b, 0, s, E, ei, ej, kv, (const float*)PS,
-                               (float*)RF, (float*)RB, st);
-            hipLaunchKernelGGL((k_sp_gather<float, float>), gn, b, 0, s, N, off_i, off_j, perm, (const float*)RF,
-                               (const float*)RB, (float*)partP, (float*)partE, st);
-            break;
+            return run(k_sp_sweep<float, float, float, true>, k_sp_sweep<float, float, float, false>, k_sp_join<float>);
         case PREC_MIXED:
-            hipLaunchKernelGGL(k_sp_pack<double>, g1, b, 0, s, N, (const double*)Pt, (const double*)S,
-                               (double*)PS, st);
-            hipLaunchKernelGGL((k_sp_sweep<float, double, double>), ge, b, 0, s, E, ei, ej, kv, (const double*)PS,
-                               (float*)RF, (float*)RB, st);
-            hipLaunchKernelGGL((k_sp_gather<float, double>), gn, b, 0, s, N, off_i, off_j, perm, (const float*)RF,
-                               (const float*)RB, (double*)partP, (double*)partE, st);
-            break;
+            return run(k_sp_sweep<float, double, double, true>, k_sp_sweep<float, double, double, false>,
+                       k_sp_join<double>);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace gabp

@@ -111,9 +111,10 @@ struct gabp_svm {
         parena;                  // working memory of gabp_svm_predict (reused)
     int aug_kind = -1, aug_mp = 0;
     // sparsified kernel: tile counts and offsets, keys, K' per edge, edge
-    // ends, degrees and offsets of the i-end and j-end lists, permutation
-    DevBuf sp_cnt, sp_toff, sp_keys, sp_keys2, sp_kv, sp_kv2, sp_ei, sp_ej, sp_degi, sp_degj, sp_offi,
-        sp_offj, sp_ids, sp_perm, sp_tmp, sp_order, sp_Xp, sp_cent, sp_rad, sp_keep, sp_tsel, sp_nsel, sp_xb;
+    // ends, offsets of the i-end and j-end lists, rows (neighbour, K') of
+    // every node, order and landmarks
+    DevBuf sp_cnt, sp_toff, sp_keys, sp_keys2, sp_kv, sp_kv2, sp_ei, sp_ej, sp_offi,
+        sp_offj, sp_len, sp_row, sp_qrow, sp_edge, sp_col, sp_rkv, sp_ids, sp_lm, sp_tmp, sp_order, sp_Xp, sp_cent, sp_rad, sp_keep, sp_tsel, sp_nsel, sp_xb;
     bool sparse = false;
     int64_t n_edges = 0;
     // residual certificate of the last solve (GABP_Q_RESIDUAL_BOUND), formed
@@ -121,11 +122,11 @@ struct gabp_svm {
     bool resid_valid = false;
     double resid[3] = {0.0, 0.0, 0.0};
 
-    DevBuf* all[72] = {&tiles, &Kp, &Pf, &Pb, &Ef, &Eb, &partP, &partE, &Xin, &yd, &mean,
+    DevBuf* all[76] = {&tiles, &Kp, &Pf, &Pb, &Ef, &Eb, &partP, &partE, &Xin, &yd, &mean,
                        &xs32, &xhi, &xlo, &xlo2, &x64, &nrm, &kdiag, &rowmax, &rsum, &Adiag, &Pt, &S, &alpha_d,
                        &blk1, &blk2, &one, &status_d, &trace_d, &flag, &tmp, &Kin, &q_rows,
                        &q_cols, &q_out, &glist, &sp_cnt, &sp_toff, &sp_keys, &sp_keys2, &sp_kv, &sp_kv2,
-                       &sp_ei, &sp_ej, &sp_degi, &sp_degj, &sp_offi, &sp_offj, &sp_ids, &sp_perm, &sp_tmp,
+                       &sp_ei, &sp_ej, &sp_offi, &sp_offj, &sp_len, &sp_row, &sp_qrow, &sp_edge, &sp_col, &sp_rkv, &sp_ids, &sp_lm, &sp_tmp,
                        &sp_order, &sp_Xp, &sp_cent, &sp_rad, &sp_keep, &sp_tsel, &sp_nsel, &sp_xb, &HI, &HM, &chunks, &xaug, &xaug0, &parena, nullptr};
     size_t held() const {
         size_t b = 0;
@@ -821,10 +822,10 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     A(h->rsum, (size_t)N * 8);
     A(h->Pt, (size_t)NPAD * 8); A(h->S, (size_t)NPAD * 8);
     A(h->alpha_d, (size_t)N * 8); A(h->tmp, (size_t)NPAD * 8);
-    A(h->blk1, (size_t)(NPAD / FB + 1) * 8); A(h->blk2, (size_t)(NPAD / FB + 1) * 8);
+    A(h->blk1, (size_t)std::max<int64_t>(NPAD / WG + 1, WG) * 8);
+    A(h->blk2, (size_t)std::max<int64_t>(NPAD / WG + 1, WG) * 8);
     A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64);
     A(h->trace_d, (size_t)p.max_sweeps * 8);
-    A(h->sp_degi, (size_t)(N + 1) * 4); A(h->sp_degj, (size_t)(N + 1) * 4);
     A(h->sp_offi, (size_t)(N + 1) * 8); A(h->sp_offj, (size_t)(N + 1) * 8);
     A(h->sp_order, (size_t)N * 4); A(h->sp_Xp, (size_t)N * m * 4);
     A(h->sp_cent, (size_t)NB * m * 8); A(h->sp_rad, (size_t)NB * 8);
@@ -862,13 +863,13 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     {
         std::vector<int32_t> lm((size_t)K);
         for (int k = 0; k < K; ++k) lm[(size_t)k] = (int32_t)((int64_t)k * N / K);
-        if (h->sp_ids.ensure((size_t)N * 4) != hipSuccess || h->sp_perm.ensure((size_t)K * 4) != hipSuccess ||
+        if (h->sp_ids.ensure((size_t)N * 4) != hipSuccess || h->sp_lm.ensure((size_t)K * 4) != hipSuccess ||
             h->sp_keys.ensure((size_t)N * 8) != hipSuccess || h->sp_keys2.ensure((size_t)N * 8) != hipSuccess) {
             h->release_all();
             return fail(h, GABP_E_NOMEM, "device allocation of the ordering arrays failed");
         }
-        HIPCHK(h, hipMemcpyAsync(h->sp_perm.p, lm.data(), (size_t)K * 4, hipMemcpyHostToDevice, s));
-        HIPCHK(h, launch_sp_order(Xd, N, m, h->sp_perm.as<int32_t>(), K, h->sp_keys.as<uint64_t>(),
+        HIPCHK(h, hipMemcpyAsync(h->sp_lm.p, lm.data(), (size_t)K * 4, hipMemcpyHostToDevice, s));
+        HIPCHK(h, launch_sp_order(Xd, N, m, h->sp_lm.as<int32_t>(), K, h->sp_keys.as<uint64_t>(),
                                   h->sp_ids.as<int32_t>(), s));
         size_t ob = 0;
         HIPCHK(h, sp_sort_ids(nullptr, &ob, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(),
@@ -939,6 +940,9 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     const float c = (float)(-p.gamma * 1.4426950408889634);
     int64_t E = 0;
     size_t tb = 0;
+    // bits of a node index: an edge's key is i << sh | j
+    int sh = 1;
+    while (((int64_t)1 << sh) < N) ++sh;
     if (nts > 0) {
         // capacity of the fill's output: the caller's hint, else 1.5 x the
         // kept pairs of every 32nd tile scaled to all tiles, plus 2^20; a
@@ -969,7 +973,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
                                                  hipGetErrorString(ae));
             }
             HIPCHK(h, hipMemsetAsync(cursor, 0, 8, s));
-            HIPCHK(h, launch_sp_fill(F, FB, tsel, nts, N, cutf, c, (float)(lam * lam), cap, cursor,
+            HIPCHK(h, launch_sp_fill(F, FB, tsel, nts, N, cutf, c, (float)(lam * lam), cap, cursor, sh,
                                      h->sp_keys.as<uint64_t>(), h->sp_kv.as<float>(), s));
             unsigned long long total = 0;
             HIPCHK(h, hipMemcpyAsync(&total, cursor, 8, hipMemcpyDeviceToHost, s));
@@ -984,47 +988,55 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     A(h->sp_keys, (size_t)E * 8); A(h->sp_keys2, (size_t)E * 8);
     A(h->sp_kv, (size_t)E * 4); A(h->sp_kv2, (size_t)E * 4);
     A(h->sp_ei, (size_t)E * 4); A(h->sp_ej, (size_t)E * 4);
-    A(h->sp_ids, (size_t)std::max(E, N) * 4); A(h->sp_perm, (size_t)E * 4);
-    // records: (P, E) pairs per edge and direction; packed aggregates
-    A(h->Pf, (size_t)2 * E * st_bytes); A(h->Pb, (size_t)2 * E * st_bytes);
-    A(h->Ef, (size_t)2 * NPAD * 8);
+    const size_t rows = (size_t)2 * E + (size_t)4 * N;      // entries, every row in whole quads
+    A(h->sp_len, (size_t)(N + 1) * 4); A(h->sp_row, (size_t)(N + 1) * 8);
+    A(h->sp_qrow, rows); A(h->sp_edge, (rows / 4 / WG + 1) * 4 * agg);
+    A(h->sp_col, rows * 4); A(h->sp_rkv, rows * 4);
+    // records: the (P, E) message into every row's node, two sweeps; packed
+    // aggregates of two sweeps
+    A(h->Pf, 2 * rows * st_bytes); A(h->Pb, 2 * rows * st_bytes);
+    A(h->Ef, (size_t)2 * NPAD * 8); A(h->Eb, (size_t)2 * NPAD * 8);
     if (ae != hipSuccess) {
         h->release_all();
         return fail(h, GABP_E_NOMEM, std::string("device allocation of the edge arrays failed: ") +
                                          hipGetErrorString(ae));
     }
-    size_t sb = 0, sb2 = 0;
+    size_t sb = 0;
     HIPCHK(h, sp_sort_keys(nullptr, &sb, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(), h->sp_kv.as<float>(),
-                           h->sp_kv2.as<float>(), E, s));
-    HIPCHK(h, sp_sort_ids(nullptr, &sb2, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(),
-                          h->sp_ids.as<int32_t>(), h->sp_perm.as<int32_t>(), E, s));
-    size_t sb3 = 0;
-    HIPCHK(h, sp_scan(nullptr, &sb3, h->sp_degi.as<int32_t>(), h->sp_offi.as<int64_t>(), N + 1, s));
-    if (h->sp_tmp.ensure(std::max(std::max(sb, sb2), std::max(sb3, tb))) != hipSuccess) {
+                           h->sp_kv2.as<float>(), E, 2 * sh, s));
+    size_t sb2 = 0;
+    HIPCHK(h, sp_scan(nullptr, &sb2, h->sp_len.as<int32_t>(), h->sp_row.as<int64_t>(), N + 1, s));
+    if (h->sp_tmp.ensure(std::max(std::max(sb, sb2), tb)) != hipSuccess) {
         h->release_all();
         return fail(h, GABP_E_NOMEM, "sort storage");
     }
-    // edges in (i, j) order: keys2 / kv2 (K' per edge from here on)
+    // edges in (i, j) order: keys2 / kv2, their ends, and the keys of the
+    // transposed order (j, i) into keys
     HIPCHK(h, sp_sort_keys(h->sp_tmp.p, &sb, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(),
-                           h->sp_kv.as<float>(), h->sp_kv2.as<float>(), E, s));
-    HIPCHK(h, hipMemsetAsync(h->sp_degi.p, 0, (size_t)(N + 1) * 4, s));
-    HIPCHK(h, hipMemsetAsync(h->sp_degj.p, 0, (size_t)(N + 1) * 4, s));
-    // ends and degrees; keys of the transposed order (j, i) into keys
-    HIPCHK(h, launch_sp_unpack(h->sp_keys2.as<uint64_t>(), E, h->sp_ei.as<int32_t>(), h->sp_ej.as<int32_t>(),
-                               h->sp_degi.as<int32_t>(), h->sp_degj.as<int32_t>(), h->sp_keys.as<uint64_t>(),
-                               h->sp_ids.as<int32_t>(), s));
-    // perm: edge ids in (j, i) order
-    HIPCHK(h, sp_sort_ids(h->sp_tmp.p, &sb2, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(),
-                          h->sp_ids.as<int32_t>(), h->sp_perm.as<int32_t>(), E, s));
-    HIPCHK(h, sp_scan(h->sp_tmp.p, &sb3, h->sp_degi.as<int32_t>(), h->sp_offi.as<int64_t>(), N + 1, s));
-    HIPCHK(h, sp_scan(h->sp_tmp.p, &sb3, h->sp_degj.as<int32_t>(), h->sp_offj.as<int64_t>(), N + 1, s));
+                           h->sp_kv.as<float>(), h->sp_kv2.as<float>(), E, 2 * sh, s));
+    HIPCHK(h, launch_sp_offsets(h->sp_keys2.as<uint64_t>(), E, sh, N, h->sp_offi.as<int64_t>(), s));
+    HIPCHK(h, launch_sp_unpack(h->sp_keys2.as<uint64_t>(), E, sh, h->sp_ei.as<int32_t>(), h->sp_ej.as<int32_t>(),
+                               h->sp_keys.as<uint64_t>(), s));
+    // edges in (j, i) order: keys2 / kv; rows of all nodes from both orders
+    HIPCHK(h, sp_sort_keys(h->sp_tmp.p, &sb, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(),
+                           h->sp_kv2.as<float>(), h->sp_kv.as<float>(), E, 2 * sh, s));
+    HIPCHK(h, launch_sp_offsets(h->sp_keys2.as<uint64_t>(), E, sh, N, h->sp_offj.as<int64_t>(), s));
+    HIPCHK(h, launch_sp_rowlen(N, h->sp_offi.as<int64_t>(), h->sp_offj.as<int64_t>(), h->sp_len.as<int32_t>(), s));
+    HIPCHK(h, sp_scan(h->sp_tmp.p, &sb2, h->sp_len.as<int32_t>(), h->sp_row.as<int64_t>(), N + 1, s));
+    HIPCHK(h, launch_sp_rows(E, N, sh, h->sp_ei.as<int32_t>(), h->sp_ej.as<int32_t>(), h->sp_kv2.as<float>(),
+                             h->sp_keys2.as<uint64_t>(), h->sp_kv.as<float>(), h->sp_offi.as<int64_t>(),
+                             h->sp_offj.as<int64_t>(), h->sp_row.as<int64_t>(), h->sp_col.as<int32_t>(),
+                             h->sp_rkv.as<float>(), h->sp_qrow.as<int32_t>(), s));
+    int64_t entries = 0;
+    HIPCHK(h, hipMemcpyAsync(&entries, h->sp_row.as<int64_t>() + N, 8, hipMemcpyDeviceToHost, s));
+    HIPCHK(h, hipStreamSynchronize(s));
     HIPCHK(h, hipEventRecord(ev[2], s));
 
     // ---- diagonal weighting from the sparse row sums (one partial per node)
     HIPCHK(h, hipMemsetAsync(h->partP.p, 0, (size_t)NPAD * 8, s));
     HIPCHK(h, hipMemsetAsync(h->partE.p, 0, (size_t)NPAD * 8, s));
-    HIPCHK(h, launch_sp_rowsum(N, h->sp_offi.as<int64_t>(), h->sp_offj.as<int64_t>(), h->sp_perm.as<int32_t>(),
-                               h->sp_kv2.as<float>(), h->partP.as<double>(), h->partE.as<double>(), s));
+    HIPCHK(h, launch_sp_rowsum(N, h->sp_row.as<int64_t>(), h->sp_rkv.as<float>(), h->partP.as<double>(),
+                               h->partE.as<double>(), s));
     HIPCHK(h, launch_fill_value(h->kdiag.as<double>(), N, 1.0 + lam * lam, s));
     HIPCHK(h, launch_diag(N, 0, h->partP.as<double>(), h->partE.as<double>(), h->kdiag.as<double>(),
                           p.diag_mode, p.C, p.diag_delta, h->Adiag.as<double>(), h->rowmax.as<double>(),
@@ -1033,23 +1045,28 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     const double boxC = (p.box_mode == GABP_BOX_PROJECT) ? p.C : 0.0;
     HIPCHK(h, launch_init(prec, N, NPAD, 1, h->Adiag.as<double>(), h->yd.as<float>(), h->Pt.p, h->S.p,
                           h->alpha_d.as<double>(), st, s, boxC));
-    for (DevBuf* b : {&h->Pf, &h->Pb}) HIPCHK(h, hipMemsetAsync(b->p, 0, (size_t)2 * E * st_bytes, s));
+    HIPCHK(h, launch_sp_pack(prec, N, h->Pt.p, h->S.p, h->Ef.p, s));
+    HIPCHK(h, launch_fill_value(h->blk1.as<double>(), WG, 0.0, s));
+    HIPCHK(h, launch_fill_value(h->blk2.as<double>(), WG, 0.0, s));
     HIPCHK(h, hipEventRecord(ev[3], s));
 
-    // ---- sweeps: edge update + per-node gather, finalize, stop rule
-    FinalizeArgs fa{};
-    fa.N = N;
-    fa.stride = fa.split = 1;       // one partial per node
-    fa.partP = h->partP.p; fa.partE = h->partE.p;
-    fa.Adiag = h->Adiag.as<double>();
-    fa.y = h->yd.as<float>();
-    fa.Pt = h->Pt.p; fa.S = h->S.p;
-    fa.alpha = h->alpha_d.as<double>();
-    fa.blk_delta = h->blk1.as<double>(); fa.blk_amax = h->blk2.as<double>();
-    fa.st = st;
-    fa.boxC = boxC;
-    fa.trace = h->trace_d.as<double>();
-    fa.rule = StopRule{p.tol_abs, p.tol_rel, p.stagnation_rel, p.max_sweeps, p.stagnation_window};
+    // ---- sweeps over the rows, each with its stop rule
+    SparseSweep sw{};
+    sw.nq = entries / 4;
+    sw.row = h->sp_row.as<int64_t>();
+    sw.qrow = h->sp_qrow.as<int32_t>();
+    sw.edge = h->sp_edge.p;
+    sw.col = h->sp_col.as<int32_t>(); sw.kv = h->sp_rkv.as<float>();
+    sw.rec[0] = h->Pf.p; sw.rec[1] = h->Pb.p;
+    sw.PS[0] = h->Ef.p; sw.PS[1] = h->Eb.p;
+    sw.Adiag = h->Adiag.as<double>();
+    sw.y = h->yd.as<float>();
+    sw.alpha = h->alpha_d.as<double>();
+    sw.dmax = h->blk1.as<double>(); sw.amax = h->blk2.as<double>();
+    sw.trace = h->trace_d.as<double>();
+    sw.st = st;
+    sw.boxC = boxC;
+    sw.rule = StopRule{p.tol_abs, p.tol_rel, p.stagnation_rel, p.max_sweeps, p.stagnation_window};
     DevStatus hs{};
     double sweep_kernel_ms = 0.0;
     int64_t launches = 0;
@@ -1057,12 +1074,8 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     for (int t = 0; t < p.max_sweeps; ++t) {
         const int slot = t % ce;
         if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot], s));
-        HIPCHK(h, launch_sp_sweep(prec, E, N, h->sp_ei.as<int32_t>(), h->sp_ej.as<int32_t>(), h->sp_kv2.as<float>(),
-                                  h->Pt.p, h->S.p, h->Ef.p, h->Pf.p, h->Pb.p, h->sp_offi.as<int64_t>(),
-                                  h->sp_offj.as<int64_t>(), h->sp_perm.as<int32_t>(), h->partP.p, h->partE.p,
-                                  st, s));
+        HIPCHK(h, launch_sp_sweep(prec, sw, t + 1, s));
         if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot + 1], s));
-        HIPCHK(h, launch_finalize(prec, fa, s));
         if ((t + 1) % ce == 0 || t + 1 == p.max_sweeps) {
             HIPCHK(h, hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
             HIPCHK(h, hipStreamSynchronize(s));
@@ -1089,7 +1102,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     HIPCHK(h, launch_sp_unpermute(h->alpha_d.as<double>(), ord, N, scr, s));
     HIPCHK(h, hipMemcpyAsync(h->alpha.data(), scr, (size_t)N * 8, hipMemcpyDeviceToHost, s));
     HIPCHK(h, hipStreamSynchronize(s));
-    HIPCHK(h, launch_convert_agg(prec, h->Pt.p, h->tmp.as<double>(), N, s));
+    HIPCHK(h, launch_sp_unpack_p(prec, N, sw.PS[hs.t & 1], h->tmp.as<double>(), s));
     HIPCHK(h, launch_sp_unpermute(h->tmp.as<double>(), ord, N, scr, s));
     HIPCHK(h, hipMemcpyAsync(h->ptilde.data(), scr, (size_t)N * 8, hipMemcpyDeviceToHost, s));
     HIPCHK(h, hipStreamSynchronize(s));
@@ -1136,13 +1149,11 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     h->plan.n_tiles = nt;
     h->plan.n_edges = E;
     h->plan.device_bytes = h->held();
-    // per edge and sweep: ends (8 B), K' (4 B), records read and written
-    // (8 x 4 B), the gather's record reads (4 x 4 B) and permutation (4 B);
-    // the packed aggregates (16 N B) are not counted
-    h->plan.alg_bytes_per_pair = 8.0 + 4.0 + 8.0 * st_bytes + 4.0 * st_bytes + 4.0;
+    // per edge and sweep, in both ends' rows: neighbour and K' (8 B), the
+    // record read and written (4 x 4 B); the packed aggregates are not counted
+    h->plan.alg_bytes_per_pair = 2.0 * (8.0 + 4.0 * st_bytes);
     h->plan.alg_bytes_per_sweep = (uint64_t)((double)E * h->plan.alg_bytes_per_pair);
     h->have_result = true;
-    (void)agg;
     if (h->status != GABP_OK) {
         h->err = (h->status == GABP_E_DIVERGED) ? "GaBP diverged: a cavity precision became <= 0 or non-finite"
                                                 : "max_sweeps reached before the stop rule held";
