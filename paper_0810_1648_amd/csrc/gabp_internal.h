@@ -335,8 +335,8 @@ hipError_t sp_tile_order(void* tmp, size_t* bytes, uint32_t* tiles, int64_t nt, 
                          uint64_t* k1, hipStream_t s);
 // Locality order: nearest of the K landmark points lm[] for every point
 // (key = landmark << 32 | point, ids = point), rows permuted into that order,
-// block centroids / radii and the tiles that may hold kept pairs, compaction
-// of the tile list, and per-node arrays back to input order.
+// block centroids / radii and the tiles that may hold kept pairs, and
+// compaction of the tile list.
 hipError_t launch_sp_order(const float* X, int64_t N, int64_t m, const int32_t* lm, int K, uint64_t* key,
                            int32_t* ids, hipStream_t s);
 hipError_t launch_sp_permute(const float* X, const float* y, int64_t N, int64_t m, const int32_t* order, float* Xp,
@@ -345,7 +345,6 @@ hipError_t launch_sp_prune(const float* Xp, int64_t N, int64_t m, int NB, const 
                            double cut, double* cent, double* rad, uint8_t* keep, hipStream_t s);
 hipError_t sp_select(void* tmp, size_t* bytes, const uint32_t* in, const uint8_t* flags, uint32_t* out,
                      int64_t* nsel, int64_t n, hipStream_t s);
-hipError_t launch_sp_unpermute(const double* in, const int32_t* order, int64_t N, double* out, hipStream_t s);
 hipError_t sp_sort_keys(void* tmp, size_t* bytes, const uint64_t* kin, uint64_t* kout, const float* vin,
                         float* vout, int64_t n, int bits, hipStream_t s);
 hipError_t sp_sort_ids(void* tmp, size_t* bytes, const uint64_t* kin, uint64_t* kout, const int32_t* vin,
@@ -363,9 +362,8 @@ hipError_t launch_sp_rows(int64_t E, int64_t N, int sh, const int32_t* ei, const
                           const uint64_t* keys_t, const float* kv_t, const int64_t* off_i, const int64_t* off_j,
                           const int64_t* row, int32_t* col, float* rkv, int32_t* qrow, hipStream_t s);
 hipError_t launch_sp_rowsum(int64_t N, const int64_t* row, const float* kv, double* psum, double* pmax, hipStream_t s);
-// (P~, S) pairs from the separate aggregates, and P~ back out of the pairs.
+// (P~, S) pairs from the separate aggregates.
 hipError_t launch_sp_pack(int prec, int64_t N, const void* Pt, const void* S, void* PS, hipStream_t s);
-hipError_t launch_sp_unpack_p(int prec, int64_t N, const void* PS, double* P, hipStream_t s);
 // Sweep t = 1, 2, ... over the rows with its stop rule: rec[t & 1] holds the
 // packed (P, E) messages into every node of sweep t - 2 and takes sweep t's,
 // PS[t & 1] the packed aggregates likewise; PS[(t - 1) & 1] those of sweep
@@ -443,6 +441,10 @@ hipError_t launch_predict_small(int kind, int mp, const uint16_t* Bt, int64_t NP
                                 hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_predict_reduce(const double* part, int nchunk, int64_t stride, int64_t nq, const double* wpart, int nw,
                                  double lam2, double* f, hipStream_t s);
-hipError_t launch_convert_agg(int prec, const void* src, double* dst, int64_t n, hipStream_t s);
+// Results of a solve packed for one download: alpha, P~ (read with `stride`
+// aggregates from one node to the next), A_ii as N doubles each, then the
+// labels as N floats; order (optional): node r of the inputs goes to order[r].
+hipError_t launch_pack_out(int prec, int64_t N, const double* alpha, const void* Pt, int stride, const double* Adiag,
+                           const float* y, const int32_t* order, double* out, hipStream_t s);
 
 }  // namespace gabp

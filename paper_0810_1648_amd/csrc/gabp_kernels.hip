@@ -850,9 +850,16 @@ __global__ void k_entries(const ST* __restrict__ Kp, int NB, const int64_t* __re
 }
 
 template <class AT>
-__global__ void k_convert(const AT* __restrict__ src, double* __restrict__ dst, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = (double)src[i];
+__global__ void k_pack_out(int64_t N, const double* __restrict__ alpha, const AT* __restrict__ Pt, int stride,
+                           const double* __restrict__ Adiag, const float* __restrict__ y,
+                           const int32_t* __restrict__ order, double* __restrict__ out) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= N) return;
+    const int64_t i = order ? order[r] : r;
+    out[i] = alpha[r];
+    out[N + i] = (double)Pt[r * stride];
+    out[2 * N + i] = Adiag[r];
+    reinterpret_cast<float*>(out + 3 * N)[i] = y[r];
 }
 
 // ----------------------------------------------------------- launchers --
@@ -1103,11 +1110,14 @@ hipError_t launch_kernel_entries(const void* Kp, int prec, int NB, const int64_t
     return hipGetLastError();
 }
 
-hipError_t launch_convert_agg(int prec, const void* src, double* dst, int64_t n, hipStream_t s) {
+hipError_t launch_pack_out(int prec, int64_t N, const double* alpha, const void* Pt, int stride, const double* Adiag,
+                           const float* y, const int32_t* order, double* out, hipStream_t s) {
     if (prec == PREC_FP32)
-        hipLaunchKernelGGL(k_convert<float>, dim3(grid1(n)), dim3(WG), 0, s, (const float*)src, dst, n);
+        hipLaunchKernelGGL(k_pack_out<float>, dim3(grid1(N)), dim3(WG), 0, s, N, alpha, (const float*)Pt, stride, Adiag,
+                           y, order, out);
     else
-        hipLaunchKernelGGL(k_convert<double>, dim3(grid1(n)), dim3(WG), 0, s, (const double*)src, dst, n);
+        hipLaunchKernelGGL(k_pack_out<double>, dim3(grid1(N)), dim3(WG), 0, s, N, alpha, (const double*)Pt, stride,
+                           Adiag, y, order, out);
     return hipGetLastError();
 }
 

@@ -301,12 +301,6 @@ __global__ void k_sp_pack(int64_t N, const AT* __restrict__ Pt, const AT* __rest
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < N) { PS[2 * k] = Pt[k]; PS[2 * k + 1] = S[k]; }
 }
-template <class AT>
-__global__ void k_sp_unpack_p(int64_t N, const AT* __restrict__ PS, double* __restrict__ P) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < N) P[k] = (double)PS[2 * k];
-}
-
 constexpr int SP_MAXS = 256;   // slots of the sweep's change / magnitude maxima
 
 // New aggregates and alpha of node k from the sums of its messages; d and am
@@ -654,13 +648,6 @@ __global__ void k_sp_augment(int64_t NPAD, int64_t m, int m_pad, int kind, const
     if (x6) lo2b[o + m + 1] = l2;
 }
 
-// out[order[r]] = in[r]: a per-node array back to input order.
-__global__ void k_sp_unpermute(const double* __restrict__ in, const int32_t* __restrict__ order, int64_t N,
-                               double* __restrict__ out) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < N) out[order[r]] = in[r];
-}
-
 template <int KIND>
 void sp_build_kind(bool fill, int mp, dim3 g, const Features& FA, const Features& FB, const uint32_t* tiles, int64_t stride, int64_t N,
                    float cut, float c, float lam2, int32_t* counts, int64_t cap, unsigned long long* cursor, int sh,
@@ -765,11 +752,6 @@ hipError_t sp_tile_order(void* tmp, size_t* bytes, uint32_t* tiles, int64_t nt, 
     return hipGetLastError();
 }
 
-hipError_t launch_sp_unpermute(const double* in, const int32_t* order, int64_t N, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_sp_unpermute, dim3(blocks(N)), dim3(WG), 0, s, in, order, N, out);
-    return hipGetLastError();
-}
-
 hipError_t sp_scan(void* tmp, size_t* bytes, const int32_t* in, int64_t* out, int64_t n, hipStream_t s) {
     return hipcub::DeviceScan::ExclusiveSum(tmp, *bytes, in, out, (int)n, s);
 }
@@ -820,14 +802,6 @@ hipError_t launch_sp_pack(int prec, int64_t N, const void* Pt, const void* S, vo
     else
         hipLaunchKernelGGL(k_sp_pack<double>, dim3(blocks(N)), dim3(WG), 0, s, N, (const double*)Pt, (const double*)S,
                            (double*)PS);
-    return hipGetLastError();
-}
-
-hipError_t launch_sp_unpack_p(int prec, int64_t N, const void* PS, double* P, hipStream_t s) {
-    if (prec == PREC_FP32)
-        hipLaunchKernelGGL(k_sp_unpack_p<float>, dim3(blocks(N)), dim3(WG), 0, s, N, (const float*)PS, P);
-    else
-        hipLaunchKernelGGL(k_sp_unpack_p<double>, dim3(blocks(N)), dim3(WG), 0, s, N, (const double*)PS, P);
     return hipGetLastError();
 }
 

@@ -47,6 +47,48 @@ struct DevBuf {
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
 
+// Page-locked host memory, kept by the handle: results and statuses arrive in
+// it without the runtime's staging copies.
+struct PinBuf {
+    void* p = nullptr;
+    size_t bytes = 0;
+    hipError_t ensure(size_t n) {
+        if (p && n <= bytes) return hipSuccess;
+        release();
+        const hipError_t e = hipHostMalloc(&p, n, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            p = nullptr;
+            (void)hipGetLastError();
+            return e;
+        }
+        bytes = n;
+        return hipSuccess;
+    }
+    void release() {
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        bytes = 0;
+    }
+};
+
+struct EventPool {
+    std::vector<hipEvent_t> ev;
+    ~EventPool() { release(); }
+    void release() {
+        for (auto e : ev) (void)hipEventDestroy(e);
+        ev.clear();
+    }
+    hipError_t make(size_t n) {
+        while (ev.size() < n) {
+            hipEvent_t e;
+            hipError_t r = hipEventCreate(&e);
+            if (r != hipSuccess) return r;
+            ev.push_back(e);
+        }
+        return hipSuccess;
+    }
+};
+
 double now_ms() {
     using namespace std::chrono;
     return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
@@ -117,17 +159,23 @@ struct gabp_svm {
         sp_offj, sp_len, sp_row, sp_qrow, sp_edge, sp_col, sp_rkv, sp_ids, sp_lm, sp_tmp, sp_order, sp_Xp, sp_cent, sp_rad, sp_keep, sp_tsel, sp_nsel, sp_xb;
     bool sparse = false;
     int64_t n_edges = 0;
+    // host side of a solve, kept from one to the next: events (6 phase marks, 2
+    // for the statuses, with time_sweeps two per sweep of two polls), the
+    // page-locked results and statuses
+    EventPool evp;
+    PinBuf pin, pin_st;
+    DevBuf out_d;
     // residual certificate of the last solve (GABP_Q_RESIDUAL_BOUND), formed
     // on the first query
     bool resid_valid = false;
     double resid[3] = {0.0, 0.0, 0.0};
 
-    DevBuf* all[76] = {&tiles, &Kp, &Pf, &Pb, &Ef, &Eb, &partP, &partE, &Xin, &yd, &mean,
+    DevBuf* all[80] = {&tiles, &Kp, &Pf, &Pb, &Ef, &Eb, &partP, &partE, &Xin, &yd, &mean,
                        &xs32, &xhi, &xlo, &xlo2, &x64, &nrm, &kdiag, &rowmax, &rsum, &Adiag, &Pt, &S, &alpha_d,
                        &blk1, &blk2, &one, &status_d, &trace_d, &flag, &tmp, &Kin, &q_rows,
                        &q_cols, &q_out, &glist, &sp_cnt, &sp_toff, &sp_keys, &sp_keys2, &sp_kv, &sp_kv2,
                        &sp_ei, &sp_ej, &sp_offi, &sp_offj, &sp_len, &sp_row, &sp_qrow, &sp_edge, &sp_col, &sp_rkv, &sp_ids, &sp_lm, &sp_tmp,
-                       &sp_order, &sp_Xp, &sp_cent, &sp_rad, &sp_keep, &sp_tsel, &sp_nsel, &sp_xb, &HI, &HM, &chunks, &xaug, &xaug0, &parena, nullptr};
+                       &sp_order, &sp_Xp, &sp_cent, &sp_rad, &sp_keep, &sp_tsel, &sp_nsel, &sp_xb, &HI, &HM, &chunks, &xaug, &xaug0, &parena, &out_d, nullptr};
     size_t held() const {
         size_t b = 0;
         for (int k = 0; all[k]; ++k) b += all[k]->bytes;
@@ -153,24 +201,96 @@ gabp_status fail(gabp_svm* h, gabp_status st, const std::string& msg) {
                         std::string(#expr ": ") + hipGetErrorString(e_));                 \
     } while (0)
 
-struct EventPool {
-    std::vector<hipEvent_t> ev;
-    ~EventPool() { for (auto e : ev) (void)hipEventDestroy(e); }
-    hipError_t make(size_t n) {
-        while (ev.size() < n) {
-            hipEvent_t e;
-            hipError_t r = hipEventCreate(&e);
-            if (r != hipSuccess) return r;
-            ev.push_back(e);
-        }
-        return hipSuccess;
-    }
-};
-
 float elapsed(hipEvent_t a, hipEvent_t b) {
     float ms = 0.0f;
     if (hipEventElapsedTime(&ms, a, b) != hipSuccess) { (void)hipGetLastError(); return 0.0f; }
     return ms;
+}
+
+// The host side of the sweep loop: the device status is read back after every
+// check_every sweeps (a poll).  With `ahead` the next poll's sweeps are
+// enqueued before a status is waited for, so that the device does not stand
+// still meanwhile (a wait and the launches after it cost about 25 us, the
+// sweeps of a small problem 8 x 15); what is enqueued past the stop returns at
+// once on the device, so the result is the same.  time_sweeps: every sweep
+// has its own event pair in the two polls that can be in flight.
+struct SweepLoop {
+    gabp_svm* h;
+    hipStream_t s;
+    int ce;
+    bool timed, ahead = true;
+    DevStatus hs{};
+    double kernel_ms = 0.0;
+    int64_t launches = 0;
+    int polls = 0, from[2] = {0, 0}, to[2] = {0, 0};
+    SweepLoop(gabp_svm* h_, hipStream_t s_) : h(h_), s(s_), ce(h_->p.check_every), timed(h_->p.time_sweeps != 0) {}
+
+    hipError_t prepare() {
+        const hipError_t e = h->evp.make(8 + (timed ? 4 * (size_t)ce : 0));
+        return e != hipSuccess ? e : h->pin_st.ensure(2 * sizeof(DevStatus));
+    }
+    // event pair of sweep t (null without time_sweeps)
+    hipEvent_t begin(int t) const { return timed ? h->evp.ev[8 + 2 * (size_t)(t % (2 * ce))] : nullptr; }
+    hipEvent_t end(int t) const { return timed ? h->evp.ev[9 + 2 * (size_t)(t % (2 * ce))] : nullptr; }
+
+    // Waits for poll k and takes its status.
+    hipError_t take(int k) {
+        const hipError_t e = hipEventSynchronize(h->evp.ev[6 + k % 2]);
+        if (e != hipSuccess) return e;
+        hs = static_cast<DevStatus*>(h->pin_st.p)[k % 2];
+        if (timed)
+            for (int u = from[k % 2]; u <= to[k % 2] && u < hs.t; ++u) {
+                kernel_ms += elapsed(begin(u), end(u));
+                ++launches;
+            }
+        return hipSuccess;
+    }
+    // After the launches of sweep t: *stop once the loop is over (hs is then
+    // the final status).
+    hipError_t step(int t, const DevStatus* st, bool* stop) {
+        *stop = false;
+        const bool over = t + 1 == h->p.max_sweeps;
+        if ((t + 1) % ce != 0 && !over) return hipSuccess;
+        const int k = polls++;
+        from[k % 2] = t / ce * ce;
+        to[k % 2] = t;
+        hipError_t e = hipMemcpyAsync(static_cast<DevStatus*>(h->pin_st.p) + k % 2, st, sizeof(DevStatus),
+                                      hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipEventRecord(h->evp.ev[6 + k % 2], s);
+        if (e == hipSuccess && ahead && k > 0) {
+            e = take(k - 1);
+            if (e == hipSuccess && hs.done) { *stop = true; return hipSuccess; }
+        }
+        if (e == hipSuccess && (!ahead || over)) {
+            e = take(k);
+            *stop = over || hs.done;
+        }
+        return e;
+    }
+};
+
+// Results of a solve: alpha, P~, A_ii (N doubles each) and the labels (N
+// floats), packed on the device and downloaded at once, with the trace.
+size_t out_bytes(int64_t N) { return (size_t)N * 28; }
+hipError_t fetch_results(gabp_svm* h, int64_t N, int sweeps, hipStream_t s) {
+    const size_t nb = out_bytes(N), nt = (size_t)std::max(sweeps, 0) * 8;
+    hipError_t e = h->pin.ensure(nb + nt);
+    if (e != hipSuccess) return e;
+    char* b = static_cast<char*>(h->pin.p);
+    e = hipMemcpyAsync(b + nt, h->out_d.p, nb, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess && nt) e = hipMemcpyAsync(b, h->trace_d.p, nt, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipEventRecord(h->evp.ev[5], s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    const double* t = reinterpret_cast<const double*>(b);
+    const double* d = reinterpret_cast<const double*>(b + nt);
+    const float* y = reinterpret_cast<const float*>(b + nt + 24 * (size_t)N);
+    h->trace.assign(t, t + std::max(sweeps, 0));
+    h->alpha.assign(d, d + N);
+    h->ptilde.assign(d + N, d + 2 * N);
+    h->adiag.assign(d + 2 * N, d + 3 * N);
+    h->yh.assign(y, y + N);
+    return hipSuccess;
 }
 
 // One solve, for RBF features (X != nullptr) or a dense kernel (K != nullptr).
@@ -301,7 +421,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     A(h->Pt, (size_t)R * NPAD * 8); A(h->S, (size_t)R * NPAD * 8);
     A(h->alpha_d, (size_t)N * 8); A(h->tmp, (size_t)NPAD * 8);
     A(h->blk1, (size_t)(NPAD / FB + 1) * 8); A(h->blk2, (size_t)(NPAD / FB + 1) * 8);
-    A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64);
+    A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64); A(h->out_d, out_bytes(N));
     A(h->trace_d, (size_t)p.max_sweeps * 8);
     if (rbf) {
         A(h->Xin, (size_t)N * m * 4); A(h->mean, (size_t)m * 8); A(h->nrm, (size_t)NPAD * 4);
@@ -318,11 +438,10 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
         return fail(h, GABP_E_NOMEM, std::string("device allocation failed: ") + hipGetErrorString(ae));
     }
 
-    EventPool evp;
     const int ce = p.check_every;
-    HIPCHK(h, evp.make(6 + 2 * (size_t)ce));
-    hipEvent_t* ev = evp.ev.data();
-    hipEvent_t* sev = ev + 6;
+    SweepLoop loop(h, s);
+    HIPCHK(h, loop.prepare());
+    hipEvent_t* ev = h->evp.ev.data();
 
     // ---- inputs and staging
     HIPCHK(h, hipEventRecord(ev[0], s));
@@ -610,12 +729,9 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     fa.part32 = sa.part32;
     fa.trace = h->trace_d.as<double>();
     fa.rule = rule;
-    DevStatus hs{};
-    double sweep_kernel_ms = 0.0;
-    int64_t launches = 0;
-    int polled = 0;
+    // a group visit is many launches: a poll ahead would cost more than the wait
+    loop.ahead = !grouped;
     for (int t = 0; t < p.max_sweeps; ++t) {
-        const int slot = t % ce;
         sa.slot_top = t % Rr;
         // every stateless sweep unrolls `depth` levels: the ring slots before
         // sweep 0 hold P~ = inf, S = 0, whose messages are exactly zero
@@ -627,13 +743,13 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
         if (!grouped) {
             // the events take the sweep dispatch's own timestamps
             HIPCHK(h, launch_sweep(prec, ksrc, gram, sa.levels, t == 0, ser, sa, s,
-                                   p.time_sweeps ? sev[2 * slot] : nullptr, p.time_sweeps ? sev[2 * slot + 1] : nullptr));
+                                   loop.begin(t), loop.end(t)));
             fa.Pt = wP; fa.S = wS; fa.Inv = wI; fa.Mean = wM;
             HIPCHK(h, launch_finalize(prec, fa, s));
         } else {
             // one visit per group: its messages, then its aggregates (the
             // timed span covers the visits and their group finalizes)
-            if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot], s));
+            if (p.time_sweeps) HIPCHK(h, hipEventRecord(loop.begin(t), s));
             const uint32_t* gl = h->glist.as<uint32_t>();
             for (int g = 0; g < G; ++g) {
                 HIPCHK(h, launch_sweep_grouped(prec, ksrc, gram, sa.levels, ser, sa, gl + g_within_off[g],
@@ -645,43 +761,22 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
                 fa.trace = (g == G - 1) ? h->trace_d.as<double>() : nullptr;
                 HIPCHK(h, launch_finalize(prec, fa, s));
             }
-            if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot + 1], s));
+            if (p.time_sweeps) HIPCHK(h, hipEventRecord(loop.end(t), s));
         }
-        if ((t + 1) % ce == 0 || t + 1 == p.max_sweeps) {
-            HIPCHK(h, hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
-            HIPCHK(h, hipStreamSynchronize(s));
-            if (p.time_sweeps) {
-                for (int u = polled; u <= t; ++u) {
-                    if (u >= hs.t) break;
-                    sweep_kernel_ms += elapsed(sev[2 * (u % ce)], sev[2 * (u % ce) + 1]);
-                    ++launches;
-                }
-            }
-            polled = t + 1;
-            if (hs.done) break;
-        }
+        bool stop = false;
+        HIPCHK(h, loop.step(t, st, &stop));
+        if (stop) break;
     }
+    const DevStatus hs = loop.hs;
     stored = cur_stored;
     HIPCHK(h, hipEventRecord(ev[4], s));
     const int final_slot = std::max(hs.t, 0) % (stored ? 1 : R);
 
     // ---- outputs
-    h->alpha.assign((size_t)N, 0.0);
-    h->ptilde.assign((size_t)N, 0.0);
-    h->adiag.assign((size_t)N, 0.0);
-    h->yh.assign((size_t)N, 0.0f);
-    HIPCHK(h, launch_convert_agg(prec, static_cast<char*>(h->Pt.p) + (size_t)final_slot * NPAD * agg_bytes,
-                                 h->tmp.as<double>(), N, s));
-    HIPCHK(h, hipMemcpyAsync(h->alpha.data(), h->alpha_d.p, (size_t)N * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipMemcpyAsync(h->ptilde.data(), h->tmp.p, (size_t)N * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipMemcpyAsync(h->adiag.data(), h->Adiag.p, (size_t)N * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipMemcpyAsync(h->yh.data(), h->yd.p, (size_t)N * 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipEventRecord(ev[5], s));
-    HIPCHK(h, hipStreamSynchronize(s));
-    h->trace.assign((size_t)std::max(hs.t, 0), 0.0);
-    if (hs.t > 0)
-        HIPCHK(h, hipMemcpy(h->trace.data(), h->trace_d.p, (size_t)hs.t * 8, hipMemcpyDeviceToHost));
+    HIPCHK(h, launch_pack_out(prec, N, h->alpha_d.as<double>(),
+                              static_cast<char*>(h->Pt.p) + (size_t)final_slot * NPAD * agg_bytes, 1,
+                              h->Adiag.as<double>(), h->yd.as<float>(), nullptr, h->out_d.as<double>(), s));
+    HIPCHK(h, fetch_results(h, N, hs.t, s));
 
     h->N = N; h->m = rbf ? m : 0; h->NB = NB; h->NPAD = NPAD; h->ntiles = nt; h->m_pad = m_pad;
     h->prec = prec; h->gram = gram; h->lam = lam; h->rbf = rbf;
@@ -698,8 +793,8 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     h->tm.kbuild_ms = elapsed(ev[1], ev[2]);
     h->tm.diag_ms = elapsed(ev[2], ev[3]);
     h->tm.sweep_loop_ms = elapsed(ev[3], ev[4]);
-    h->tm.sweep_kernel_ms = sweep_kernel_ms;
-    h->tm.sweep_launches = launches;
+    h->tm.sweep_kernel_ms = loop.kernel_ms;
+    h->tm.sweep_launches = loop.launches;
     h->tm.d2h_ms = elapsed(ev[4], ev[5]);
     h->tm.total_ms = now_ms() - t_start;
     h->plan = gabp_plan{};
@@ -799,8 +894,8 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     const double lam = (p.lambda_aug < 0.0) ? 1.0 / (double)N : p.lambda_aug;
     const double cut = -std::log(p.sparse_tau) / p.gamma;
     HIPCHK(h, hipSetDevice(p.device));
-    h->release_all();
 
+    // buffers of the previous solve are reused where large enough
     hipError_t ae = hipSuccess;
     auto A = [&](DevBuf& b, size_t n) { if (ae == hipSuccess) ae = b.ensure(std::max<size_t>(n, 16)); };
     A(h->tiles, (size_t)nt * 4);
@@ -824,7 +919,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     A(h->alpha_d, (size_t)N * 8); A(h->tmp, (size_t)NPAD * 8);
     A(h->blk1, (size_t)std::max<int64_t>(NPAD / WG + 1, WG) * 8);
     A(h->blk2, (size_t)std::max<int64_t>(NPAD / WG + 1, WG) * 8);
-    A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64);
+    A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64); A(h->out_d, out_bytes(N));
     A(h->trace_d, (size_t)p.max_sweeps * 8);
     A(h->sp_offi, (size_t)(N + 1) * 8); A(h->sp_offj, (size_t)(N + 1) * 8);
     A(h->sp_order, (size_t)N * 4); A(h->sp_Xp, (size_t)N * m * 4);
@@ -835,11 +930,10 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
         h->release_all();
         return fail(h, GABP_E_NOMEM, std::string("device allocation failed: ") + hipGetErrorString(ae));
     }
-    EventPool evp;
     const int ce = p.check_every;
-    HIPCHK(h, evp.make(6 + 2 * (size_t)ce));
-    hipEvent_t* ev = evp.ev.data();
-    hipEvent_t* sev = ev + 6;
+    SweepLoop loop(h, s);
+    HIPCHK(h, loop.prepare());
+    hipEvent_t* ev = h->evp.ev.data();
 
     // ---- inputs and staging (as the dense RBF solve)
     HIPCHK(h, hipEventRecord(ev[0], s));
@@ -1067,55 +1161,21 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     sw.st = st;
     sw.boxC = boxC;
     sw.rule = StopRule{p.tol_abs, p.tol_rel, p.stagnation_rel, p.max_sweeps, p.stagnation_window};
-    DevStatus hs{};
-    double sweep_kernel_ms = 0.0;
-    int64_t launches = 0;
-    int polled = 0;
     for (int t = 0; t < p.max_sweeps; ++t) {
-        const int slot = t % ce;
-        if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot], s));
+        if (p.time_sweeps) HIPCHK(h, hipEventRecord(loop.begin(t), s));
         HIPCHK(h, launch_sp_sweep(prec, sw, t + 1, s));
-        if (p.time_sweeps) HIPCHK(h, hipEventRecord(sev[2 * slot + 1], s));
-        if ((t + 1) % ce == 0 || t + 1 == p.max_sweeps) {
-            HIPCHK(h, hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
-            HIPCHK(h, hipStreamSynchronize(s));
-            if (p.time_sweeps) {
-                for (int u = polled; u <= t; ++u) {
-                    if (u >= hs.t) break;
-                    sweep_kernel_ms += elapsed(sev[2 * (u % ce)], sev[2 * (u % ce) + 1]);
-                    ++launches;
-                }
-            }
-            polled = t + 1;
-            if (hs.done) break;
-        }
+        if (p.time_sweeps) HIPCHK(h, hipEventRecord(loop.end(t), s));
+        bool stop = false;
+        HIPCHK(h, loop.step(t, st, &stop));
+        if (stop) break;
     }
+    const DevStatus hs = loop.hs;
     HIPCHK(h, hipEventRecord(ev[4], s));
 
-    // ---- outputs, back in input order (through partP as scratch)
-    h->alpha.assign((size_t)N, 0.0);
-    h->ptilde.assign((size_t)N, 0.0);
-    h->adiag.assign((size_t)N, 0.0);
-    h->yh.assign((size_t)N, 0.0f);
-    double* scr = h->partP.as<double>();
-    const int32_t* ord = h->sp_order.as<int32_t>();
-    HIPCHK(h, launch_sp_unpermute(h->alpha_d.as<double>(), ord, N, scr, s));
-    HIPCHK(h, hipMemcpyAsync(h->alpha.data(), scr, (size_t)N * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipStreamSynchronize(s));
-    HIPCHK(h, launch_sp_unpack_p(prec, N, sw.PS[hs.t & 1], h->tmp.as<double>(), s));
-    HIPCHK(h, launch_sp_unpermute(h->tmp.as<double>(), ord, N, scr, s));
-    HIPCHK(h, hipMemcpyAsync(h->ptilde.data(), scr, (size_t)N * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipStreamSynchronize(s));
-    HIPCHK(h, launch_sp_unpermute(h->Adiag.as<double>(), ord, N, scr, s));
-    HIPCHK(h, hipMemcpyAsync(h->adiag.data(), scr, (size_t)N * 8, hipMemcpyDeviceToHost, s));
-    if (mem == GABP_MEM_HOST) std::copy(y, y + N, h->yh.begin());
-    else HIPCHK(h, hipMemcpyAsync(h->yh.data(), y, (size_t)N * 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipEventRecord(ev[5], s));
-    HIPCHK(h, hipStreamSynchronize(s));
-    h->trace.assign((size_t)std::max(hs.t, 0), 0.0);
-    if (hs.t > 0)
-        HIPCHK(h, hipMemcpy(h->trace.data(), h->trace_d.p, (size_t)hs.t * 8, hipMemcpyDeviceToHost));
+    // ---- outputs, back in input order
+    HIPCHK(h, launch_pack_out(prec, N, h->alpha_d.as<double>(), sw.PS[hs.t & 1], 2, h->Adiag.as<double>(),
+                              h->yd.as<float>(), h->sp_order.as<int32_t>(), h->out_d.as<double>(), s));
+    HIPCHK(h, fetch_results(h, N, hs.t, s));
 
     h->N = N; h->m = m; h->NB = NB; h->NPAD = NPAD; h->ntiles = nt; h->m_pad = m_pad;
     h->prec = prec; h->gram = gram; h->lam = lam; h->rbf = true;
@@ -1134,8 +1194,8 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     h->tm.kbuild_ms = elapsed(ev[1], ev[2]);
     h->tm.diag_ms = elapsed(ev[2], ev[3]);
     h->tm.sweep_loop_ms = elapsed(ev[3], ev[4]);
-    h->tm.sweep_kernel_ms = sweep_kernel_ms;
-    h->tm.sweep_launches = launches;
+    h->tm.sweep_kernel_ms = loop.kernel_ms;
+    h->tm.sweep_launches = loop.launches;
     h->tm.d2h_ms = elapsed(ev[4], ev[5]);
     h->tm.total_ms = now_ms() - t_start;
     h->plan = gabp_plan{};
@@ -1253,7 +1313,14 @@ gabp_status gabp_svm_solve(gabp_svm* h, const float* X, const float* y, int64_t 
                            int32_t mem, void* stream) {
     if (!h) return GABP_E_INVALID;
     if (!X) return fail(h, GABP_E_INVALID, "X is NULL");
-    if (h->p.kernel == GABP_KERNEL_RBF_SPARSE) return solve_sparse_impl(h, X, y, N, m, mem, (hipStream_t)stream);
+    if (h->p.kernel == GABP_KERNEL_RBF_SPARSE) {
+        // (a solve that fails for memory has released every buffer: one that
+        // held some from the solve before it starts again without them)
+        const bool held = h->held() > 0;
+        const gabp_status st = solve_sparse_impl(h, X, y, N, m, mem, (hipStream_t)stream);
+        if (st != GABP_E_NOMEM || !held) return st;
+        return solve_sparse_impl(h, X, y, N, m, mem, (hipStream_t)stream);
+    }
     return solve_impl(h, X, nullptr, y, N, m, mem, (hipStream_t)stream);
 }
 
@@ -1584,6 +1651,8 @@ void gabp_svm_destroy(gabp_svm* h) {
     if (!h) return;
     (void)hipSetDevice(h->p.device);
     h->release_all();
+    h->pin.release();
+    h->pin_st.release();
     delete h;
 }
 
