@@ -633,6 +633,274 @@ struct MsgT {
     using T = typename std::conditional<F32, float, MT>::type;
 };
 
+// A tile's sums to its partial slots, or, with `out`, to the caller (a chunk
+// adds them up first).
+template <class AT>
+__device__ inline void put_tile_sums(const SweepArgs& a, const TileCoord& tc, AT rowP, AT rowE, const AT (&cP)[4],
+                                     const AT (&cE)[4], TileSums<AT>* out, int split, int sub) {
+    if (out) {
+        out->rp = rowP; out->re = rowE;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) { out->cp[c] = cP[c]; out->ce[c] = cE[c]; }
+        return;
+    }
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, rows = TILE / split;
+    const bool p32 = a.part32 != 0;
+    const PartSlots ps{a.NB, split};
+    if (tid / rows == sub) {
+        const size_t rowslot = ps.row(tc.I, tc.J) + tid;
+        put_part(a.partP, rowslot, rowP, p32);
+        put_part(a.partE, rowslot, rowE, p32);
+    }
+    if (l < 16) {
+        const size_t cb = ps.col(tc.I, tc.J, sub) + w * 64 + l * 4;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) { put_part(a.partP, cb + c, cP[c], p32); put_part(a.partE, cb + c, cE[c], p32); }
+    }
+}
+
+// Series sweeps of at most three levels as sums over powers of a = K'_ij
+// (mom_plan): with u = 1/P~, primes marking the level (u, S of sweep t - 1; u',
+// m' = S'/P~' of t - 2; m'' of t - 3) the series' messages into node j expand to
+//   P_ij = -a^2 u_i + a^4 u_i^2 u'_j
+//   E_ij = -a u_i S_i - a^2 u_i m'_j + a^3 u'_j (u_i^2 S_i - u_i m''_i) + a^4 u_i^2 u'_j m'_j
+// (one level: the first term of each; two: m'' = 0; three levels of form 3
+// leave out a^5 u_i^2 u'_j^2 m''_i, rr^4), so that a node's sums are its own
+// factors times sums of a^k x_k with x_1 = u S, x_2 = u, x_3 = u^2 S - u m'',
+// x_4 = u^2 of its neighbours: per pair the powers of a and one FMA per power
+// and direction, 8 or 11 VALU slots where the recursion level by level takes
+// 17, and three or four values per node in registers.  The a^4 terms are at
+// most rr^3 of the aggregates; MIXED plans take three levels only below 2^-30
+// and leave them out, 64 times under the precision of their FP32 messages
+// (FP32 takes them from 2^-24 on, where they would show).
+template <int D, int SER> constexpr bool mom_plan() {
+    return SER > 0 && (D == 1 || (D == 2 && SER == 1) || (D == 3 && SER == 3));
+}
+template <class XT, bool XF, int D> struct Mom {
+    static constexpr bool Q3 = D >= 2, Q4 = D == 2 || (D == 3 && !XF);
+    XT x1, x2, x3, x4;           // of a node as the source of messages
+    XT ku, km;                   // u', m' of a node as their target
+};
+
+// W consecutive values of a ring (W = 4: 16-byte aligned).
+template <int W, class T> __device__ inline void ld_nodes(const T* p, T (&v)[W]) {
+    if constexpr (W == 4) {
+        const V4<T> x = ld4(p);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = x.v[c];
+    } else {
+        static_assert(W == 1, "one node or four");
+        v[0] = p[0];
+    }
+}
+
+// Factors of W consecutive nodes for the moment sums.
+template <int W, class XT, bool XF, int D, class AT>
+__device__ inline void mom_nodes(const SweepArgs& a, int slot_top, int64_t node, Mom<XT, XF, D> (&m)[W]) {
+    const AT* HP = static_cast<const AT*>(a.HP);
+    const AT* HS = static_cast<const AT*>(a.HS);
+    const AT* HI = static_cast<const AT*>(a.HI);
+    const AT* HM = static_cast<const AT*>(a.HM);
+    // 1/P~ and S/P~ from the rings when the finalize formed them (the same
+    // IEEE quotients)
+    auto inv = [&](int64_t o, AT (&v)[W]) {
+        ld_nodes<W>((HI ? HI : HP) + o, v);
+        if (!HI)
+#pragma unroll
+            for (int c = 0; c < W; ++c) v[c] = (AT)1 / v[c];
+    };
+    auto mean = [&](int64_t o, AT (&v)[W]) {
+        ld_nodes<W>((HM ? HM : HS) + o, v);
+        if (!HM) {
+            AT p[W];
+            ld_nodes<W>(HP + o, p);
+#pragma unroll
+            for (int c = 0; c < W; ++c) v[c] = v[c] / p[c];
+        }
+    };
+    const int64_t o = (int64_t)slot_top * a.NPAD + node;
+    const int64_t o1 = (int64_t)((slot_top - 1 + a.R) % a.R) * a.NPAD + node;
+    const int64_t o2 = (int64_t)((slot_top - 2 + a.R) % a.R) * a.NPAD + node;
+    AT u[W], s[W], ku[W], km[W], mm[W];
+    inv(o, u);
+    ld_nodes<W>(HS + o, s);
+    if constexpr (D >= 2) { inv(o1, ku); mean(o1, km); }
+    if constexpr (D >= 3) mean(o2, mm);
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+        m[c].x1 = (XT)(u[c] * s[c]);
+        m[c].x2 = (XT)u[c];
+        m[c].x4 = (XT)(u[c] * u[c]);
+        if constexpr (D >= 2) {
+            m[c].ku = (XT)ku[c];
+            m[c].km = (XT)km[c];
+            AT z = u[c] * s[c];
+            if constexpr (D >= 3) z -= mm[c];
+            m[c].x3 = (XT)(u[c] * z);
+        } else {
+            m[c].x3 = m[c].ku = m[c].km = 0;
+        }
+    }
+}
+
+// Sums of a node's messages from its moment sums.
+template <class T, bool Q3, bool Q4>
+__device__ inline void mom_sums(T m1, T m2, T m3, T m4, T ku, T km, T& p, T& e) {
+    p = Q4 ? fma(ku, m4, -m2) : -m2;
+    if constexpr (Q3) e = fma(ku, Q4 ? fma(km, m4, m3) : m3, -fma(km, m2, m1));
+    else e = -m1;
+}
+
+// sweep_tile for the plans of mom_plan.
+template <class ST, class MT, class AT, int KSRC, int GK, int D, int SER>
+__device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot_top, TileSums<AT>* out, int split,
+                                      int sub) {
+    using XT = typename MsgT<ST, MT, AT, SER>::T;
+    constexpr bool XF = MsgT<ST, MT, AT, SER>::F32;
+    using MM = Mom<XT, XF, D>;
+    constexpr bool Q3 = MM::Q3, Q4 = MM::Q4;
+    const uint32_t ij = a.tiles[tile];
+    const TileCoord tc{(int)(ij >> 16), (int)(ij & 0xFFFFu)};
+    const size_t tbase = (size_t)tile * TT;
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 4, q = l & 15;
+    const int col0 = w * 64 + q * 4;
+    const ST* Kp = static_cast<const ST*>(a.Kp);
+    const uint32_t lo = (uint32_t)(g * TILE + col0);
+    const int bb0 = sub * (TILE / 32 / split), bb1 = bb0 + TILE / 32 / split;
+    const int u0 = 8 * bb0, u1 = 8 * bb1;
+    constexpr bool RING = (KSRC == KSRC_PLANE) && std::is_same<ST, float>::value;
+    constexpr int KR = RING ? KRING : 1;
+    __shared__ __attribute__((aligned(16))) float kring[KR][4][RING ? 256 : 4];
+    if constexpr (RING) {
+#pragma unroll
+        for (int u = 0; u < KR; ++u)
+            dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)(u0 + u) * 4 * TILE, lo * 4u,
+                  lds_offset(&kring[u][w][0]));
+    }
+    // row nodes: x_1 .. x_4 and (u', m'); column nodes: (u', m'), needed at
+    // the end only
+    typedef XT X4 __attribute__((ext_vector_type(4)));
+    typedef XT X2 __attribute__((ext_vector_type(2)));
+    __shared__ X4 sx[TILE];
+    __shared__ X2 sk[Q3 ? TILE : 1], sc[Q3 ? TILE : 1];
+    using RT = typename std::conditional<XF, XT, AT>::type;
+    __shared__ RT rP[4][TILE], rE[4][TILE];
+    __shared__ RT red[4][2][2][64];
+    __shared__ float kband[KSRC == KSRC_RECOMPUTE ? 4 : 1][KSRC == KSRC_RECOMPUTE ? 32 * 64 : 1];
+    {
+        MM m[1];
+        mom_nodes<1, XT, XF, D, AT>(a, slot_top, (int64_t)tc.I * TILE + tid, m);
+        sx[tid] = X4{m[0].x1, m[0].x2, m[0].x3, m[0].x4};
+        if constexpr (Q3) sk[tid] = X2{m[0].ku, m[0].km};
+    }
+    XT y1[4], y2[4], y3[4], y4[4];
+    {
+        MM m[4];
+        mom_nodes<4, XT, XF, D, AT>(a, slot_top, (int64_t)tc.J * TILE + col0, m);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            y1[c] = m[c].x1; y2[c] = m[c].x2; y3[c] = m[c].x3; y4[c] = m[c].x4;
+            if constexpr (Q3) {
+                if (g == 0) sc[col0 + c] = X2{m[c].ku, m[c].km};
+            }
+        }
+    }
+    XT c1[4] = {0, 0, 0, 0}, c2[4] = {0, 0, 0, 0}, c3[4] = {0, 0, 0, 0}, c4[4] = {0, 0, 0, 0};
+    __syncthreads();
+
+    size_t off = tbase + (size_t)u0 * 4 * TILE;
+    V4<ST> k{};
+    if constexpr (!RING && KSRC == KSRC_PLANE) k = ld4nt(lane_ptr(Kp + off, lo));
+    for (int b = bb0; b < bb1; ++b) {
+        if constexpr (KSRC == KSRC_RECOMPUTE) {
+            gram_band<GK>(a.F, a.kp, tc.I, tc.J, 32 * b, 64 * w, kband[w]);
+            wave_lds_sync();
+        }
+        // (not unrolled: four steps with static ring slots take 137 instead of 97 VGPRs
+        // and 154 instead of 147 us at N = 20,000)
+#pragma unroll 1
+        for (int s2 = 0; s2 < 8; ++s2) {
+            const int r = 32 * b + 4 * s2 + g;
+            const int u = b * 8 + s2;                 // row step
+            const size_t off2 = (u + 1 < u1) ? off + 4 * TILE : off;
+            V4<ST> k2;
+            if constexpr (RING) {
+                if (u + KR <= u1) wait_vm<KR - 1>();
+                else wait_vm<0>();
+                const float4 kk = *reinterpret_cast<const float4*>(&kring[u % KR][w][4 * l]);
+                k = V4<ST>{{(ST)kk.x, (ST)kk.y, (ST)kk.z, (ST)kk.w}};
+            } else if constexpr (KSRC == KSRC_PLANE) {
+                k2 = ld4nt(lane_ptr(Kp + off2, lo));
+            } else {
+                const float4 kk = *reinterpret_cast<const float4*>(&kband[w][(4 * s2 + g) * 64 + 4 * q]);
+                k = V4<ST>{{(ST)kk.x, (ST)kk.y, (ST)kk.z, (ST)kk.w}};
+            }
+            const X4 x = sx[r];
+            XT m1 = 0, m2 = 0, m3 = 0, m4 = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const XT av = (XT)k.v[c], a2 = av * av;
+                c1[c] = fma(av, x[0], c1[c]);
+                m1 = fma(av, y1[c], m1);
+                c2[c] = fma(a2, x[1], c2[c]);
+                m2 = fma(a2, y2[c], m2);
+                if constexpr (Q3) {
+                    const XT a3 = a2 * av;
+                    c3[c] = fma(a3, x[2], c3[c]);
+                    m3 = fma(a3, y3[c], m3);
+                }
+                if constexpr (Q4) {
+                    const XT a4 = a2 * a2;
+                    c4[c] = fma(a4, x[3], c4[c]);
+                    m4 = fma(a4, y4[c], m4);
+                }
+            }
+            XT rp, re;
+            const X2 f = Q3 ? sk[r] : X2{0, 0};
+            mom_sums<XT, Q3, Q4>(m1, m2, m3, m4, f[0], f[1], rp, re);
+            // row sums over the 16 column lanes through LDS every two row
+            // steps (as in sweep_tile)
+            red[w][0][s2 & 1][l] = (RT)rp;
+            red[w][1][s2 & 1][l] = (RT)re;
+            if (s2 & 1) {
+                wave_lds_sync();
+                const int qty = l >> 5, idx = l & 31, stp = idx >> 4, gg = (idx >> 2) & 3, pt = idx & 3;
+                const RT* src = &red[w][qty][stp][16 * gg + 4 * pt];
+                RT v = (src[0] + src[1]) + (src[2] + src[3]);
+                v = v + dpp<0xB1>(v);
+                v = v + dpp<0x4E>(v);
+                const int row = 32 * b + 4 * ((s2 & 6) + stp) + gg;
+                if (pt == 0) {
+                    if (qty == 0) rP[w][row] = v;
+                    else rE[w][row] = v;
+                }
+                wave_lds_sync();
+            }
+            if constexpr (RING) {
+                if (u + KR < u1)
+                    dma16(reinterpret_cast<const float*>(Kp) + tbase + (size_t)(u + KR) * 4 * TILE, lo * 4u,
+                          lds_offset(&kring[u % KR][w][0]));
+            } else if constexpr (KSRC == KSRC_PLANE) {
+                k = k2;
+            }
+            off = off2;
+        }
+        if constexpr (KSRC == KSRC_RECOMPUTE) wave_lds_sync();
+    }
+    AT cP[4], cE[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const X2 f = Q3 ? sc[col0 + c] : X2{0, 0};
+        mom_sums<AT, Q3, Q4>((AT)c1[c], (AT)c2[c], (AT)c3[c], (AT)c4[c], (AT)f[0], (AT)f[1], cP[c], cE[c]);
+        cP[c] = sum_groups(cP[c]);
+        cE[c] = sum_groups(cE[c]);
+    }
+    __syncthreads();
+    const AT rowP = ((AT)rP[0][tid] + (AT)rP[1][tid]) + ((AT)rP[2][tid] + (AT)rP[3][tid]);
+    const AT rowE = ((AT)rE[0][tid] + (AT)rE[1][tid]) + ((AT)rE[2][tid] + (AT)rE[3][tid]);
+    put_tile_sums<AT>(a, tc, rowP, rowE, cP, cE, out, split, sub);
+}
+
 // One synchronous sweep over all tiles.  Template parameters:
 //   ST storage type of K' and the message planes, MT type of the top-level
 //   update (cavity denominators, reciprocals), AT aggregate type;
@@ -663,6 +931,10 @@ struct MsgT {
 template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER>
 __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top, TileSums<AT>* out = nullptr,
                                   int split = 1, int sub = 0) {
+    if constexpr (mom_plan<D, SER>()) {
+        sweep_tile_mom<ST, MT, AT, KSRC, GK, D, SER>(a, tile, slot_top, out, split, sub);
+        return;
+    } else {
     DevStatus* st = a.st;
     // lower levels: FP32 storage precision; with the series and up to three
     // levels they run in the top level's type (FP64 FMA issues at the FP32
@@ -1010,23 +1282,7 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
     if (__any(bad) && l == 0) st->bad = 1;
     const AT rowP = ((AT)rP[0][tid] + (AT)rP[1][tid]) + ((AT)rP[2][tid] + (AT)rP[3][tid]);
     const AT rowE = ((AT)rE[0][tid] + (AT)rE[1][tid]) + ((AT)rE[2][tid] + (AT)rE[3][tid]);
-    if (out) {
-        out->rp = rowP; out->re = rowE;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) { out->cp[c] = cP[c]; out->ce[c] = cE[c]; }
-        return;
-    }
-    const bool p32 = a.part32 != 0;
-    const PartSlots ps{NB, split};
-    if (tid >= 4 * u0 && tid < 4 * u1) {
-        const size_t rowslot = ps.row(tc.I, tc.J) + tid;
-        put_part(a.partP, rowslot, rowP, p32);
-        put_part(a.partE, rowslot, rowE, p32);
-    }
-    if (g == 0) {
-        const size_t cb = ps.col(tc.I, tc.J, sub) + col0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) { put_part(a.partP, cb + c, cP[c], p32); put_part(a.partE, cb + c, cE[c], p32); }
+    put_tile_sums<AT>(a, tc, rowP, rowE, cP, cE, out, split, sub);
     }
 }
 
