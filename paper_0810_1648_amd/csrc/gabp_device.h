@@ -1381,6 +1381,181 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void
                                                               blockIdx.x % a.split);
 }
 
+// Three-level series sweep (form 3, FP32 messages) with K' recomputed from
+// augmented rows of MP features, in the MFMA's own layout: a wave forms 32 x 32
+// blocks of its 32-row band against the tile's eight column blocks (B
+// fragments staged once per workgroup, as in k_gram_sums), a lane holding 16
+// rows of one column.  Each K' entry goes from the MFMA output through exp2
+// straight into the moment sums (mom_plan): the rows' factors and sums stay in
+// registers over the band, a column's over the block.  No K' band passes
+// through LDS, and nothing is reduced across lanes but one vector per band.
+// 13 VALU slots per pair (exp2 4, + lambda^2, a^2, a^3, six FMAs) beside the
+// MFMAs; the VALU is busy for three quarters of the time.  N = 120,000, m =
+// 20: 8.0 (bands through LDS, level by level) -> 7.3 (moment sums) -> 5.0 ms
+// per sweep; three waves per SIMD with 80 bytes of spills take as long.
+template <int KIND, int MP>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_sweep_rc_mom(SweepArgs a) {
+    if (a.st->done) return;
+    using MM = Mom<float, true, 3>;
+    using BS = BStage<KIND>;
+    typedef float X4 __attribute__((ext_vector_type(4)));
+    typedef float X2 __attribute__((ext_vector_type(2)));
+    constexpr int CH = BS::NP * (MP / 16) * 64, PR = (CH + WG - 1) / WG, NS = MP / 16;
+    __shared__ bf16x8 sb[2][CH];
+    __shared__ __attribute__((aligned(16))) float sx[3][TILE];   // x_1 .. x_3 of the row nodes
+    __shared__ X4 sy[TILE];                     // ... of the column nodes
+    __shared__ X2 sk[TILE], sc[TILE];           // u', m'
+    __shared__ float cs[4][3][TILE];            // column sums per wave
+    const int split = a.split, sub = blockIdx.x % split;
+    const uint32_t ij = a.tiles[blockIdx.x / split];
+    const TileCoord tc{(int)(ij >> 16), (int)(ij & 0xFFFFu)};
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, h = l >> 5, l32 = l & 31;
+    const int64_t i0 = (int64_t)tc.I * TILE, j0 = (int64_t)tc.J * TILE;
+    const float lam2 = (float)a.kp.lam2;
+    // this thread's 16-byte chunks of a staged block: plane, row and column of
+    // the row-major planes, in the order of BStage
+    const uint16_t* const bt = a.F.aug1 + j0 * MP;
+    int64_t so[PR];
+#pragma unroll
+    for (int i = 0; i < PR; ++i) {
+        const int k = tid + WG * i, pl = k / (64 * NS), rem = k % (64 * NS);
+        so[i] = pl * a.F.aug_plane + rem / (2 * NS) * MP + rem % (2 * NS) * 8;
+        if (k < CH) sb[0][BS::dst(NS, k)] = *reinterpret_cast<const bf16x8*>(bt + so[i]);
+    }
+    {
+        MM m[1];
+        mom_nodes<1, float, true, 3, double>(a, a.slot_top, i0 + tid, m);
+        sx[0][tid] = m[0].x1; sx[1][tid] = m[0].x2; sx[2][tid] = m[0].x3;
+        sk[tid] = X2{m[0].ku, m[0].km};
+        mom_nodes<1, float, true, 3, double>(a, a.slot_top, j0 + tid, m);
+        sy[tid] = X4{m[0].x1, m[0].x2, m[0].x3, 0.0f};
+        sc[tid] = X2{m[0].ku, m[0].km};
+    }
+    __syncthreads();
+    const int passes = 2 / split;
+    const bool p32 = a.part32 != 0;
+    const PartSlots ps{a.NB, split};
+    int cur = 0;
+#pragma unroll 1
+    for (int pass = 0; pass < passes; ++pass) {
+        const int band = 4 * (sub * passes + pass) + w;
+        RowFrag<KIND, MP> fa;
+        {
+            const uint16_t* const at = a.F.aug0 + (i0 + band * 32 + l32) * MP + 8 * h;
+#pragma unroll
+            for (int st = 0; st < NS; ++st) {
+                fa.hi[st] = *reinterpret_cast<const bf16x8*>(at + 16 * st);
+                if constexpr (BS::NP >= 2) fa.lo[st] = *reinterpret_cast<const bf16x8*>(at + a.F.aug_plane + 16 * st);
+                if constexpr (BS::NP >= 3)
+                    fa.lo2[st] = *reinterpret_cast<const bf16x8*>(at + 2 * a.F.aug_plane + 16 * st);
+            }
+        }
+        float r1[16], r2[16], r3[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) r1[r] = r2[r] = r3[r] = 0.0f;
+#pragma unroll 1
+        for (int cb = 0; cb < TILE / 32; ++cb) {
+            // the next block (the first again after the last of a pass)
+            const bool more = !(pass == passes - 1 && cb == TILE / 32 - 1);
+            const int nb0 = ((cb + 1) % (TILE / 32)) * 32 * MP;
+            bf16x8 pre[PR];
+            if (more) {
+#pragma unroll
+                for (int i = 0; i < PR; ++i) {
+                    const int k = tid + WG * i;
+                    if (k < CH) pre[i] = *reinterpret_cast<const bf16x8*>(bt + so[i] + nb0);
+                }
+            }
+            f32x16 acc = {};
+            BS::template mma<MP>(fa, sb[cur], NS, l, acc);
+            const int col = cb * 32 + l32;
+            const X4 y = sy[col];
+            // the index test matters only on diagonal tiles and past N
+            if (!((tc.I < tc.J) && (j0 + cb * 32 + 32 <= a.kp.N))) {
+                const int64_t j = j0 + col;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t i = i0 + band * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+                    const float kv = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(acc[r]), 0.0f, 1.0f) + lam2;
+                    acc[r] = (i < j && j < a.kp.N) ? kv : 0.0f;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    acc[r] = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(acc[r]), 0.0f, 1.0f) + lam2;
+            }
+            float c1 = 0.0f, c2 = 0.0f, c3 = 0.0f;
+            // four consecutive rows at a time (one 16-byte LDS read per factor)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int o = band * 32 + 8 * t + 4 * h;
+                const X4 x1 = *reinterpret_cast<const X4*>(&sx[0][o]), x2 = *reinterpret_cast<const X4*>(&sx[1][o]),
+                         x3 = *reinterpret_cast<const X4*>(&sx[2][o]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = 4 * t + v;
+                    const float av = acc[r], a2 = av * av, a3 = a2 * av;
+                    c1 = fmaf(av, x1[v], c1);
+                    r1[r] = fmaf(av, y[0], r1[r]);
+                    c2 = fmaf(a2, x2[v], c2);
+                    r2[r] = fmaf(a2, y[1], r2[r]);
+                    c3 = fmaf(a3, x3[v], c3);
+                    r3[r] = fmaf(a3, y[2], r3[r]);
+                }
+            }
+            // (the row sums are formed here: the compiler otherwise carries a,
+            // a^2 and a^3 over into the next block, 48 registers)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(r1[r]), "+v"(r2[r]), "+v"(r3[r]));
+            // the column's 32 rows of this band: both lane halves
+            c1 = c1 + __shfl_xor(c1, 32);
+            c2 = c2 + __shfl_xor(c2, 32);
+            c3 = c3 + __shfl_xor(c3, 32);
+            if (h == 0) {
+                if (pass > 0) { c1 += cs[w][0][col]; c2 += cs[w][1][col]; c3 += cs[w][2][col]; }
+                cs[w][0][col] = c1; cs[w][1][col] = c2; cs[w][2][col] = c3;
+            }
+            if (more) {
+#pragma unroll
+                for (int i = 0; i < PR; ++i) {
+                    const int k = tid + WG * i;
+                    if (k < CH) sb[cur ^ 1][BS::dst(NS, k)] = pre[i];
+                }
+            }
+            __syncthreads();
+            cur ^= 1;
+        }
+        // the band's row sums over the 32 columns a half holds; lane r of a
+        // half keeps row r's
+        float vp = 0.0f, ve = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const X2 f = sk[band * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
+            float p, e;
+            mom_sums<float, true, false>(r1[r], r2[r], r3[r], 0.0f, f[0], f[1], p, e);
+            p = sum16(p);
+            e = sum16(e);
+            p = p + __shfl_xor(p, 16);
+            e = e + __shfl_xor(e, 16);
+            if (l32 == r) { vp = p; ve = e; }
+        }
+        if (l32 < 16) {
+            const size_t o = ps.row(tc.I, tc.J) + band * 32 + 8 * (l32 >> 2) + 4 * h + (l32 & 3);
+            put_part(a.partP, o, (double)vp, p32);
+            put_part(a.partE, o, (double)ve, p32);
+        }
+    }
+    double m[3], p, e;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        m[k] = ((double)cs[0][k][tid] + (double)cs[1][k][tid]) + ((double)cs[2][k][tid] + (double)cs[3][k][tid]);
+    const X2 f = sc[tid];
+    mom_sums<double, true, false>(m[0], m[1], m[2], 0.0, (double)f[0], (double)f[1], p, e);
+    const size_t o = ps.col(tc.I, tc.J, sub) + tid;
+    put_part(a.partP, o, p, p32);
+    put_part(a.partE, o, e, p32);
+}
+
 // ------------------------------------------------ grouped (Gauss-Seidel) --
 //
 // Grouped schedule: the block rows are split into G ordered groups and a
@@ -1891,6 +2066,15 @@ inline hipError_t sweep_d(bool first, const SweepArgs& a, hipStream_t s, hipEven
     if constexpr (D == 0) {
         if (first) {
             launch_ev(k_sweep<ST, MT, AT, KSRC, GK, D, true, 0>, g, blk, s, e0, e1, a);
+            return hipSuccess;
+        }
+    }
+    if constexpr (KSRC == KSRC_RECOMPUTE && GK != GRAM_F32 && D == 3 && SER == 3 && MsgT<ST, MT, AT, SER>::F32) {
+        // K' straight from the MFMA output: augmented rows of 32 or 64
+        // features, at least one band per wave
+        if (a.F.aug0 && a.split <= 2 && (a.F.m_pad == 32 || a.F.m_pad == 64)) {
+            if (a.F.m_pad == 32) launch_ev(k_sweep_rc_mom<GK, 32>, g, blk, s, e0, e1, a);
+            else launch_ev(k_sweep_rc_mom<GK, 64>, g, blk, s, e0, e1, a);
             return hipSuccess;
         }
     }
