@@ -911,7 +911,14 @@ __device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot
 //      from the aggregates of the D - 1 earlier sweeps held in the ring (a
 //      slot from before sweep 0 holds P~ = inf, S = 0 and yields exactly zero
 //      messages), lower levels in LT (see below);
-//   FIRST: the stored planes are all zero (sweep 1) and are not read.
+//   FIRST: the stored planes are all zero (sweep 1) and are not read;
+//   XL, WR (stored state): the planes hold the messages of XL sweeps before
+//      the previous one, and the XL sweeps between are formed again from the
+//      aggregates of their time (ring slots slot_top - XL .. slot_top - 1),
+//      each message rounded to ST as it was when stored elsewhere, so that the
+//      result is the same to the bit; WR: this sweep's messages are written.
+//      Writing every kStoredPeriod-th sweep only takes 20 + 16 / period bytes
+//      per FP32 pair instead of 36.
 // Work of one tile: its row and column sums go to the tile's partial slots,
 // or, with `out`, to the caller (a chunk adds them up first).  split > 1: only
 // the sub-th of `split` equal row parts of the tile.  SER (stateless
@@ -928,7 +935,7 @@ __device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot
 // level (reverse messages zero) is G = u, F = -S/P~ of its source and costs
 // nothing, a middle level costs four operations per direction (two with
 // G = u).
-template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER>
+template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER, int XL = 0, bool WR = true>
 __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top, TileSums<AT>* out = nullptr,
                                   int split = 1, int sub = 0) {
     if constexpr (mom_plan<D, SER>()) {
@@ -1037,6 +1044,19 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
         pqj[c] = ptj[c] * ptj[c];
     }
     if constexpr (SQ1) sPq[tid] = sPt[tid] * sPt[tid];
+    // stored state, sweeps between: aggregates of their time per row and column
+    constexpr int XN = XL > 0 ? XL : 1, XR = XL > 0 ? TILE : 1;
+    __shared__ __attribute__((aligned(16))) XT xrP[XN][XR], xrS[XN][XR], xcP[XN][XR], xcS[XN][XR];
+    if constexpr (XL > 0) {
+#pragma unroll
+        for (int m = 0; m < XL; ++m) {
+            const int64_t base = (int64_t)((slot_top - XL + m + a.R) % a.R) * a.NPAD;
+            xrP[m][tid] = (XT)HP[base + (int64_t)tc.I * TILE + tid];
+            xrS[m][tid] = (XT)HS[base + (int64_t)tc.I * TILE + tid];
+            xcP[m][tid] = (XT)HP[base + (int64_t)tc.J * TILE + tid];
+            xcS[m][tid] = (XT)HS[base + (int64_t)tc.J * TILE + tid];
+        }
+    }
     // lower levels per node: P~ (exact) or u = 1/P~ (series) at every level;
     // exact: S at every level; series: S and u^2 at the middle levels, S/P~
     // at the deepest
@@ -1142,6 +1162,22 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
                 XT opf, opb, oef, oeb;
                 if constexpr (STORED) {
                     opf = (XT)pf.v[c]; opb = (XT)pb.v[c]; oef = (XT)ef.v[c]; oeb = (XT)eb.v[c];
+                    if constexpr (XL > 0) {
+                        const XT a2 = av * av;
+#pragma unroll
+                        for (int m = 0; m < XL; ++m) {
+                            // (a product fused into the next difference would
+                            // skip the rounding that storing it brought)
+#pragma clang fp contract(off)
+                            const XT rf = rcp_fast(xrP[m][r] - opb), rb = rcp_fast(xcP[m][col0 + c] - opf);
+                            const XT nef = (XT)(ST)(-av * (xrS[m][r] - oeb) * rf);
+                            const XT neb = (XT)(ST)(-av * (xcS[m][col0 + c] - oef) * rb);
+                            opf = (XT)(ST)(-a2 * rf);
+                            opb = (XT)(ST)(-a2 * rb);
+                            oef = nef;
+                            oeb = neb;
+                        }
+                    }
                 } else if constexpr (SER) {
                     // G = P / (-a^2), F = E / a of the previous sweep's messages,
                     // rebuilt from the deepest level up (XT = LT on this path)
@@ -1218,9 +1254,11 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
                     eji_m = -av * (sj[c] - oef) * rb;
                 }
                 if constexpr (STORED) {
-                    // the aggregates add the values as stored
+                    // the aggregates add the values as stored (also where this
+                    // sweep's are not: no product fused into the sum)
+#pragma clang fp contract(off)
                     const ST pij = (ST)pij_m, eij = (ST)eij_m, pji = (ST)pji_m, eji = (ST)eji_m;
-                    npf.v[c] = pij; nef.v[c] = eij; npb.v[c] = pji; neb.v[c] = eji;
+                    if constexpr (WR) { npf.v[c] = pij; nef.v[c] = eij; npb.v[c] = pji; neb.v[c] = eji; }
                     cP[c] += (AT)pij; cE[c] += (AT)eij;     // received by column node j
                     rp += (AT)pji; re += (AT)eji;            // received by row node i
                 } else if constexpr (XF) {
@@ -1232,8 +1270,10 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
                 }
             }
             if constexpr (STORED) {
-                st4nt(lane_ptr(Pf + off, lo), npf); st4nt(lane_ptr(Pb + off, lo), npb);
-                st4nt(lane_ptr(Ef + off, lo), nef); st4nt(lane_ptr(Eb + off, lo), neb);
+                if constexpr (WR) {
+                    st4nt(lane_ptr(Pf + off, lo), npf); st4nt(lane_ptr(Pb + off, lo), npb);
+                    st4nt(lane_ptr(Ef + off, lo), nef); st4nt(lane_ptr(Eb + off, lo), neb);
+                }
                 rp = sum16(rp);
                 re = sum16(re);
                 if (q == 0) { rP[w][r] = rp; rE[w][r] = re; }
@@ -1286,10 +1326,10 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
     }
 }
 
-template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER>
+template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER, int XL = 0, bool WR = true>
 __global__ __launch_bounds__(WG) void k_sweep(SweepArgs a) {
     if (a.st->done) return;
-    sweep_tile<ST, MT, AT, KSRC, GK, D, FIRST, SER>(a, blockIdx.x / a.split, a.slot_top, nullptr, a.split,
+    sweep_tile<ST, MT, AT, KSRC, GK, D, FIRST, SER, XL, WR>(a, blockIdx.x / a.split, a.slot_top, nullptr, a.split,
                                                     blockIdx.x % a.split);
 }
 
@@ -2063,7 +2103,23 @@ inline hipError_t sweep_d(bool first, const SweepArgs& a, hipStream_t s, hipEven
             return hipErrorInvalidValue;
         }
     }
-    if constexpr (D == 0) {
+    if constexpr (D == 0 && KSRC == KSRC_PLANE) {
+        // sweep a.between + 1 of its period: the planes written by the last
+        // one only (before the first period's end they are zero)
+        static_assert(kStoredPeriod == 3, "one instantiation per sweep of the period");
+        if (a.period != kStoredPeriod || a.between < 0 || a.between >= kStoredPeriod) return hipErrorInvalidValue;
+#define GABP_ST(F_, X_) launch_ev(k_sweep<ST, MT, AT, KSRC, GK, 0, F_, 0, X_, X_ == kStoredPeriod - 1>, g, blk, s, e0, e1, a)
+        switch (a.between + (first ? kStoredPeriod : 0)) {
+            case 0: GABP_ST(false, 0); break;
+            case 1: GABP_ST(false, 1); break;
+            case 2: GABP_ST(false, 2); break;
+            case 3: GABP_ST(true, 0); break;
+            case 4: GABP_ST(true, 1); break;
+            default: GABP_ST(true, 2); break;
+        }
+#undef GABP_ST
+        return hipSuccess;
+    } else if constexpr (D == 0) {
         if (first) {
             launch_ev(k_sweep<ST, MT, AT, KSRC, GK, D, true, 0>, g, blk, s, e0, e1, a);
             return hipSuccess;

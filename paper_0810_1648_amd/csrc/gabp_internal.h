@@ -157,6 +157,13 @@ inline int tile_split(int64_t items) {
 // part_slots(K) of them are in use.
 __host__ __device__ inline int part_stride(int NB, int split) { return NB * split + 1; }
 __host__ __device__ inline int part_slots(int K, int NB, int split) { return split * (K + 1) + NB - K; }
+// Synchronous sweeps with stored pair records over a K' plane (single solves)
+// write the records every third sweep and form the sweeps between again from
+// the aggregates: 25.3 bytes per FP32 pair and sweep instead of 36, for one
+// more message level per sweep on average.  N = 20,011 (2.0e8 pairs, 7.2 GB of
+// planes) 116 -> 77 ms per solve of 76 sweeps, the same to the bit; a period
+// of four would save 5% of the bytes more and take another level in registers.
+constexpr int kStoredPeriod = 3;
 // Storage index of tile (I, J), I <= J: row-major over the upper triangle.
 __host__ __device__ inline int64_t tile_index(int I, int J, int NB) {
     return (int64_t)I * NB - (int64_t)I * (I - 1) / 2 + (J - I);
@@ -213,6 +220,8 @@ struct SweepArgs {
     int64_t nchunks;
     int chunk;                    // tiles per chunk side (0 or 1: one tile per workgroup)
     int split;                    // row parts per tile (1 with chunks)
+    int period, between;          // stored state: sweeps per write of the planes (0 or 1: every sweep), and how
+                                  // many sweeps before this one they were last written
     DevStatus* st;
     Features F;                   // KSRC_RECOMPUTE
     KernelParams kp;

@@ -388,7 +388,10 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     // and stateless waits for the contraction bound computed after the
     // diagonal weighting; the planes are allocated only if stored wins.
     const bool probe = stored && p.edge_state == GABP_EDGE_AUTO;
-    const int R = (stored && !probe) ? 1 : 8;
+    // (synchronous stored sweeps over the plane write their records every
+    // kStoredPeriod-th sweep and keep the aggregates of the sweeps between)
+    const int period = (kmat && !grouped) ? kStoredPeriod : 1;
+    const int R = (stored && !probe) ? period : 8;
     {
         // buffers of the previous solve are reused where large enough (a
         // repeated solve of the same shape allocates nothing); everything is
@@ -622,7 +625,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
 
     // ---- sweeps
     const size_t agg_bytes = (prec == PREC_FP32) ? 4 : 8;
-    const int Rr = cur_stored ? 1 : R;
+    const int Rr = cur_stored ? period : R;
     // series sweeps: per-node 1/P~ and S/P~ rings, formed by the finalize
     // once per node (without them every tile forms the same quotients)
     void* hinv = nullptr;
@@ -659,6 +662,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     sa.nchunks = nchunks;
     sa.chunk = chunked ? 2 : 1;
     sa.split = chunked ? 1 : split;
+    sa.period = cur_stored ? period : 1;
     sa.st = st;
     sa.F = F;
     sa.kp = kp;
@@ -736,13 +740,14 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
         // every stateless sweep unrolls `depth` levels: the ring slots before
         // sweep 0 hold P~ = inf, S = 0, whose messages are exactly zero
         sa.levels = cur_stored ? 0 : depth;
+        sa.between = t % period;
         char* wP = static_cast<char*>(h->Pt.p) + (size_t)((t + 1) % Rr) * NPAD * agg_bytes;
         char* wS = static_cast<char*>(h->S.p) + (size_t)((t + 1) % Rr) * NPAD * agg_bytes;
         char* wI = hinv ? static_cast<char*>(hinv) + (size_t)((t + 1) % Rr) * NPAD * agg_bytes : nullptr;
         char* wM = hmean ? static_cast<char*>(hmean) + (size_t)((t + 1) % Rr) * NPAD * agg_bytes : nullptr;
         if (!grouped) {
             // the events take the sweep dispatch's own timestamps
-            HIPCHK(h, launch_sweep(prec, ksrc, gram, sa.levels, t == 0, ser, sa, s,
+            HIPCHK(h, launch_sweep(prec, ksrc, gram, sa.levels, t < sa.period, ser, sa, s,
                                    loop.begin(t), loop.end(t)));
             fa.Pt = wP; fa.S = wS; fa.Inv = wI; fa.Mean = wM;
             HIPCHK(h, launch_finalize(prec, fa, s));
@@ -770,7 +775,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     const DevStatus hs = loop.hs;
     stored = cur_stored;
     HIPCHK(h, hipEventRecord(ev[4], s));
-    const int final_slot = std::max(hs.t, 0) % (stored ? 1 : R);
+    const int final_slot = std::max(hs.t, 0) % Rr;
 
     // ---- outputs
     HIPCHK(h, launch_pack_out(prec, N, h->alpha_d.as<double>(),
