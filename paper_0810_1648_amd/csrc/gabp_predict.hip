@@ -150,6 +150,67 @@ __global__ __launch_bounds__(WG) void k_predict_mfma(Features Ft, Features Fq, c
     }
 }
 
+// FP32 features of exactly MP columns: k_predict_mfma with all of a block's B
+// fragment in flight at once.  The general form tests every k-step against the
+// row length, which keeps each load behind its own branch and its latency in
+// front of its four MFMAs (256 cycles): 10,007 queries on 20,000 points of 100
+// features 585 -> 420 us, 70% of the rate of a large FP32 product.
+template <int MP>
+__global__ __launch_bounds__(WG) void k_predict_f32(Features Ft, Features Fq, const double* __restrict__ w,
+                                                    int64_t nblk32, int bpc, float neg_gamma_log2e, int64_t NQPAD,
+                                                    double* __restrict__ part) {
+    constexpr int NS = MP / 8;
+    const int wv = threadIdx.x >> 6, l = threadIdx.x & 63, h = l >> 5, l32 = l & 31;
+    const int64_t q0 = (int64_t)blockIdx.x * QB + wv * 32;
+    float ni[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ni[r] = Fq.nrm[q0 + 8 * (r >> 2) + 4 * h + (r & 3)];
+    f32x4v fa[NS], fb[NS];
+    auto load = [&](const float* x, int64_t row, f32x4v (&f)[NS]) {
+        const float* p = x + row * MP + h * (MP / 2);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) f[s] = *reinterpret_cast<const f32x4v*>(p + 4 * s);
+    };
+    load(Fq.f32, q0 + l32, fa);
+    double acc[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0;
+    const int64_t b0 = (int64_t)blockIdx.y * bpc;
+    const int64_t b1 = (b0 + bpc < nblk32) ? b0 + bpc : nblk32;
+    if (b0 < b1) load(Ft.f32, b0 * 32 + l32, fb);
+    for (int64_t b = b0; b < b1; ++b) {
+        const int64_t colB = b * 32 + l32;
+        const float nj = Ft.nrm[colB];
+        const double wj = w[colB];
+        f32x4v fn[NS];
+        load(Ft.f32, (b + 1 < b1) ? colB + 32 : colB, fn);
+        f32x16 g = {};
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) g = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s][e], fb[s][e], g, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float d2 = fmaxf(ni[r] + nj - 2.0f * g[r], 0.0f);
+            acc[r] = fma((double)__builtin_amdgcn_exp2f(neg_gamma_log2e * d2), wj, acc[r]);
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) fb[s] = fn[s];
+    }
+    // sum over the 32 training rows held by lanes l % 32 of each half
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        double v = sum16(acc[r]);
+        v = v + __shfl_xor(v, 16);
+        acc[r] = v;
+    }
+    if (l32 == 0) {
+        double* out = part + (int64_t)blockIdx.y * NQPAD + q0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) out[8 * (r >> 2) + 4 * h + (r & 3)] = acc[r];
+    }
+}
+
 // BF16 Gram kinds with m_pad <= MP: the workgroup's four waves share every
 // 32-row training block, so the block's B fragments (all split planes) are
 // staged once in LDS, in fragment order (chunk (plane, step, lane) holds the
@@ -595,6 +656,18 @@ void predict_kind(int mp, dim3 grid, const Features& Ft, const Features& Fq, con
             hipLaunchKernelGGL((k_predict_lds<KIND, 64>), grid, dim3(WG), 0, s, Ft, Fq, w, nblk32, bpc, c, NQPAD, part);
             return;
         }
+    }
+    if constexpr (KIND == GRAM_F32) {
+#define GABP_WIDE(M) case M: hipLaunchKernelGGL((k_predict_f32<M>), grid, dim3(WG), 0, s, Ft, Fq, w, nblk32, bpc, c, NQPAD, part); return
+        switch (mp) {
+            GABP_WIDE(64);
+            GABP_WIDE(80);
+            GABP_WIDE(96);
+            GABP_WIDE(112);
+            GABP_WIDE(128);
+            default: break;
+        }
+#undef GABP_WIDE
     }
     if (mp <= 32)
         hipLaunchKernelGGL((k_predict_mfma<KIND, 32>), grid, dim3(WG), 0, s, Ft, Fq, w, nblk32, bpc, c, NQPAD, part);
