@@ -155,6 +155,7 @@ struct Req {
 };
 
 constexpr int kRing = 8;   // aggregate ring slots (stateless form)
+constexpr int kSide = 3;   // streams beside the main one for a step's sweeps
 
 void plan_sizes(Req& r) {
     const size_t st = (r.prec == PREC_FP64) ? 8 : 4;
@@ -194,6 +195,13 @@ struct gabp_server {
     gabp_server_params p{};
     Arena arena;
     hipStream_t stream = nullptr;
+    // A step's launch groups touch different requests, and most of their
+    // launches fill only part of the chip: their sweeps run on up to four
+    // streams, forked from and joined to the main one (four is HIP's number
+    // of hardware queues).  A burst of 48 requests in ten groups takes 49
+    // ms, on one stream 53.
+    hipStream_t side[kSide] = {};
+    hipEvent_t fork = nullptr, join[kSide] = {};
     std::thread worker;
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
@@ -658,22 +666,44 @@ void worker_loop(gabp_server* S) {
         for (int k = 0; k < S->p.steps_per_poll && e == hipSuccess; ++k) {
             e = build_step(S, k, plan);
             const uint2* items = S->step_lists.empty() ? nullptr : S->step_lists[k].d;
+            // the groups with work, the longest first, each to the stream with
+            // the least so far (items weigh by their message levels)
+            struct Job { gabp_server::Group* G; std::pair<int64_t, int> dir, win; double load; };
+            std::vector<Job> jobs;
             size_t gi = 0;
             for (auto& kv : S->groups) {
                 auto& G = kv.second;
                 const auto dir = plan.dir[gi], win = plan.win[gi];
                 ++gi;
-                if (!G.nslots || e != hipSuccess) continue;
+                if (!G.nslots) continue;
+                const double items = G.grouped ? (double)dir.second + 2.0 * win.second : 2.0 * G.ntiles;
+                jobs.push_back(Job{&G, dir, win, items * (2.0 + G.levels)});
+            }
+            std::sort(jobs.begin(), jobs.end(), [](const Job& x, const Job& y) { return x.load > y.load; });
+            const int nside = std::min<int>(kSide, (int)jobs.size() - 1);
+            if (e == hipSuccess && nside > 0) e = hipEventRecord(S->fork, S->stream);
+            for (int u = 0; u < nside && e == hipSuccess; ++u) e = hipStreamWaitEvent(S->side[u], S->fork, 0);
+            double sum[kSide + 1] = {};
+            for (const Job& j : jobs) {
+                if (e != hipSuccess) break;
+                const int u = (int)(std::min_element(sum, sum + nside + 1) - sum);
+                sum[u] += j.load;
+                hipStream_t st = u == 0 ? S->stream : S->side[u - 1];
+                const auto& G = *j.G;
                 if (G.grouped) {
                     // stored records: the tiles inside the group (both directions), then the crossing ones
-                    if (win.second)
-                        e = launch_served_sweep(G.prec, G.levels, G.ser, false, S->d_reqs, items + win.first, win.second,
-                                                S->stream);
+                    if (j.win.second)
+                        e = launch_served_sweep(G.prec, G.levels, G.ser, false, S->d_reqs, items + j.win.first,
+                                                j.win.second, st);
                     if (e == hipSuccess)
-                        e = launch_served_sweep(G.prec, G.levels, G.ser, true, S->d_reqs, items + dir.first,
-                                                dir.second, S->stream);
+                        e = launch_served_sweep(G.prec, G.levels, G.ser, true, S->d_reqs, items + j.dir.first,
+                                                j.dir.second, st);
                 } else
-                    e = launch_served_sweep(G.prec, G.levels, G.ser, false, S->d_reqs, G.d_tiles, G.ntiles, S->stream);
+                    e = launch_served_sweep(G.prec, G.levels, G.ser, false, S->d_reqs, G.d_tiles, G.ntiles, st);
+            }
+            for (int u = 0; u < nside && e == hipSuccess; ++u) {
+                e = hipEventRecord(S->join[u], S->side[u]);
+                if (e == hipSuccess) e = hipStreamWaitEvent(S->stream, S->join[u], 0);
             }
             if (e == hipSuccess && plan.n_f32)
                 e = launch_served_finalize(true, S->d_reqs, items + plan.off_f32, plan.n_f32, S->stream);
@@ -771,6 +801,10 @@ gabp_status gabp_server_create(const gabp_server_params* params, gabp_server** o
     const int A = params->max_active;
     bool ok = S->arena.init(arena) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&S->stream, hipStreamNonBlocking) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&S->fork, hipEventDisableTiming) == hipSuccess;
+    for (int u = 0; u < kSide && ok; ++u)
+        ok = hipStreamCreateWithFlags(&S->side[u], hipStreamNonBlocking) == hipSuccess &&
+             hipEventCreateWithFlags(&S->join[u], hipEventDisableTiming) == hipSuccess;
     ok = ok && hipMalloc((void**)&S->d_reqs, (size_t)A * sizeof(ReqDesc)) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&S->h_reqs, (size_t)A * sizeof(ReqDesc), hipHostMallocDefault) == hipSuccess;
     ok = ok && hipMalloc((void**)&S->d_stat, (size_t)A * sizeof(DevStatus)) == hipSuccess;
@@ -917,6 +951,8 @@ void gabp_server_destroy(gabp_server* S) {
     if (S->worker.joinable()) S->worker.join();
     (void)hipSetDevice(S->p.device);
     if (S->stream) (void)hipStreamSynchronize(S->stream);
+    for (hipStream_t t : S->side)
+        if (t) (void)hipStreamSynchronize(t);
     for (auto& kv : S->groups) {
         auto& G = kv.second;
         if (G.d_tiles) (void)hipFree(G.d_tiles);
@@ -933,6 +969,11 @@ void gabp_server_destroy(gabp_server* S) {
     if (S->d_stat) (void)hipFree(S->d_stat);
     if (S->h_stat) (void)hipHostFree(S->h_stat);
     S->arena.destroy();
+    for (hipStream_t t : S->side)
+        if (t) (void)hipStreamDestroy(t);
+    for (hipEvent_t t : S->join)
+        if (t) (void)hipEventDestroy(t);
+    if (S->fork) (void)hipEventDestroy(S->fork);
     if (S->stream) (void)hipStreamDestroy(S->stream);
     for (auto& kv : S->reqs) delete kv.second;
     delete S;
