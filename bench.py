@@ -33,6 +33,26 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 VALU_PEAK_GSLOT = 256 * 64 * 2.4
 # dense MFMA peaks (MI355X, no sparsity)
 MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
+
+
+def moment_plan(levels, series):
+    """Plans whose sweep sums powers of K' (mom_plan in gabp_device.h)."""
+    return levels >= 1 and (levels == 1 and series > 0 or levels == 2 and series == 1 or levels == 3 and series == 3)
+
+
+def sweep_slots_per_pair(levels, series, precision="mixed"):
+    """VALU issue slots per pair of one stateless sweep as it runs: sums over
+    powers of K' take the powers beyond the first (one multiply each) and one
+    multiply-add per power and direction, two powers at one level, four at two
+    levels and in FP32 / FP64 at three, three in MIXED at three; other plans
+    rebuild the messages level by level."""
+    series = int(series)
+    if not moment_plan(levels, series):
+        return stateless_slots_per_pair(levels, series, precision)
+    powers = 2 if levels == 1 else 3 if levels == 3 and precision == "mixed" else 4
+    return powers - 1 + 2 * powers
+
+
 # K' of one pair recomputed inside the sweep, beyond the MFMA Gram: the
 # distance (norm sum, -2 g, clamp: 3), the scale (1), exp2 (a transcendental:
 # 4) and + lambda^2 (1); from augmented rows, whose Gram is the exponent, the
@@ -44,6 +64,26 @@ RECOMPUTE_AUG_SLOTS_PER_PAIR = 6
 def recompute_slots(plan):
     """VALU slots per pair of K' recomputed in the sweep (the plan's form)."""
     return RECOMPUTE_AUG_SLOTS_PER_PAIR if plan.get("recompute_aug", 0) else RECOMPUTE_SLOTS_PER_PAIR
+
+
+def moment_recompute(plan, precision="mixed"):
+    """Whether the recompute sweep takes its powers straight from the MFMA
+    output (k_sweep_rc_mom)."""
+    return bool(plan.get("recompute_aug", 0)) and precision == "mixed" and \
+        plan["stateless_depth"] == 3 and int(plan["series_reciprocal"]) == 3
+
+
+def recompute_sweep_slots(plan, precision="mixed"):
+    """VALU slots per pair of the recompute sweep as it runs; in the moment
+    form from augmented rows the clamp is exp2's modifier (no slot)."""
+    return sweep_slots_per_pair(plan["stateless_depth"], plan["series_reciprocal"], precision) + \
+        recompute_slots(plan) - (1 if moment_recompute(plan, precision) else 0)
+
+
+def recompute_label(plan, precision="mixed"):
+    return f"k_sweep_rc{'_mom' if moment_recompute(plan, precision) else ''} (stateless, K' recomputed)"
+
+
 # decision function on augmented rows (the MFMA emits the scaled exponent),
 # VALU slots per (query, training point) pair: exp2 with its clamp modifier
 # (a transcendental: 4 slots) and the FP32 multiply-add of the weighted sum
@@ -614,11 +654,11 @@ def main():
         # pair-record planes): HBM-bound on its algorithmic bytes
         roof = hbm_roof(plan, avg_ms, klaunch, sweep_label(plan, edge_name), traffic)
     else:
-        roof = {"bound": "alu", "kernel": "k_sweep_rc (stateless, K' recomputed)", "traffic": None}
+        roof = {"bound": "alu", "kernel": recompute_label(plan, a.precision), "traffic": None}
     if stateless:
-        slots = stateless_slots_per_pair(plan["stateless_depth"], int(plan["series_reciprocal"]), a.precision)
+        slots = sweep_slots_per_pair(plan["stateless_depth"], int(plan["series_reciprocal"]), a.precision)
         if recompute:
-            slots += recompute_slots(plan)
+            slots = recompute_sweep_slots(plan, a.precision)
         valu = slots * pairs / (avg_ms * 1e-3) / 1e9 if klaunch else None
         roof.update({"valu_slots_per_pair": slots, "valu_gslot_per_s": valu, "valu_peak_gslot_per_s": VALU_PEAK_GSLOT,
                      "valu_frac": (valu / VALU_PEAK_GSLOT) if valu else None,
@@ -638,7 +678,7 @@ def main():
                       "sweeps_per_solve": sinfo["sweeps_per_solve"], "reason": sinfo["reason"],
                       "err_vs_oracle": rel_err(sinfo["alpha"], aref),
                       "rel_diff_alpha_vs_main": rel_err(sinfo["alpha"], info["alpha"]),
-                      "roofline": hbm_roof(sp, sk_ / max(sl_, 1), sl_, "k_sweep (stored, K' materialised)",
+                      "roofline": hbm_roof(sp, sk_ / max(sl_, 1), sl_, "k_sweep_st (stored, K' materialised)",
                                            counter_traffic_kernel(a.traffic_json, sweep_kernel_name(a.precision, sp)))}
         print(f"[bench] stored state: {ss_} sweeps in {sw_:.3f} s", file=sys.stderr, flush=True)
 
@@ -690,8 +730,7 @@ def main():
         g4 = ginfo4["plan"]
         pairs4 = wl4.N * (wl4.N - 1) / 2.0
         ms4 = gk4 / max(gl4, 1)
-        slots4 = stateless_slots_per_pair(g4["stateless_depth"], int(g4["series_reciprocal"]), "mixed") + \
-            recompute_slots(g4)
+        slots4 = recompute_sweep_slots(g4)
         v4 = slots4 * pairs4 / (ms4 * 1e-3) / 1e9 if gl4 else None
         mp4 = (wl4.m + 15) // 16 * 16
         mf4 = 2.0 * mp4 * 6 * pairs4 / (ms4 * 1e-3) / 1e12 if gl4 else None
@@ -701,7 +740,7 @@ def main():
                  "stateless_depth": g4["stateless_depth"], "device_bytes": g4["device_bytes"],
                  "err_vs_oracle": rel_err(ginfo4["alpha"], r4["alpha"] if r4 is not None else None),
                  "certificate": ginfo4["certificate"],
-                 "roofline": {"bound": "alu", "kernel": "k_sweep_rc (stateless, K' recomputed)", "achieved": v4,
+                 "roofline": {"bound": "alu", "kernel": recompute_label(g4), "achieved": v4,
                               "peak": VALU_PEAK_GSLOT, "unit": "Gslot/s", "frac": v4 / VALU_PEAK_GSLOT if v4 else None,
                               "valu_slots_per_pair": slots4, "avg_launch_ms": ms4, "launches": gl4,
                               "mfma_issued_tflops": mf4, "mfma_frac": mf4 / MFMA_PEAK_TFLOPS["bf16"] if mf4 else None,

@@ -1326,10 +1326,18 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
     }
 }
 
-template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER, int XL = 0, bool WR = true>
+template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER>
 __global__ __launch_bounds__(WG) void k_sweep(SweepArgs a) {
     if (a.st->done) return;
-    sweep_tile<ST, MT, AT, KSRC, GK, D, FIRST, SER, XL, WR>(a, blockIdx.x / a.split, a.slot_top, nullptr, a.split,
+    sweep_tile<ST, MT, AT, KSRC, GK, D, FIRST, SER>(a, blockIdx.x / a.split, a.slot_top, nullptr, a.split,
+                                                    blockIdx.x % a.split);
+}
+
+// stored records over the plane, written every kStoredPeriod sweeps
+template <class ST, class MT, class AT, int KSRC, int GK, bool FIRST, int XL, bool WR>
+__global__ __launch_bounds__(WG) void k_sweep_st(SweepArgs a) {
+    if (a.st->done) return;
+    sweep_tile<ST, MT, AT, KSRC, GK, 0, FIRST, 0, XL, WR>(a, blockIdx.x / a.split, a.slot_top, nullptr, a.split,
                                                     blockIdx.x % a.split);
 }
 
@@ -2108,7 +2116,7 @@ inline hipError_t sweep_d(bool first, const SweepArgs& a, hipStream_t s, hipEven
         // one only (before the first period's end they are zero)
         static_assert(kStoredPeriod == 3, "one instantiation per sweep of the period");
         if (a.period != kStoredPeriod || a.between < 0 || a.between >= kStoredPeriod) return hipErrorInvalidValue;
-#define GABP_ST(F_, X_) launch_ev(k_sweep<ST, MT, AT, KSRC, GK, 0, F_, 0, X_, X_ == kStoredPeriod - 1>, g, blk, s, e0, e1, a)
+#define GABP_ST(F_, X_) launch_ev(k_sweep_st<ST, MT, AT, KSRC, GK, F_, X_, X_ == kStoredPeriod - 1>, g, blk, s, e0, e1, a)
         switch (a.between + (first ? kStoredPeriod : 0)) {
             case 0: GABP_ST(false, 0); break;
             case 1: GABP_ST(false, 1); break;

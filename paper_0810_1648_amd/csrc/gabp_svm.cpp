@@ -819,7 +819,8 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     h->plan.n_blocks = NB;
     h->plan.n_tiles = nt;
     h->plan.device_bytes = h->held();
-    h->plan.alg_bytes_per_pair = (double)st_bytes * ((stored ? 8.0 : 0.0) + (kmat ? 1.0 : 0.0));
+    // stored records: read in every sweep, written in every period-th
+    h->plan.alg_bytes_per_pair = (double)st_bytes * ((stored ? 4.0 + 4.0 / sa.period : 0.0) + (kmat ? 1.0 : 0.0));
     h->plan.alg_bytes_per_sweep = (uint64_t)((double)N * (double)(N - 1) / 2.0 * h->plan.alg_bytes_per_pair);
     h->sparse = false;
     h->n_edges = 0;
