@@ -671,40 +671,36 @@ __global__ void k_sp_prune(const uint32_t* __restrict__ tiles, int64_t nt, int64
 // B row i (a copy of A's first m columns) gets (-1/2, -n_i/2), each value
 // split into the Gram kind's planes as the features are (hi, then the BF16
 // remainders), so that sum_k a_ik b_jk = x_i . x_j - n_i/2 - n_j/2 for the
-// products the kind forms.  One thread per row; columns past m + 1 stay 0.
-__global__ void k_sp_augment(int64_t NPAD, int64_t m, int m_pad, int kind, const float* __restrict__ nrm,
+// products the kind forms.  Columns past m + 1 stay 0.  One thread per value,
+// so that accesses are contiguous (a thread per row: 327 us, a thread per value 31 us
+// for 200,000 rows).
+__global__ void k_sp_augment(int64_t NPAD, int m, int m_pad, int kind, const float* __restrict__ nrm,
                              float* f32a, uint16_t* hia, uint16_t* loa, uint16_t* lo2a, float* f32b,
                              uint16_t* hib, uint16_t* lob, uint16_t* lo2b) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= NPAD) return;
-    const int64_t o = i * m_pad;
-    const float n = nrm[i], nb = -0.5f * n;
+    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (o >= NPAD * m_pad) return;
+    const int64_t i = o / m_pad;
+    const int k = (int)(o - i * m_pad);
+    const float n = nrm[i];
+    // (A's value where it is not a feature, B's)
+    const float va = k == m ? n : 1.0f, vb = k == m ? -0.5f : k == m + 1 ? -0.5f * n : 0.0f;
+    const bool extra = k == m || k == m + 1;
     if (kind == GRAM_F32) {
-        for (int64_t k = 0; k < m; ++k) f32b[o + k] = f32a[o + k];
-        f32a[o + m] = n;
-        f32a[o + m + 1] = 1.0f;
-        f32b[o + m] = -0.5f;
-        f32b[o + m + 1] = nb;
-        for (int64_t k = m + 2; k < m_pad; ++k) f32b[o + k] = 0.0f;
+        if (extra) f32a[o] = va;
+        f32b[o] = k < m ? f32a[o] : vb;
         return;
     }
     const bool x3 = (kind == GRAM_BF16X3 || kind == GRAM_BF16X6), x6 = (kind == GRAM_BF16X6);
-    for (int64_t k = 0; k < m_pad; ++k) {
-        hib[o + k] = (k < m) ? hia[o + k] : 0;
-        if (x3) lob[o + k] = (k < m) ? loa[o + k] : 0;
-        if (x6) lo2b[o + k] = (k < m) ? lo2a[o + k] : 0;
-    }
     uint16_t h, l, l2;
-    split3(n, h, l, l2);
-    hia[o + m] = h;
-    hia[o + m + 1] = f2bf(1.0f);
-    hib[o + m] = f2bf(-0.5f);
-    if (x3) { loa[o + m] = l; loa[o + m + 1] = 0; lob[o + m] = 0; }
-    if (x6) { lo2a[o + m] = l2; lo2a[o + m + 1] = 0; lo2b[o + m] = 0; }
-    split3(nb, h, l, l2);
-    hib[o + m + 1] = h;
-    if (x3) lob[o + m + 1] = l;
-    if (x6) lo2b[o + m + 1] = l2;
+    split3(vb, h, l, l2);
+    hib[o] = k < m ? hia[o] : h;
+    if (x3) lob[o] = k < m ? loa[o] : l;
+    if (x6) lo2b[o] = k < m ? lo2a[o] : l2;
+    if (!extra) return;
+    split3(va, h, l, l2);
+    hia[o] = h;
+    if (x3) loa[o] = l;
+    if (x6) lo2a[o] = l2;
 }
 
 template <int KIND>
@@ -768,7 +764,7 @@ hipError_t launch_sp_augment(int64_t NPAD, int64_t m, int m_pad, int kind, const
                              uint16_t* hia, uint16_t* loa, uint16_t* lo2a, float* f32b, uint16_t* hib,
                              uint16_t* lob, uint16_t* lo2b, hipStream_t s) {
     if (m + 2 > m_pad) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_sp_augment, dim3(blocks(NPAD)), dim3(WG), 0, s, NPAD, m, m_pad, kind, nrm, f32a, hia, loa,
+    hipLaunchKernelGGL(k_sp_augment, dim3(blocks(NPAD * m_pad)), dim3(WG), 0, s, NPAD, (int)m, m_pad, kind, nrm, f32a, hia, loa,
                        lo2a, f32b, hib, lob, lo2b);
     return hipGetLastError();
 }
