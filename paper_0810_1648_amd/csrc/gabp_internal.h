@@ -330,7 +330,7 @@ hipError_t launch_sweep_grouped_f64(int ksrc, int gram, int levels, int ser, con
 // FA, FB: the augmented A and B rows (launch_sp_augment), whose Gram is
 // -d^2 / 2.
 hipError_t launch_sp_count(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles,
-                           int64_t stride, int64_t N, float cut, int32_t* counts, hipStream_t s);
+                           int64_t stride, int64_t N, float cut, int64_t* counts, hipStream_t s);
 hipError_t launch_sp_fill(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles, int64_t N,
                           float cut, float neg_gamma_log2e, float lam2, int64_t cap, unsigned long long* cursor, int sh,
                           uint64_t* keys, float* kv, hipStream_t s);
@@ -339,7 +339,9 @@ hipError_t launch_sp_fill(const Features& FA, const Features& FB, const uint32_t
 hipError_t launch_sp_augment(int64_t NPAD, int64_t m, int m_pad, int kind, const float* nrm, float* f32a,
                              uint16_t* hia, uint16_t* loa, uint16_t* lo2a, float* f32b, uint16_t* hib,
                              uint16_t* lob, uint16_t* lo2b, hipStream_t s);
-hipError_t sp_scan(void* tmp, size_t* bytes, const int32_t* in, int64_t* out, int64_t n, hipStream_t s);
+// Exclusive sums of n 64-bit values (64 bits on both sides: the scan adds in
+// its input's type, and the sums of all rows pass 2^31 from 2^30 kept pairs on).
+hipError_t sp_scan(void* tmp, size_t* bytes, const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
 // The tile list in super-blocked order (S x S tiles per super-block, NB
 // blocks per side), through the key buffers k0, k1 (nt entries each).
 hipError_t sp_tile_order(void* tmp, size_t* bytes, uint32_t* tiles, int64_t nt, int S, int NB, uint64_t* k0,
@@ -368,7 +370,7 @@ hipError_t launch_sp_offsets(const uint64_t* keys, int64_t E, int sh, int64_t N,
 // the rows of all nodes (neighbour, K') from row[k] (the exclusive sums of the
 // lengths), a node's i-end edges first; at most 2 E + 4 N entries.  qrow: the
 // node of every quad.
-hipError_t launch_sp_rowlen(int64_t N, const int64_t* off_i, const int64_t* off_j, int32_t* len, hipStream_t s);
+hipError_t launch_sp_rowlen(int64_t N, const int64_t* off_i, const int64_t* off_j, int64_t* len, hipStream_t s);
 hipError_t launch_sp_rows(int64_t E, int64_t N, int sh, const int32_t* ei, const int32_t* ej, const float* kv,
                           const uint64_t* keys_t, const float* kv_t, const int64_t* off_i, const int64_t* off_j,
                           const int64_t* row, int32_t* col, float* rkv, int32_t* qrow, hipStream_t s);

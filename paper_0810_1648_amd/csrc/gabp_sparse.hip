@@ -118,7 +118,7 @@ __device__ inline void sp_tiles(const Features& FA, const Features& FB, const ui
 // count per launched tile; the host sums a strided sample to size the fill.
 template <int KIND, int MP>
 __global__ __launch_bounds__(WG) void k_sp_count(Features FA, Features FB, const uint32_t* __restrict__ tiles, int64_t stride,
-                                                 int64_t N, float cut, int32_t* __restrict__ counts) {
+                                                 int64_t N, float cut, int64_t* __restrict__ counts) {
     __shared__ int wsum[4];
     int c = 0;   // wave-uniform
     sp_tiles<KIND, MP>(FA, FB, tiles + (int64_t)blockIdx.x * stride, 0, 1, N, cut, [&](const f32x16& g0, const f32x16& g1, int64_t, int64_t, float hc) {
@@ -235,11 +235,11 @@ __global__ void k_sp_offsets(const uint64_t* __restrict__ keys, int64_t E, int s
 
 // Row lengths: a node's edges of both ends in whole quads, at least one.
 __global__ void k_sp_rowlen(int64_t N, const int64_t* __restrict__ off_i, const int64_t* __restrict__ off_j,
-                            int32_t* __restrict__ len) {
+                            int64_t* __restrict__ len) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k > N) return;
     const int64_t d = (k < N) ? (off_i[k + 1] - off_i[k]) + (off_j[k + 1] - off_j[k]) : 0;
-    len[k] = (k < N) ? (d > 0 ? (int32_t)((d + 3) / 4 * 4) : 4) : 0;
+    len[k] = (k < N) ? (d > 0 ? (d + 3) / 4 * 4 : 4) : 0;
 }
 
 // Rows (neighbour, K'): node k's row begins at row[k] with its i-end edges,
@@ -705,7 +705,7 @@ __global__ void k_sp_augment(int64_t NPAD, int m, int m_pad, int kind, const flo
 
 template <int KIND>
 void sp_build_kind(bool fill, int mp, dim3 g, const Features& FA, const Features& FB, const uint32_t* tiles, int64_t stride, int64_t N,
-                   float cut, float c, float lam2, int32_t* counts, int64_t cap, unsigned long long* cursor, int sh,
+                   float cut, float c, float lam2, int64_t* counts, int64_t cap, unsigned long long* cursor, int sh,
                    uint64_t* keys, float* kv, hipStream_t s) {
     const dim3 gf((unsigned)(((int64_t)g.x + SP_TPW - 1) / SP_TPW));
 #define GABP_SP_LAUNCH(MPV)                                                                                  \
@@ -726,7 +726,7 @@ void sp_build_kind(bool fill, int mp, dim3 g, const Features& FA, const Features
 }
 
 hipError_t sp_build(bool fill, const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles,
-                    int64_t stride, int64_t N, float cut, float c, float lam2, int32_t* counts, int64_t cap,
+                    int64_t stride, int64_t N, float cut, float c, float lam2, int64_t* counts, int64_t cap,
                     unsigned long long* cursor, int sh, uint64_t* keys, float* kv, hipStream_t s) {
     const dim3 g((unsigned)ntiles);
 #define GABP_SP_KIND(K) sp_build_kind<K>(fill, FA.m_pad, g, FA, FB, tiles, stride, N, cut, c, lam2, counts, cap, cursor, sh, keys, kv, s)
@@ -746,7 +746,7 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + WG - 1) / WG); }
 }  // namespace
 
 hipError_t launch_sp_count(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles,
-                           int64_t stride, int64_t N, float cut, int32_t* counts, hipStream_t s) {
+                           int64_t stride, int64_t N, float cut, int64_t* counts, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
     return sp_build(false, FA, FB, tiles, ntiles, stride, N, cut, 0.0f, 0.0f, counts, 0, nullptr, 0, nullptr,
                     nullptr, s);
@@ -819,7 +819,7 @@ hipError_t sp_tile_order(void* tmp, size_t* bytes, uint32_t* tiles, int64_t nt, 
     return hipGetLastError();
 }
 
-hipError_t sp_scan(void* tmp, size_t* bytes, const int32_t* in, int64_t* out, int64_t n, hipStream_t s) {
+hipError_t sp_scan(void* tmp, size_t* bytes, const int64_t* in, int64_t* out, int64_t n, hipStream_t s) {
     return hipcub::DeviceScan::ExclusiveSum(tmp, *bytes, in, out, (int)n, s);
 }
 
@@ -844,7 +844,7 @@ hipError_t launch_sp_offsets(const uint64_t* keys, int64_t E, int sh, int64_t N,
     return hipGetLastError();
 }
 
-hipError_t launch_sp_rowlen(int64_t N, const int64_t* off_i, const int64_t* off_j, int32_t* len, hipStream_t s) {
+hipError_t launch_sp_rowlen(int64_t N, const int64_t* off_i, const int64_t* off_j, int64_t* len, hipStream_t s) {
     hipLaunchKernelGGL(k_sp_rowlen, dim3(blocks(N + 1)), dim3(WG), 0, s, N, off_i, off_j, len);
     return hipGetLastError();
 }

@@ -917,7 +917,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     const size_t plane_b = (size_t)NPAD * m_pad * 2;
     A(h->sp_xb, plane_b * planes);
     A(h->yd, (size_t)N * 4);
-    A(h->sp_cnt, (size_t)(nt / 32 + 1) * 4); A(h->sp_toff, (size_t)(nt / 32 + 1) * 8);   // sampled tiles
+    A(h->sp_cnt, (size_t)(nt / 32 + 1) * 8); A(h->sp_toff, (size_t)(nt / 32 + 1) * 8);   // sampled tiles
     A(h->partP, (size_t)NPAD * 8); A(h->partE, (size_t)NPAD * 8);
     A(h->kdiag, (size_t)N * 8); A(h->Adiag, (size_t)N * 8); A(h->rowmax, (size_t)N * 8);
     A(h->rsum, (size_t)N * 8);
@@ -1052,14 +1052,13 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
         int64_t cap = p.sparse_edges_hint;
         if (cap == 0) {
             const int64_t stride = 32, ns = (nts + stride - 1) / stride;
-            HIPCHK(h, launch_sp_count(F, FB, tsel, ns, stride, N, cutf, h->sp_cnt.as<int32_t>(), s));
-            HIPCHK(h, sp_scan(nullptr, &tb, h->sp_cnt.as<int32_t>(), h->sp_toff.as<int64_t>(), ns, s));
+            HIPCHK(h, launch_sp_count(F, FB, tsel, ns, stride, N, cutf, h->sp_cnt.as<int64_t>(), s));
+            HIPCHK(h, sp_scan(nullptr, &tb, h->sp_cnt.as<int64_t>(), h->sp_toff.as<int64_t>(), ns, s));
             if (h->sp_tmp.ensure(tb) != hipSuccess) { h->release_all(); return fail(h, GABP_E_NOMEM, "scan storage"); }
-            HIPCHK(h, sp_scan(h->sp_tmp.p, &tb, h->sp_cnt.as<int32_t>(), h->sp_toff.as<int64_t>(), ns, s));
-            int64_t last_off = 0;
-            int32_t last_cnt = 0;
+            HIPCHK(h, sp_scan(h->sp_tmp.p, &tb, h->sp_cnt.as<int64_t>(), h->sp_toff.as<int64_t>(), ns, s));
+            int64_t last_off = 0, last_cnt = 0;
             HIPCHK(h, hipMemcpyAsync(&last_off, h->sp_toff.as<int64_t>() + (ns - 1), 8, hipMemcpyDeviceToHost, s));
-            HIPCHK(h, hipMemcpyAsync(&last_cnt, h->sp_cnt.as<int32_t>() + (ns - 1), 4, hipMemcpyDeviceToHost, s));
+            HIPCHK(h, hipMemcpyAsync(&last_cnt, h->sp_cnt.as<int64_t>() + (ns - 1), 8, hipMemcpyDeviceToHost, s));
             HIPCHK(h, hipStreamSynchronize(s));
             const double est = (double)(last_off + last_cnt) * ((double)nts / (double)ns);
             cap = std::min<int64_t>(emax, (int64_t)(1.5 * est) + ((int64_t)1 << 20));
@@ -1089,7 +1088,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     A(h->sp_kv, (size_t)E * 4); A(h->sp_kv2, (size_t)E * 4);
     A(h->sp_ei, (size_t)E * 4); A(h->sp_ej, (size_t)E * 4);
     const size_t rows = (size_t)2 * E + (size_t)4 * N;      // entries, every row in whole quads
-    A(h->sp_len, (size_t)(N + 1) * 4); A(h->sp_row, (size_t)(N + 1) * 8);
+    A(h->sp_len, (size_t)(N + 1) * 8); A(h->sp_row, (size_t)(N + 1) * 8);
     A(h->sp_qrow, rows); A(h->sp_edge, (rows / 4 / WG + 1) * 4 * agg);
     A(h->sp_col, rows * 4); A(h->sp_rkv, rows * 4);
     // records: the (P, E) message into every row's node, two sweeps; packed
@@ -1105,7 +1104,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     HIPCHK(h, sp_sort_keys(nullptr, &sb, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(), h->sp_kv.as<float>(),
                            h->sp_kv2.as<float>(), E, 2 * sh, s));
     size_t sb2 = 0;
-    HIPCHK(h, sp_scan(nullptr, &sb2, h->sp_len.as<int32_t>(), h->sp_row.as<int64_t>(), N + 1, s));
+    HIPCHK(h, sp_scan(nullptr, &sb2, h->sp_len.as<int64_t>(), h->sp_row.as<int64_t>(), N + 1, s));
     if (h->sp_tmp.ensure(std::max(std::max(sb, sb2), tb)) != hipSuccess) {
         h->release_all();
         return fail(h, GABP_E_NOMEM, "sort storage");
@@ -1121,15 +1120,17 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     HIPCHK(h, sp_sort_keys(h->sp_tmp.p, &sb, h->sp_keys.as<uint64_t>(), h->sp_keys2.as<uint64_t>(),
                            h->sp_kv2.as<float>(), h->sp_kv.as<float>(), E, 2 * sh, s));
     HIPCHK(h, launch_sp_offsets(h->sp_keys2.as<uint64_t>(), E, sh, N, h->sp_offj.as<int64_t>(), s));
-    HIPCHK(h, launch_sp_rowlen(N, h->sp_offi.as<int64_t>(), h->sp_offj.as<int64_t>(), h->sp_len.as<int32_t>(), s));
-    HIPCHK(h, sp_scan(h->sp_tmp.p, &sb2, h->sp_len.as<int32_t>(), h->sp_row.as<int64_t>(), N + 1, s));
+    HIPCHK(h, launch_sp_rowlen(N, h->sp_offi.as<int64_t>(), h->sp_offj.as<int64_t>(), h->sp_len.as<int64_t>(), s));
+    HIPCHK(h, sp_scan(h->sp_tmp.p, &sb2, h->sp_len.as<int64_t>(), h->sp_row.as<int64_t>(), N + 1, s));
+    // (the rows are placed by these sums: every one of them inside the arrays)
+    int64_t entries = 0;
+    HIPCHK(h, hipMemcpyAsync(&entries, h->sp_row.as<int64_t>() + N, 8, hipMemcpyDeviceToHost, s));
+    HIPCHK(h, hipStreamSynchronize(s));
+    if (entries < 4 * N || entries > (int64_t)rows) return fail(h, GABP_E_DEVICE, "row offsets of the sparse graph");
     HIPCHK(h, launch_sp_rows(E, N, sh, h->sp_ei.as<int32_t>(), h->sp_ej.as<int32_t>(), h->sp_kv2.as<float>(),
                              h->sp_keys2.as<uint64_t>(), h->sp_kv.as<float>(), h->sp_offi.as<int64_t>(),
                              h->sp_offj.as<int64_t>(), h->sp_row.as<int64_t>(), h->sp_col.as<int32_t>(),
                              h->sp_rkv.as<float>(), h->sp_qrow.as<int32_t>(), s));
-    int64_t entries = 0;
-    HIPCHK(h, hipMemcpyAsync(&entries, h->sp_row.as<int64_t>() + N, 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipStreamSynchronize(s));
     HIPCHK(h, hipEventRecord(ev[2], s));
 
     // ---- diagonal weighting from the sparse row sums (one partial per node)

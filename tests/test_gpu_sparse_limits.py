@@ -1,0 +1,66 @@
+"""The sparse graph build beyond 32 bits: its scan by itself, and a graph whose
+rows hold more than 2^31 entries.
+
+Tolerances: whole numbers are equal; alpha 1e-5 (inf-norm, relative), as for
+the other sparse tests.
+"""
+import ctypes as ct
+
+import numpy as np
+import pytest
+
+from paper_0810_1648_amd import gabp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as _t
+    if not _t.cuda.is_available():
+        pytest.skip("no GPU")
+    return _t
+
+
+def _entry(name, *argtypes):
+    f = getattr(gabp.lib(), name)
+    f.argtypes, f.restype = argtypes, ct.c_int
+    return f
+
+
+# row lengths whose sums pass 2^31 (at 2^30 kept pairs) and 2^32
+@pytest.mark.parametrize("n,length", [(3, 2 ** 30 + 4), (1 << 16, 1 << 16), (100_003, 65_540)])
+def test_row_offsets_beyond_32_bits(torch, n, length):
+    vp = ct.c_void_p
+    scan = _entry("_ZN4gabp7sp_scanEPvPmPKlPllP12ihipStream_t", vp, ct.POINTER(ct.c_size_t), vp, vp, ct.c_int64, vp)
+    x = torch.full((n + 1,), length, dtype=torch.int64, device="cuda")
+    out = torch.zeros_like(x)
+    s = torch.cuda.current_stream().cuda_stream
+    nb = ct.c_size_t(0)
+    assert scan(None, ct.byref(nb), x.data_ptr(), out.data_ptr(), n + 1, s) == 0
+    tmp = torch.empty(max(nb.value, 16), dtype=torch.uint8, device="cuda")
+    assert scan(tmp.data_ptr(), ct.byref(nb), x.data_ptr(), out.data_ptr(), n + 1, s) == 0
+    assert torch.equal(out, length * torch.arange(n + 1, dtype=torch.int64, device="cuda"))
+    assert int(out[-1]) > 2 ** 31
+
+
+# every pair of 47,000 points kept: 1.1e9 pairs, 2.2e9 directed edges, the same
+# system as the dense solve over stored records
+def test_graph_of_more_than_2_30_pairs(torch):
+    n = 47_000
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GiB of device memory")
+    rng = np.random.default_rng(5)
+    X = torch.from_numpy((0.3 * rng.standard_normal((n, 6))).astype(np.float32)).cuda()
+    y = torch.from_numpy(np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)).cuda()
+    kw = dict(gamma=0.5, C=10.0, lambda_aug=1.0 / n, precision="mixed", max_sweeps=5, tol_abs=0.0, tol_rel=0.0,
+              stagnation_window=0)
+    a = {}
+    for kernel, how in (("rbf", dict(edge_state="stored", kstore="materialise")), ("rbf_sparse", dict(sparse_tau=1e-12))):
+        s = gabp.GabpSVM(kernel=kernel, **kw, **how)
+        s.solve(X, y)
+        if kernel == "rbf_sparse":
+            assert s.plan()["n_edges"] == n * (n - 1) // 2
+        a[kernel] = s.alpha()
+        s.close()
+    assert float(np.max(np.abs(a["rbf_sparse"] - a["rbf"])) / np.max(np.abs(a["rbf"]))) <= 1e-5
