@@ -673,34 +673,36 @@ __global__ void k_sp_prune(const uint32_t* __restrict__ tiles, int64_t nt, int64
 // remainders), so that sum_k a_ik b_jk = x_i . x_j - n_i/2 - n_j/2 for the
 // products the kind forms.  Columns past m + 1 stay 0.  One thread per value,
 // so that accesses are contiguous (a thread per row: 327 us, a thread per value 31 us
-// for 200,000 rows).
+// for 200,000 rows), 2^30 threads at most: a launch holds fewer than 2^32, and the
+// largest staged matrices have more values.
 __global__ void k_sp_augment(int64_t NPAD, int m, int m_pad, int kind, const float* __restrict__ nrm,
                              float* f32a, uint16_t* hia, uint16_t* loa, uint16_t* lo2a, float* f32b,
                              uint16_t* hib, uint16_t* lob, uint16_t* lo2b) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= NPAD * m_pad) return;
-    const int64_t i = o / m_pad;
-    const int k = (int)(o - i * m_pad);
-    const float n = nrm[i];
-    // (A's value where it is not a feature, B's)
-    const float va = k == m ? n : 1.0f, vb = k == m ? -0.5f : k == m + 1 ? -0.5f * n : 0.0f;
-    const bool extra = k == m || k == m + 1;
-    if (kind == GRAM_F32) {
-        if (extra) f32a[o] = va;
-        f32b[o] = k < m ? f32a[o] : vb;
-        return;
-    }
     const bool x3 = (kind == GRAM_BF16X3 || kind == GRAM_BF16X6), x6 = (kind == GRAM_BF16X6);
-    uint16_t h, l, l2;
-    split3(vb, h, l, l2);
-    hib[o] = k < m ? hia[o] : h;
-    if (x3) lob[o] = k < m ? loa[o] : l;
-    if (x6) lo2b[o] = k < m ? lo2a[o] : l2;
-    if (!extra) return;
-    split3(va, h, l, l2);
-    hia[o] = h;
-    if (x3) loa[o] = l;
-    if (x6) lo2a[o] = l2;
+    for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < NPAD * m_pad;
+         o += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t i = o / m_pad;
+        const int k = (int)(o - i * m_pad);
+        const float n = nrm[i];
+        // (A's value where it is not a feature, B's)
+        const float va = k == m ? n : 1.0f, vb = k == m ? -0.5f : k == m + 1 ? -0.5f * n : 0.0f;
+        const bool extra = k == m || k == m + 1;
+        if (kind == GRAM_F32) {
+            if (extra) f32a[o] = va;
+            f32b[o] = k < m ? f32a[o] : vb;
+            continue;
+        }
+        uint16_t h, l, l2;
+        split3(vb, h, l, l2);
+        hib[o] = k < m ? hia[o] : h;
+        if (x3) lob[o] = k < m ? loa[o] : l;
+        if (x6) lo2b[o] = k < m ? lo2a[o] : l2;
+        if (!extra) continue;
+        split3(va, h, l, l2);
+        hia[o] = h;
+        if (x3) loa[o] = l;
+        if (x6) lo2a[o] = l2;
+    }
 }
 
 template <int KIND>
@@ -764,8 +766,9 @@ hipError_t launch_sp_augment(int64_t NPAD, int64_t m, int m_pad, int kind, const
                              uint16_t* hia, uint16_t* loa, uint16_t* lo2a, float* f32b, uint16_t* hib,
                              uint16_t* lob, uint16_t* lo2b, hipStream_t s) {
     if (m + 2 > m_pad) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_sp_augment, dim3(blocks(NPAD * m_pad)), dim3(WG), 0, s, NPAD, (int)m, m_pad, kind, nrm, f32a, hia, loa,
-                       lo2a, f32b, hib, lob, lo2b);
+    const unsigned g = blocks(std::min<int64_t>(NPAD * m_pad, (int64_t)1 << 30));
+    hipLaunchKernelGGL(k_sp_augment, dim3(g), dim3(WG), 0, s, NPAD, (int)m, m_pad, kind, nrm, f32a, hia, loa, lo2a,
+                       f32b, hib, lob, lo2b);
     return hipGetLastError();
 }
 

@@ -64,3 +64,22 @@ def test_graph_of_more_than_2_30_pairs(torch):
         a[kernel] = s.alpha()
         s.close()
     assert float(np.max(np.abs(a["rbf_sparse"] - a["rbf"])) / np.max(np.abs(a["rbf"]))) <= 1e-5
+
+
+# augmented rows of more values than one launch holds threads
+def test_augmented_rows_of_more_than_2_32_values(torch):
+    vp, n, mp = ct.c_void_p, 65_792, 65_536
+    m = mp - 2
+    aug = _entry("_ZN4gabp17launch_sp_augmentElliiPKfPfPtS3_S3_S2_S3_S3_S3_P12ihipStream_t", ct.c_int64, ct.c_int64,
+                 ct.c_int, ct.c_int, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp)
+    a = torch.ones((n, mp), dtype=torch.bfloat16, device="cuda")
+    b = torch.zeros_like(a)
+    nrm = 2.0 ** (torch.arange(n, device="cuda") % 8).float()      # exact in BF16
+    one_term = 1                                                    # the kind whose rows are one BF16 plane
+    assert a.numel() > 2 ** 32
+    assert aug(n, m, mp, one_term, nrm.data_ptr(), None, a.data_ptr(), None, None, None, b.data_ptr(), None, None,
+               torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert bool((b[:, :m] == 1).all()) and bool((a[:, :m] == 1).all())
+    assert torch.equal(a[:, m].float(), nrm) and bool((a[:, m + 1] == 1).all())
+    assert bool((b[:, m] == -0.5).all()) and torch.equal(b[:, m + 1].float(), -0.5 * nrm)
