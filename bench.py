@@ -44,12 +44,11 @@ def sweep_slots_per_pair(levels, series, precision="mixed"):
     """VALU issue slots per pair of one stateless sweep as it runs: sums over
     powers of K' take the powers beyond the first (one multiply each) and one
     multiply-add per power and direction, two powers at one level, four at two
-    levels and in FP32 / FP64 at three, three in MIXED at three; other plans
-    rebuild the messages level by level."""
+    and three; other plans rebuild the messages level by level."""
     series = int(series)
     if not moment_plan(levels, series):
         return stateless_slots_per_pair(levels, series, precision)
-    powers = 2 if levels == 1 else 3 if levels == 3 and precision == "mixed" else 4
+    powers = 2 if levels == 1 else 4
     return powers - 1 + 2 * powers
 
 

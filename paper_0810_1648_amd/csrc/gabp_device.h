@@ -665,19 +665,19 @@ __device__ inline void put_tile_sums(const SweepArgs& a, const TileCoord& tc, AT
 //   P_ij = -a^2 u_i + a^4 u_i^2 u'_j
 //   E_ij = -a u_i S_i - a^2 u_i m'_j + a^3 u'_j (u_i^2 S_i - u_i m''_i) + a^4 u_i^2 u'_j m'_j
 // (one level: the first term of each; two: m'' = 0; three levels of form 3
-// leave out a^5 u_i^2 u'_j^2 m''_i, rr^4), so that a node's sums are its own
-// factors times sums of a^k x_k with x_1 = u S, x_2 = u, x_3 = u^2 S - u m'',
-// x_4 = u^2 of its neighbours: per pair the powers of a and one FMA per power
-// and direction, 8 or 11 VALU slots where the recursion level by level takes
-// 17, and three or four values per node in registers.  The a^4 terms are at
-// most rr^3 of the aggregates; MIXED plans take three levels only below 2^-30
-// and leave them out, 64 times under the precision of their FP32 messages
-// (FP32 takes them from 2^-24 on, where they would show).
+// leave out a^5 u_i^2 u'_j^2 m''_i, rr^4, under the rr^3 that form 3 errs by),
+// so that a node's sums are its own factors times sums of a^k x_k with
+// x_1 = u S, x_2 = u, x_3 = u^2 S - u m'', x_4 = u^2 of its neighbours: per
+// pair the powers of a and one FMA per power and direction, 11 VALU slots
+// (one level: 5) where the recursion level by level takes 17.  The a^4 terms
+// are rr^2 of the message sums and stay in: without them a sweep of 100,000
+// points over the plane took 0.8% less and one recomputed from 120,000 points
+// 8%, with the precisions P~ off by rr^3.
 template <int D, int SER> constexpr bool mom_plan() {
     return SER > 0 && (D == 1 || (D == 2 && SER == 1) || (D == 3 && SER == 3));
 }
-template <class XT, bool XF, int D> struct Mom {
-    static constexpr bool Q3 = D >= 2, Q4 = D == 2 || (D == 3 && !XF);
+template <class XT, int D> struct Mom {
+    static constexpr bool Q = D >= 2;   // the powers beyond a^2
     XT x1, x2, x3, x4;           // of a node as the source of messages
     XT ku, km;                   // u', m' of a node as their target
 };
@@ -695,8 +695,8 @@ template <int W, class T> __device__ inline void ld_nodes(const T* p, T (&v)[W])
 }
 
 // Factors of W consecutive nodes for the moment sums.
-template <int W, class XT, bool XF, int D, class AT>
-__device__ inline void mom_nodes(const SweepArgs& a, int slot_top, int64_t node, Mom<XT, XF, D> (&m)[W]) {
+template <int W, class XT, int D, class AT>
+__device__ inline void mom_nodes(const SweepArgs& a, int slot_top, int64_t node, Mom<XT, D> (&m)[W]) {
     const AT* HP = static_cast<const AT*>(a.HP);
     const AT* HS = static_cast<const AT*>(a.HS);
     const AT* HI = static_cast<const AT*>(a.HI);
@@ -744,11 +744,15 @@ __device__ inline void mom_nodes(const SweepArgs& a, int slot_top, int64_t node,
 }
 
 // Sums of a node's messages from its moment sums.
-template <class T, bool Q3, bool Q4>
+template <class T, bool Q>
 __device__ inline void mom_sums(T m1, T m2, T m3, T m4, T ku, T km, T& p, T& e) {
-    p = Q4 ? fma(ku, m4, -m2) : -m2;
-    if constexpr (Q3) e = fma(ku, Q4 ? fma(km, m4, m3) : m3, -fma(km, m2, m1));
-    else e = -m1;
+    if constexpr (Q) {
+        p = fma(ku, m4, -m2);
+        e = fma(ku, fma(km, m4, m3), -fma(km, m2, m1));
+    } else {
+        p = -m2;
+        e = -m1;
+    }
 }
 
 // sweep_tile for the plans of mom_plan.
@@ -757,8 +761,8 @@ __device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot
                                       int sub) {
     using XT = typename MsgT<ST, MT, AT, SER>::T;
     constexpr bool XF = MsgT<ST, MT, AT, SER>::F32;
-    using MM = Mom<XT, XF, D>;
-    constexpr bool Q3 = MM::Q3, Q4 = MM::Q4;
+    using MM = Mom<XT, D>;
+    constexpr bool Q = MM::Q;
     const uint32_t ij = a.tiles[tile];
     const TileCoord tc{(int)(ij >> 16), (int)(ij & 0xFFFFu)};
     const size_t tbase = (size_t)tile * TT;
@@ -782,25 +786,25 @@ __device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot
     typedef XT X4 __attribute__((ext_vector_type(4)));
     typedef XT X2 __attribute__((ext_vector_type(2)));
     __shared__ X4 sx[TILE];
-    __shared__ X2 sk[Q3 ? TILE : 1], sc[Q3 ? TILE : 1];
+    __shared__ X2 sk[Q ? TILE : 1], sc[Q ? TILE : 1];
     using RT = typename std::conditional<XF, XT, AT>::type;
     __shared__ RT rP[4][TILE], rE[4][TILE];
     __shared__ RT red[4][2][2][64];
     __shared__ float kband[KSRC == KSRC_RECOMPUTE ? 4 : 1][KSRC == KSRC_RECOMPUTE ? 32 * 64 : 1];
     {
         MM m[1];
-        mom_nodes<1, XT, XF, D, AT>(a, slot_top, (int64_t)tc.I * TILE + tid, m);
+        mom_nodes<1, XT, D, AT>(a, slot_top, (int64_t)tc.I * TILE + tid, m);
         sx[tid] = X4{m[0].x1, m[0].x2, m[0].x3, m[0].x4};
-        if constexpr (Q3) sk[tid] = X2{m[0].ku, m[0].km};
+        if constexpr (Q) sk[tid] = X2{m[0].ku, m[0].km};
     }
     XT y1[4], y2[4], y3[4], y4[4];
     {
         MM m[4];
-        mom_nodes<4, XT, XF, D, AT>(a, slot_top, (int64_t)tc.J * TILE + col0, m);
+        mom_nodes<4, XT, D, AT>(a, slot_top, (int64_t)tc.J * TILE + col0, m);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             y1[c] = m[c].x1; y2[c] = m[c].x2; y3[c] = m[c].x3; y4[c] = m[c].x4;
-            if constexpr (Q3) {
+            if constexpr (Q) {
                 if (g == 0) sc[col0 + c] = X2{m[c].ku, m[c].km};
             }
         }
@@ -844,20 +848,17 @@ __device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot
                 m1 = fma(av, y1[c], m1);
                 c2[c] = fma(a2, x[1], c2[c]);
                 m2 = fma(a2, y2[c], m2);
-                if constexpr (Q3) {
-                    const XT a3 = a2 * av;
+                if constexpr (Q) {
+                    const XT a3 = a2 * av, a4 = a2 * a2;
                     c3[c] = fma(a3, x[2], c3[c]);
                     m3 = fma(a3, y3[c], m3);
-                }
-                if constexpr (Q4) {
-                    const XT a4 = a2 * a2;
                     c4[c] = fma(a4, x[3], c4[c]);
                     m4 = fma(a4, y4[c], m4);
                 }
             }
             XT rp, re;
-            const X2 f = Q3 ? sk[r] : X2{0, 0};
-            mom_sums<XT, Q3, Q4>(m1, m2, m3, m4, f[0], f[1], rp, re);
+            const X2 f = Q ? sk[r] : X2{0, 0};
+            mom_sums<XT, Q>(m1, m2, m3, m4, f[0], f[1], rp, re);
             // row sums over the 16 column lanes through LDS every two row
             // steps (as in sweep_tile)
             red[w][0][s2 & 1][l] = (RT)rp;
@@ -890,8 +891,8 @@ __device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot
     AT cP[4], cE[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const X2 f = Q3 ? sc[col0 + c] : X2{0, 0};
-        mom_sums<AT, Q3, Q4>((AT)c1[c], (AT)c2[c], (AT)c3[c], (AT)c4[c], (AT)f[0], (AT)f[1], cP[c], cE[c]);
+        const X2 f = Q ? sc[col0 + c] : X2{0, 0};
+        mom_sums<AT, Q>((AT)c1[c], (AT)c2[c], (AT)c3[c], (AT)c4[c], (AT)f[0], (AT)f[1], cP[c], cE[c]);
         cP[c] = sum_groups(cP[c]);
         cE[c] = sum_groups(cE[c]);
     }
@@ -1437,23 +1438,23 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void
 // straight into the moment sums (mom_plan): the rows' factors and sums stay in
 // registers over the band, a column's over the block.  No K' band passes
 // through LDS, and nothing is reduced across lanes but one vector per band.
-// 13 VALU slots per pair (exp2 4, + lambda^2, a^2, a^3, six FMAs) beside the
+// 16 VALU slots per pair (exp2 4, + lambda^2, a^2, a^3, a^4, eight FMAs) beside the
 // MFMAs; the VALU is busy for three quarters of the time.  N = 120,000, m =
 // 20: 8.0 (bands through LDS, level by level) -> 7.3 (moment sums) -> 5.0 ms
 // per sweep; three waves per SIMD with 80 bytes of spills take as long.
 template <int KIND, int MP>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_sweep_rc_mom(SweepArgs a) {
     if (a.st->done) return;
-    using MM = Mom<float, true, 3>;
+    using MM = Mom<float, 3>;
     using BS = BStage<KIND>;
     typedef float X4 __attribute__((ext_vector_type(4)));
     typedef float X2 __attribute__((ext_vector_type(2)));
     constexpr int CH = BS::NP * (MP / 16) * 64, PR = (CH + WG - 1) / WG, NS = MP / 16;
     __shared__ bf16x8 sb[2][CH];
-    __shared__ __attribute__((aligned(16))) float sx[3][TILE];   // x_1 .. x_3 of the row nodes
+    __shared__ __attribute__((aligned(16))) float sx[4][TILE];   // x_1 .. x_4 of the row nodes
     __shared__ X4 sy[TILE];                     // ... of the column nodes
     __shared__ X2 sk[TILE], sc[TILE];           // u', m'
-    __shared__ float cs[4][3][TILE];            // column sums per wave
+    __shared__ float cs[4][4][TILE];            // column sums per wave
     const int split = a.split, sub = blockIdx.x % split;
     const uint32_t ij = a.tiles[blockIdx.x / split];
     const TileCoord tc{(int)(ij >> 16), (int)(ij & 0xFFFFu)};
@@ -1472,11 +1473,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void
     }
     {
         MM m[1];
-        mom_nodes<1, float, true, 3, double>(a, a.slot_top, i0 + tid, m);
-        sx[0][tid] = m[0].x1; sx[1][tid] = m[0].x2; sx[2][tid] = m[0].x3;
+        mom_nodes<1, float, 3, double>(a, a.slot_top, i0 + tid, m);
+        sx[0][tid] = m[0].x1; sx[1][tid] = m[0].x2; sx[2][tid] = m[0].x3; sx[3][tid] = m[0].x4;
         sk[tid] = X2{m[0].ku, m[0].km};
-        mom_nodes<1, float, true, 3, double>(a, a.slot_top, j0 + tid, m);
-        sy[tid] = X4{m[0].x1, m[0].x2, m[0].x3, 0.0f};
+        mom_nodes<1, float, 3, double>(a, a.slot_top, j0 + tid, m);
+        sy[tid] = X4{m[0].x1, m[0].x2, m[0].x3, m[0].x4};
         sc[tid] = X2{m[0].ku, m[0].km};
     }
     __syncthreads();
@@ -1498,9 +1499,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void
                     fa.lo2[st] = *reinterpret_cast<const bf16x8*>(at + 2 * a.F.aug_plane + 16 * st);
             }
         }
-        float r1[16], r2[16], r3[16];
+        float r1[16], r2[16], r3[16], r4[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) r1[r] = r2[r] = r3[r] = 0.0f;
+        for (int r = 0; r < 16; ++r) r1[r] = r2[r] = r3[r] = r4[r] = 0.0f;
 #pragma unroll 1
         for (int cb = 0; cb < TILE / 32; ++cb) {
             // the next block (the first again after the last of a pass)
@@ -1532,36 +1533,39 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void
                 for (int r = 0; r < 16; ++r)
                     acc[r] = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(acc[r]), 0.0f, 1.0f) + lam2;
             }
-            float c1 = 0.0f, c2 = 0.0f, c3 = 0.0f;
+            float c1 = 0.0f, c2 = 0.0f, c3 = 0.0f, c4 = 0.0f;
             // four consecutive rows at a time (one 16-byte LDS read per factor)
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int o = band * 32 + 8 * t + 4 * h;
                 const X4 x1 = *reinterpret_cast<const X4*>(&sx[0][o]), x2 = *reinterpret_cast<const X4*>(&sx[1][o]),
-                         x3 = *reinterpret_cast<const X4*>(&sx[2][o]);
+                         x3 = *reinterpret_cast<const X4*>(&sx[2][o]), x4 = *reinterpret_cast<const X4*>(&sx[3][o]);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int r = 4 * t + v;
-                    const float av = acc[r], a2 = av * av, a3 = a2 * av;
+                    const float av = acc[r], a2 = av * av, a3 = a2 * av, a4 = a2 * a2;
                     c1 = fmaf(av, x1[v], c1);
                     r1[r] = fmaf(av, y[0], r1[r]);
                     c2 = fmaf(a2, x2[v], c2);
                     r2[r] = fmaf(a2, y[1], r2[r]);
                     c3 = fmaf(a3, x3[v], c3);
                     r3[r] = fmaf(a3, y[2], r3[r]);
+                    c4 = fmaf(a4, x4[v], c4);
+                    r4[r] = fmaf(a4, y[3], r4[r]);
                 }
             }
-            // (the row sums are formed here: the compiler otherwise carries a,
-            // a^2 and a^3 over into the next block, 48 registers)
+            // (the row sums are formed here: the compiler otherwise carries the
+            // powers of a over into the next block, 64 registers)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(r1[r]), "+v"(r2[r]), "+v"(r3[r]));
+            for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(r1[r]), "+v"(r2[r]), "+v"(r3[r]), "+v"(r4[r]));
             // the column's 32 rows of this band: both lane halves
             c1 = c1 + __shfl_xor(c1, 32);
             c2 = c2 + __shfl_xor(c2, 32);
             c3 = c3 + __shfl_xor(c3, 32);
+            c4 = c4 + __shfl_xor(c4, 32);
             if (h == 0) {
-                if (pass > 0) { c1 += cs[w][0][col]; c2 += cs[w][1][col]; c3 += cs[w][2][col]; }
-                cs[w][0][col] = c1; cs[w][1][col] = c2; cs[w][2][col] = c3;
+                if (pass > 0) { c1 += cs[w][0][col]; c2 += cs[w][1][col]; c3 += cs[w][2][col]; c4 += cs[w][3][col]; }
+                cs[w][0][col] = c1; cs[w][1][col] = c2; cs[w][2][col] = c3; cs[w][3][col] = c4;
             }
             if (more) {
 #pragma unroll
@@ -1580,7 +1584,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void
         for (int r = 0; r < 16; ++r) {
             const X2 f = sk[band * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
             float p, e;
-            mom_sums<float, true, false>(r1[r], r2[r], r3[r], 0.0f, f[0], f[1], p, e);
+            mom_sums<float, true>(r1[r], r2[r], r3[r], r4[r], f[0], f[1], p, e);
             p = sum16(p);
             e = sum16(e);
             p = p + __shfl_xor(p, 16);
@@ -1593,12 +1597,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void
             put_part(a.partE, o, (double)ve, p32);
         }
     }
-    double m[3], p, e;
+    double m[4], p, e;
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 4; ++k)
         m[k] = ((double)cs[0][k][tid] + (double)cs[1][k][tid]) + ((double)cs[2][k][tid] + (double)cs[3][k][tid]);
     const X2 f = sc[tid];
-    mom_sums<double, true, false>(m[0], m[1], m[2], 0.0, (double)f[0], (double)f[1], p, e);
+    mom_sums<double, true>(m[0], m[1], m[2], m[3], (double)f[0], (double)f[1], p, e);
     const size_t o = ps.col(tc.I, tc.J, sub) + tid;
     put_part(a.partP, o, p, p32);
     put_part(a.partE, o, e, p32);

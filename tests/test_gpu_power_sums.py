@@ -1,0 +1,80 @@
+"""Series sweeps summed over powers of K' (one, two and three levels) where
+the powers beyond the second matter: their terms in the message sums.
+
+The message sums A_ii - P~_i of systems of about 300 points, whose
+contraction is the largest that three levels of form 3 take (1.25 rho just
+below 2^-8): a third and a fourth power of K' enter them with rho^2, 9e-6.
+Tolerance (relative) against the FP64 oracle: 16 x 2^-24 = 9.5e-7; at most 8
+roundings of one message in FP32 (K' and its power, the factors and their
+products) and 8 = sqrt(64) for sums of 64 messages.  alpha: 1e-5 (inf-norm,
+relative) as everywhere.
+"""
+import numpy as np
+import pytest
+
+from oracle import gabp_ref as R
+from paper_0810_1648_amd import gabp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as _t
+    if not _t.cuda.is_available():
+        pytest.skip("no GPU")
+    return _t
+
+
+def labels(rng, n):
+    return np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+
+
+def check_messages(s, K, y, sweeps):
+    adiag = s.adiag()
+    A = (y[:, None] * y[None, :]).astype(np.float64) * K
+    np.fill_diagonal(A, adiag)
+    ref = R.gabp_solve(A, np.ones(len(y)), max_sweeps=sweeps, tol_rel=0.0)
+    want = adiag - ref.ptilde
+    err = float(np.max(np.abs((adiag - s.ptilde()) / want - 1.0)))
+    ea = float(np.max(np.abs(s.alpha() - ref.alpha)) / np.max(np.abs(ref.alpha)))
+    print(f"[case] message sums {err:.2e}, alpha {ea:.2e}", flush=True)
+    assert err <= 16 * 2.0 ** -24 and ea <= 1e-5, (err, ea)
+
+
+FIXED = dict(precision="mixed", edge_state="stateless", stateless_depth=3, tol_abs=0.0, tol_rel=0.0,
+             stagnation_window=0)
+
+
+@pytest.mark.parametrize("n", [300, 513])
+@pytest.mark.parametrize("chunk", [1, 2])
+@pytest.mark.parametrize("sweeps", [1, 2, 3, 6])
+def test_fourth_power_over_the_plane(torch, n, chunk, sweeps):
+    rng = np.random.default_rng(n)
+    K = 1.0 + 0.01 * rng.random((n, n))
+    K = ((K + K.T) / 2).astype(np.float32).astype(np.float64)      # exact in the plane
+    y = labels(rng, n)
+    s = gabp.GabpSVM(kernel="precomputed", C=1.0, tile_chunk=chunk, max_sweeps=sweeps, **FIXED)
+    s.solve_kernel(torch.from_numpy(K).cuda(), torch.from_numpy(y).cuda())
+    p = s.plan()
+    assert p["series_reciprocal"] == 3 and p["tile_chunk"] == chunk and 1.25 * p["stateless_rho"] < 2.0 ** -8
+    check_messages(s, K, y, sweeps)
+    s.close()
+
+
+# 300 points: tiles in eight parts (through the LDS band); 6,000: two parts,
+# from the MFMA output (against the same system over the plane)
+@pytest.mark.parametrize("m", [20, 62])
+def test_fourth_power_recomputed(torch, m):
+    rng = np.random.default_rng(m)
+    gamma, n = 0.05, 300
+    X = (0.05 * rng.standard_normal((n, m))).astype(np.float32)
+    y = labels(rng, n)
+    d = X.astype(np.float64)
+    K = np.exp(-gamma * ((d[:, None, :] - d[None, :, :]) ** 2).sum(axis=2)) + (1.0 / n) ** 2
+    s = gabp.GabpSVM(gamma=gamma, C=1.0, kstore="recompute", max_sweeps=4, **FIXED)
+    s.solve(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda())
+    p = s.plan()
+    assert p["series_reciprocal"] == 3 and p["recompute_aug"] == 1 and 1.25 * p["stateless_rho"] < 2.0 ** -8
+    check_messages(s, K, y, 4)
+    s.close()
