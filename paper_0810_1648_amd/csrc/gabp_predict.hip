@@ -349,11 +349,18 @@ __device__ inline void aug_row(const float* __restrict__ x, const double* __rest
 #pragma unroll
     for (int j = 0; j < CW; ++j) {
         const int k = CW * e + j;
-        float v = (side == 0) ? xc[j] : c * xc[j];
-        if (k == m) v = (side == 0) ? nrm : (live ? -0.5f * c : 0.0f);
-        if (k == m + 1) v = (side == 0) ? (live ? 1.0f : 0.0f) : -0.5f * c * nrm;
-        uint16_t h, l, l2;
-        split3(v, h, l, l2);
+        // the value as a product a b: the terms split the product itself, not
+        // its FP32 rounding (which -c/2 |x|^2, a few units large, would put
+        // into every exponent of the row)
+        float a = (side == 0) ? xc[j] : c * xc[j], b = 1.0f;
+        if (k == m) a = (side == 0) ? nrm : (live ? -0.5f * c : 0.0f);
+        if (k == m + 1) {
+            a = (side == 0) ? (live ? 1.0f : 0.0f) : -0.5f * c;
+            if (side != 0) b = nrm;
+        }
+        const uint16_t h = f2bf(a * b);
+        const float r1 = fmaf(a, b, -bf2f(h));
+        const uint16_t l = f2bf(r1), l2 = f2bf(r1 - bf2f(l));
         if (j & 1) { p0[j / 2] |= (uint32_t)h << 16; p1[j / 2] |= (uint32_t)l << 16; p2[j / 2] |= (uint32_t)l2 << 16; }
         else { p0[j / 2] = h; p1[j / 2] = l; p2[j / 2] = l2; }
     }
