@@ -1430,6 +1430,32 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void
                                                               blockIdx.x % a.split);
 }
 
+// Sums of v[r] over the 32 lanes of a half, row r in the lanes whose low four
+// bits are r's in reverse; each step halves the rows a lane holds, so all 16
+// take 16 additions instead of 80.
+__device__ inline double sum_rows16(const float (&v)[16], int l) {
+    double s[8];
+    const bool b0 = l & 1, b1 = l & 2, b2 = l & 4, b3 = l & 8;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const float keep = b0 ? v[k + 8] : v[k], give = b0 ? v[k] : v[k + 8];
+        s[k] = (double)keep + (double)__shfl_xor(give, 1);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double keep = b1 ? s[k + 4] : s[k], give = b1 ? s[k] : s[k + 4];
+        s[k] = keep + __shfl_xor(give, 2);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const double keep = b2 ? s[k + 2] : s[k], give = b2 ? s[k] : s[k + 2];
+        s[k] = keep + __shfl_xor(give, 4);
+    }
+    const double keep = b3 ? s[1] : s[0], give = b3 ? s[0] : s[1];
+    s[0] = keep + __shfl_xor(give, 8);
+    return s[0] + __shfl_xor(s[0], 16);
+}
+
 // Three-level series sweep (form 3, FP32 messages) with K' recomputed from
 // augmented rows of MP features, in the MFMA's own layout: a wave forms 32 x 32
 // blocks of its 32-row band against the tile's eight column blocks (B
@@ -1440,8 +1466,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void
 // through LDS, and nothing is reduced across lanes but one vector per band.
 // 16 VALU slots per pair (exp2 4, + lambda^2, a^2, a^3, a^4, eight FMAs) beside the
 // MFMAs; the VALU is busy for three quarters of the time.  N = 120,000, m =
-// 20: 8.0 (bands through LDS, level by level) -> 7.3 (moment sums) -> 5.0 ms
-// per sweep; three waves per SIMD with 80 bytes of spills take as long.
+// 20: 8.0 (bands through LDS, level by level) -> 7.3 (moment sums) -> 5.3 ms
+// per sweep, 0.04 of it the row sums across lanes in FP64.
 template <int KIND, int MP>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_sweep_rc_mom(SweepArgs a) {
     if (a.st->done) return;
@@ -1577,24 +1603,22 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void
             __syncthreads();
             cur ^= 1;
         }
-        // the band's row sums over the 32 columns a half holds; lane r of a
-        // half keeps row r's
-        float vp = 0.0f, ve = 0.0f;
+        // the band's row sums over the 32 lanes of a half, in FP64 (a lane's
+        // eight columns are FP32 sums): step by step a lane keeps half of the
+        // rows it holds and adds its partner's sums of them, so that lane l of
+        // a half ends with row 8 (l & 1) + 4 (l >> 1 & 1) + 2 (l >> 2 & 1) + (l >> 3 & 1)
+        float fp[16], fe[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const X2 f = sk[band * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
-            float p, e;
-            mom_sums<float, true>(r1[r], r2[r], r3[r], r4[r], f[0], f[1], p, e);
-            p = sum16(p);
-            e = sum16(e);
-            p = p + __shfl_xor(p, 16);
-            e = e + __shfl_xor(e, 16);
-            if (l32 == r) { vp = p; ve = e; }
+            mom_sums<float, true>(r1[r], r2[r], r3[r], r4[r], f[0], f[1], fp[r], fe[r]);
         }
+        const double vp = sum_rows16(fp, l), ve = sum_rows16(fe, l);
         if (l32 < 16) {
-            const size_t o = ps.row(tc.I, tc.J) + band * 32 + 8 * (l32 >> 2) + 4 * h + (l32 & 3);
-            put_part(a.partP, o, (double)vp, p32);
-            put_part(a.partE, o, (double)ve, p32);
+            const int r = 8 * (l & 1) + 2 * (l & 2) + (l >> 1 & 2) + (l >> 3 & 1);
+            const size_t o = ps.row(tc.I, tc.J) + band * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+            put_part(a.partP, o, vp, p32);
+            put_part(a.partE, o, ve, p32);
         }
     }
     double m[4], p, e;

@@ -78,3 +78,26 @@ def test_fourth_power_recomputed(torch, m):
     assert p["series_reciprocal"] == 3 and p["recompute_aug"] == 1 and 1.25 * p["stateless_rho"] < 2.0 ** -8
     check_messages(s, K, y, 4)
     s.close()
+
+
+# The recomputed form adds a row's 256 columns of a tile in FP64 (a lane's eight
+# in FP32), the plane four strips of 64 added in FP32: its message sums must be
+# the closer ones to FP64 (rms over the nodes; the longer FP32 sums make up
+# about half of the plane's error here, so by 5% at least).
+def test_recomputed_row_sums_in_64_bits(torch):
+    from paper_0810_1648_amd import inputs
+    X, y = inputs.cluster_mixture(6000, 20, 71)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    m = {}
+    for name, kw in (("fp64", dict(precision="fp64", edge_state="stored", kstore="materialise")),
+                     ("plane", dict(FIXED, kstore="materialise")), ("recompute", dict(FIXED, kstore="recompute"))):
+        base = dict(tol_abs=0.0, tol_rel=0.0, stagnation_window=0)
+        s = gabp.GabpSVM(gamma=0.0005, C=1.0, max_sweeps=6, **dict(base, **kw))
+        s.solve(Xd, yd)
+        if name != "fp64":
+            assert s.plan()["series_reciprocal"] == 3
+        m[name] = s.adiag() - s.ptilde()
+        s.close()
+    rms = {k: float(np.std(m[k] / m["fp64"])) for k in ("plane", "recompute")}
+    print(f"[case] message sums rms {rms}", flush=True)
+    assert rms["recompute"] <= 0.95 * rms["plane"], rms
