@@ -673,7 +673,7 @@ __device__ inline void put_tile_sums(const SweepArgs& a, const TileCoord& tc, AT
 // are rr^2 of the message sums and stay in: without them a sweep of 100,000
 // points over the plane took 0.8% less and one recomputed from 120,000 points
 // 8%, with the precisions P~ off by rr^3.
-template <int D, int SER> constexpr bool mom_plan() {
+template <int D, int SER> constexpr bool mom_plan() {   // (not with kSerLevels)
     return SER > 0 && (D == 1 || (D == 2 && SER == 1) || (D == 3 && SER == 3));
 }
 template <class XT, int D> struct Mom {
@@ -930,16 +930,18 @@ __device__ inline void sweep_tile_mom(const SweepArgs& a, int64_t tile, int slot
 // the top (SER = 3: one term at the top, none at the lower levels).
 // |e| <= rho^2 holds for every message by the a-priori contraction bound (no
 // run-time check is needed); the host picks the series only when the
-// neglected terms are below the arithmetic's precision.  The lower levels
-// carry G = P / (-a^2) and F = E / a, which the one-term series turns into
-// G_ij = u_i - a^2 u_i^2 G_ji and F_ij = G_ij (a F_ji - S_i): the deepest
-// level (reverse messages zero) is G = u, F = -S/P~ of its source and costs
-// nothing, a middle level costs four operations per direction (two with
+// neglected terms are below the arithmetic's precision.  KSER: SER, with
+// kSerLevels where powers of K' would leave the range (series_kernels).  The
+// lower levels carry G = P / (-a^2) and F = E / a, which the one-term series
+// turns into G_ij = u_i - a^2 u_i^2 G_ji and F_ij = G_ij (a F_ji - S_i): the
+// deepest level (reverse messages zero) is G = u, F = -S/P~ of its source and
+// costs nothing, a middle level costs four operations per direction (two with
 // G = u).
-template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int SER, int XL = 0, bool WR = true>
+template <class ST, class MT, class AT, int KSRC, int GK, int D, bool FIRST, int KSER, int XL = 0, bool WR = true>
 __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top, TileSums<AT>* out = nullptr,
                                   int split = 1, int sub = 0) {
-    if constexpr (mom_plan<D, SER>()) {
+    constexpr int SER = KSER & ~kSerLevels;
+    if constexpr (mom_plan<D, KSER>()) {
         sweep_tile_mom<ST, MT, AT, KSRC, GK, D, SER>(a, tile, slot_top, out, split, sub);
         return;
     } else {
@@ -1348,7 +1350,7 @@ __global__ __launch_bounds__(WG) void k_sweep_st(SweepArgs a) {
 template <class ST, class MT, class AT, int KSRC, int D, int SER>
 constexpr bool chunk_sweep_ok() {
     return KSRC == KSRC_PLANE && std::is_same<ST, float>::value &&
-           chunk_plan(std::is_same<AT, float>::value || MsgT<ST, MT, AT, SER>::F32, D, SER);
+           chunk_plan(std::is_same<AT, float>::value || MsgT<ST, MT, AT, SER>::F32, D, SER & ~kSerLevels);
 }
 
 // Synchronous sweep over chunks of C x C tiles (a.chunks: Ic << 16 | Jc,
@@ -2071,17 +2073,19 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4, 8))) void
 // Run-time (levels, reciprocal form) of a stateless launch to the
 // compile-time pair (D, SER): exact reciprocals up to 8 levels, the series
 // (one- or two-term top level) up to 6.  Every pair is its own
-// instantiation, so the level loops are fully unrolled and branch-free.
+// instantiation, so the level loops are fully unrolled and branch-free.  The
+// forms of kSerLevels run where the powers of K' leave the range.
 template <class F>
 inline hipError_t with_stateless(int levels, int ser, F&& f) {
     using std::integral_constant;
 #define GABP_SL(S_, L_) \
-    case S_ * 16 + L_: f(integral_constant<int, L_>{}, integral_constant<int, S_>{}); return hipSuccess;
+    case (S_) * 16 + L_: f(integral_constant<int, L_>{}, integral_constant<int, S_>{}); return hipSuccess;
     switch (ser * 16 + levels) {
         GABP_SL(0, 1) GABP_SL(0, 2) GABP_SL(0, 3) GABP_SL(0, 4) GABP_SL(0, 5) GABP_SL(0, 6) GABP_SL(0, 7) GABP_SL(0, 8)
         GABP_SL(1, 1) GABP_SL(1, 2) GABP_SL(1, 3) GABP_SL(1, 4) GABP_SL(1, 5) GABP_SL(1, 6)
         GABP_SL(2, 1) GABP_SL(2, 2) GABP_SL(2, 3) GABP_SL(2, 4) GABP_SL(2, 5) GABP_SL(2, 6)
         GABP_SL(3, 3) GABP_SL(3, 4) GABP_SL(3, 5) GABP_SL(3, 6)
+        GABP_SL(1 + kSerLevels, 2) GABP_SL(3 + kSerLevels, 3)
         default: return hipErrorInvalidValue;
     }
 #undef GABP_SL
@@ -2091,7 +2095,7 @@ template <class ST, class MT, class AT, int D, int SER>
 inline void served_d(bool grouped, const ReqDesc* reqs, const uint2* items, int n, hipStream_t s) {
     const int g = std::max(1, std::min(n, 2048));
     if (grouped)
-        hipLaunchKernelGGL((k_sweep_dir_batched<ST, MT, AT, D, SER>), dim3(g), dim3(WG), 0, s, reqs, items, n);
+        hipLaunchKernelGGL((k_sweep_dir_batched<ST, MT, AT, D, (SER & ~kSerLevels)>), dim3(g), dim3(WG), 0, s, reqs, items, n);
     else if constexpr (chunk_sweep_ok<ST, MT, AT, KSRC_PLANE, D, SER>())
         hipLaunchKernelGGL((k_sweep_batched_chunk<ST, MT, AT, D, SER>), dim3(g), dim3(WG), 0, s, reqs, items, n);
     else
@@ -2215,7 +2219,7 @@ inline hipError_t sweep_grouped(int levels, int ser, const SweepArgs& a, const u
         return hipGetLastError();
     }
     const hipError_t e = with_stateless(levels, ser, [&](auto L_, auto S_) {
-        grouped_d<ST, MT, AT, KSRC, GK, decltype(L_)::value, decltype(S_)::value>(a, dir, ndir, t, s);
+        grouped_d<ST, MT, AT, KSRC, GK, decltype(L_)::value, (decltype(S_)::value & ~kSerLevels)>(a, dir, ndir, t, s);
     });
     return e != hipSuccess ? e : hipGetLastError();
 }

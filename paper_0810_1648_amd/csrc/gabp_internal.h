@@ -111,6 +111,24 @@ inline int stateless_series_form(int prec, int levels, double rr) {
     if (std::pow(rr, 6) <= eps) return 2;
     return 0;
 }
+// The kernels of a synchronous series sweep: the form, plus kSerLevels where the
+// plan would sum over powers of K' (two levels of form 1, three of form 3) but
+// those powers leave the range of its arithmetic, and the sweep runs level by
+// level instead.  The recursion forms K'^2 only; the sums K'^3 and K'^4, beside
+// 1/P~^2.  amax bounds |K'_ij|, pmin (the contraction bound's m*) every P~ from
+// below.  FP32: K' up to 2^30 keeps K'^4 at 2^120, so that its products, which
+// are below K'^2 again, sum without overflow; P~ from 2^-16 on: what underflow
+// takes from K'^4 (2^-126 each) is then at most 2^-126 2^64 of P~ for one
+// pair, 2^-38 for 2^24 of them.  FP64 likewise with 2^240 and 2^-200.  (Entries
+// of order one, as every RBF kernel has, run 1.05 to 1.5 times as fast by the
+// sums; the parameter lambda_aug and a given matrix reach any scale.)
+constexpr int kSerLevels = 4;
+inline int series_kernels(int prec, int levels, int ser, double amax, double pmin) {
+    if (!((levels == 2 && ser == 1) || (levels == 3 && ser == 3))) return ser;
+    const bool fp64 = prec == PREC_FP64;
+    const bool in_range = amax <= std::ldexp(1.0, fp64 ? 240 : 30) && pmin >= std::ldexp(1.0, fp64 ? -200 : -16);
+    return in_range ? ser : ser | kSerLevels;
+}
 // Entries of the grouped schedule's visit lists: bit 31 = messages into the
 // row block (BWD; clear: into the column block), bit 30 = both blocks lie in
 // the visited group, low 30 bits = tile index.
@@ -399,7 +417,8 @@ struct SparseSweep {
 };
 hipError_t launch_sp_sweep(int prec, const SparseSweep& a, int t, hipStream_t s);
 // A-priori contraction bound: one[0] = -m* (minus the aggregate lower
-// bound), one[1] = rho (+inf when no bound exists).
+// bound), one[1] = rho (+inf when no bound exists), one[2] = max |K'_ij|.
+// blk: two doubles per 256 nodes.
 hipError_t launch_rho_bound(int64_t N, const double* Adiag, const double* rowmax, const double* rsum,
                             double* blk, double* one, hipStream_t s);
 // Residual certificate of a finished dense solve: out[0] = ||1 - A alpha||_inf,

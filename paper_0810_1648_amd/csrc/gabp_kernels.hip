@@ -620,12 +620,13 @@ __global__ void k_diag(int64_t N, int NB, const double* __restrict__ psum,
     }
 }
 
+// Maxima of consecutive arrays of n values, one workgroup each.
 __global__ void k_max_reduce(int n, const double* __restrict__ in, double* out) {
     __shared__ double sh4[4];
     double v = -INFINITY;
-    for (int k = threadIdx.x; k < n; k += blockDim.x) v = fmax(v, in[k]);
+    for (int k = threadIdx.x; k < n; k += blockDim.x) v = fmax(v, in[(size_t)blockIdx.x * n + k]);
     v = block_max(v, sh4);
-    if (threadIdx.x == 0) *out = v;
+    if (threadIdx.x == 0) out[blockIdx.x] = v;
 }
 
 __global__ void k_diag_shift(int64_t N, const double* __restrict__ kdiag,
@@ -878,7 +879,11 @@ __global__ void k_bound_rho(int64_t N, const double* __restrict__ Adiag, const d
         v = (m > 0.0 && lo >= m * (1.0 - 1e-12)) ? rowmax[i] / lo : INFINITY;
     }
     v = block_max(v, sh4);
-    if (threadIdx.x == 0) blk[blockIdx.x] = v;
+    const double mx = block_max(i < N ? rowmax[i] : 0.0, sh4);
+    if (threadIdx.x == 0) {
+        blk[blockIdx.x] = v;
+        blk[gridDim.x + blockIdx.x] = mx;
+    }
 }
 
 // ------------------------------------------------------------- queries --
@@ -1140,7 +1145,7 @@ hipError_t launch_rho_bound(int64_t N, const double* Adiag, const double* rowmax
     hipLaunchKernelGGL(k_bound_root, dim3(nb), dim3(WG), 0, s, N, Adiag, rowmax, rsum, blk);
     hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(WG), 0, s, (int)nb, blk, one);
     hipLaunchKernelGGL(k_bound_rho, dim3(nb), dim3(WG), 0, s, N, Adiag, rowmax, rsum, one, blk);
-    hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(WG), 0, s, (int)nb, blk, one + 1);
+    hipLaunchKernelGGL(k_max_reduce, dim3(2), dim3(WG), 0, s, (int)nb, blk, one + 1);
     return hipGetLastError();
 }
 

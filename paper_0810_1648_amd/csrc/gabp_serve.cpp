@@ -140,7 +140,8 @@ struct Req {
     int bypassed = 0;
     int32_t refused = 0; // set up but refused (gabp_status): no plan without a bound
     int levels = 0;      // 0: stored pair records; >= 1: stateless levels
-    int ser = 0;         // stateless reciprocals: 0 exact, 1 / 2 series (top-level terms)
+    int ser = 0;         // stateless reciprocals: 0 exact, 1 - 3 series (stateless_series_form)
+    int kser = 0;        // ... and the kernels that run it (series_kernels)
     int split = 1;       // row parts per tile
     bool chunked = false;  // synchronous sweeps over 2 x 2 chunks of tiles
     double rho = 0.0;    // contraction bound
@@ -308,8 +309,8 @@ hipError_t setup_request(gabp_server* S, Req& r) {
     // edge state from the contraction bound (same rule as a single solve)
     CK(launch_rho_bound(r.N, (double*)P(B_ADIAG), (double*)P(B_ROWMAX), (double*)P(B_RSUM),
                         (double*)P(B_BLK1), (double*)P(B_ONE), s));
-    double hb[2] = {0.0, 0.0};
-    CK(hipMemcpyAsync(hb, P(B_ONE), 16, hipMemcpyDeviceToHost, s));
+    double hb[3] = {0.0, 0.0, 0.0};
+    CK(hipMemcpyAsync(hb, P(B_ONE), 24, hipMemcpyDeviceToHost, s));
     CK(hipStreamSynchronize(s));
     r.rho = hb[1];
     const double rr = 1.25 * r.rho;
@@ -325,6 +326,7 @@ hipError_t setup_request(gabp_server* S, Req& r) {
     }
     r.levels = stateless ? (r.p.stateless_depth > 0 ? r.p.stateless_depth : std::min(dneed, 8)) : 0;
     r.ser = stateless ? stateless_series_form(r.prec, r.levels, rr) : 0;
+    r.kser = r.p.schedule == GABP_SCHED_GROUPED ? r.ser : series_kernels(r.prec, r.levels, r.ser, hb[2], -hb[0]);
     if (stateless) {
         // the pair-record planes are not needed: give them back to the arena
         const std::vector<int> planes = {B_PF, B_PB, B_EF, B_EB};
@@ -421,7 +423,7 @@ hipError_t setup_request(gabp_server* S, Req& r) {
 // Sweep item: the request's slot and the row part of the tile or entry.
 inline uint2 part_item(int slot, int part, unsigned tile) { return make_uint2((unsigned)slot | (unsigned)part << 16, tile); }
 
-inline int group_key(const Req& r) { return (r.grouped ? 1000 : 0) + r.prec * 100 + r.ser * 10 + r.levels; }
+inline int group_key(const Req& r) { return (r.grouped ? 1000 : 0) + r.prec * 100 + r.kser * 10 + r.levels; }
 
 // Rebuilds the launch groups, their fixed tile lists and the slot order
 // from the active slots.
@@ -434,7 +436,7 @@ hipError_t rebuild_lists(gabp_server* S) {
         auto& G = S->groups[group_key(*r)];
         G.prec = r->prec;
         G.levels = r->levels;
-        G.ser = r->ser;
+        G.ser = r->kser;
         G.grouped = r->grouped;
         G.slot_list.push_back((int)k);
     }

@@ -580,14 +580,16 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     // ---- plan of the edge state from the contraction bound (rho bounds
     // |A_ij| / Q_ij; stateless_levels_needed and stateless_series_form give
     // the level count and the reciprocal form)
-    double rho = INFINITY;
+    double rho = INFINITY, pmin = 0.0, amax = 0.0;
     {
-        double hb[2] = {0.0, 0.0};
+        double hb[3] = {0.0, 0.0, 0.0};
         HIPCHK(h, launch_rho_bound(N, h->Adiag.as<double>(), h->rowmax.as<double>(), h->rsum.as<double>(),
                                    h->blk1.as<double>(), h->one.as<double>(), s));
-        HIPCHK(h, hipMemcpyAsync(hb, h->one.p, 16, hipMemcpyDeviceToHost, s));
+        HIPCHK(h, hipMemcpyAsync(hb, h->one.p, 24, hipMemcpyDeviceToHost, s));
         HIPCHK(h, hipStreamSynchronize(s));
+        pmin = -hb[0];
         rho = hb[1];
+        amax = hb[2];
     }
     const double rr = 1.25 * rho;
     const int dneed = stateless_levels_needed(prec, rr);
@@ -614,6 +616,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     }
     if (!cur_stored) depth = (p.stateless_depth > 0) ? p.stateless_depth : std::min(dneed, 8);
     const int ser = cur_stored ? 0 : stateless_series_form(prec, depth, rr);
+    const int kser = series_kernels(prec, depth, ser, amax, pmin);
     if (probe && cur_stored) {
         if (h->Pf.ensure(plane) != hipSuccess || h->Pb.ensure(plane) != hipSuccess ||
             h->Ef.ensure(plane) != hipSuccess || h->Eb.ensure(plane) != hipSuccess) {
@@ -747,7 +750,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
         char* wM = hmean ? static_cast<char*>(hmean) + (size_t)((t + 1) % Rr) * NPAD * agg_bytes : nullptr;
         if (!grouped) {
             // the events take the sweep dispatch's own timestamps
-            HIPCHK(h, launch_sweep(prec, ksrc, gram, sa.levels, t < sa.period, ser, sa, s,
+            HIPCHK(h, launch_sweep(prec, ksrc, gram, sa.levels, t < sa.period, kser, sa, s,
                                    loop.begin(t), loop.end(t)));
             fa.Pt = wP; fa.S = wS; fa.Inv = wI; fa.Mean = wM;
             HIPCHK(h, launch_finalize(prec, fa, s));

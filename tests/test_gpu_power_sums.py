@@ -101,3 +101,64 @@ def test_recomputed_row_sums_in_64_bits(torch):
     rms = {k: float(np.std(m[k] / m["fp64"])) for k in ("plane", "recompute")}
     print(f"[case] message sums rms {rms}", flush=True)
     assert rms["recompute"] <= 0.95 * rms["plane"], rms
+
+
+# A system times a power of two is the same system: the same rho, depth and
+# form, alpha over the scale.  Beyond 2^30 (or P~ below 2^-16) the fourth power
+# of K' leaves the range of FP32, and the sweep runs level by level.
+# Tolerance: the rounding of the two ways, 16 x 2^-24 each.
+@pytest.mark.parametrize("exponent", [-53, -43, -20, 30, 33, 43, 53])
+@pytest.mark.parametrize("prec,depth", [("fp32", 2), ("fp32", 3), ("mixed", 2), ("mixed", 3)])
+@pytest.mark.parametrize("chunk", [1, 2])
+def test_given_matrix_of_any_scale(torch, exponent, prec, depth, chunk):
+    n, scale = 513, 2.0 ** exponent
+    rng = np.random.default_rng(n)
+    K = 1.0 + 0.01 * rng.random((n, n))
+    K = ((K + K.T) / 2).astype(np.float32).astype(np.float64)
+    y = labels(rng, n)
+    yd = torch.from_numpy(y).cuda()
+    got = {}
+    for f in (1.0, scale):
+        s = gabp.GabpSVM(kernel="precomputed", C=1e30, tile_chunk=chunk, max_sweeps=6,
+                         **dict(FIXED, precision=prec, stateless_depth=depth))
+        assert s.solve_kernel(torch.from_numpy(K * f).cuda(), yd) == gabp.E_NOT_CONVERGED     # (sweeps as asked)
+        p = s.plan()
+        assert p["series_reciprocal"] == (3 if depth == 3 else 1) and p["tile_chunk"] == chunk
+        got[f] = s.alpha() * f
+        if prec == "mixed":
+            check_messages(s, K * f, y, 6)
+        s.close()
+    err = float(np.max(np.abs(got[scale] - got[1.0])) / np.max(np.abs(got[1.0])))
+    assert err <= 32 * 2.0 ** -24, err
+
+
+# the augmentation lambda^2 = 2^44 makes every entry of an RBF system that large:
+# the plane, K' recomputed (through the band; 6,000 points: the plans that take
+# the MFMA output otherwise) and a served request, against FP64
+@pytest.mark.parametrize("n", [513, 6000])
+def test_large_augmentation(torch, n):
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, 20)).astype(np.float32)
+    y = labels(rng, n)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    common = dict(gamma=0.05, C=1.0, lambda_aug=2.0 ** 22, max_sweeps=5, tol_abs=0.0, tol_rel=0.0, stagnation_window=0)
+    s = gabp.GabpSVM(precision="fp64", edge_state="stored", kstore="materialise", **common)
+    s.solve(Xd, yd)
+    ref = s.alpha()
+    s.close()
+    for prec, depth, kstore in (("mixed", 3, "materialise"), ("mixed", 3, "recompute"), ("fp32", 2, "materialise"),
+                                ("fp32", 2, "recompute")):
+        print(f"[case] lambda 2^22 n={n} {prec} {depth} {kstore}", flush=True)
+        kw = dict(common, precision=prec, stateless_depth=depth, edge_state="stateless", kstore=kstore)
+        s = gabp.GabpSVM(**kw)
+        assert s.solve(Xd, yd) == gabp.E_NOT_CONVERGED
+        assert s.plan()["series_reciprocal"] == (3 if depth == 3 else 1)
+        a = s.alpha()
+        s.close()
+        assert float(np.max(np.abs(a - ref)) / np.max(np.abs(ref))) <= 1e-5
+        if kstore == "materialise" and n == 513:
+            with gabp.GabpServer() as srv:
+                t = srv.submit(X, y, **kw)
+                assert srv.wait(t, 60.0)
+                served, _ = srv.result(t)
+            assert np.array_equal(served, a)
