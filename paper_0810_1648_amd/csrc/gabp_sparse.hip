@@ -352,11 +352,12 @@ __device__ inline void sp_maxima(double d, double am, const SparseSweep& a) {
 // t's), and nothing is scattered or gathered but the neighbours' packed
 // aggregates: 25 bytes per directed edge in row order and one 16-byte read
 // that the locality order keeps in L2.  With q = P~_k - P_jk of the older
-// pair, P_kj = -a^2 / q and E_kj = -a (S_k - E_jk) / q, both new messages
-// follow from one reciprocal:
-//   P_jk = -a^2 q / D,  E_jk = -a (S_j q + a (S_k - E_jk)) / D,  D = P~_j q + a^2
-// (q > 0 was checked as the reverse message's own cavity one sweep earlier,
-// so the cavity P~_j - P_kj = D / q is positive where D is).
+// pair (checked as the reverse message's own cavity one sweep earlier) and
+// h = a / q, the reverse message is P_kj = -a h, E_kj = -h (S_k - E_jk), and
+//   P_jk = -a^2 / Q,  E_jk = -a (S_j + h (S_k - E_jk)) / Q,  Q = P~_j + a h.
+// (Both follow from the one reciprocal of Q q as well, but its products a^2 q
+// and P~_j q leave the range of FP32 at entries of 1e12, a^2 only at 1e19;
+// the second reciprocal costs nothing beside the neighbours' reads.)
 // (Records per edge updated by one thread and gathered by node through a
 // permutation moved 12.1 GB per sweep at 90.8 M edges, 2.63 ms with their five
 // launches; this is 4.5 GB and 1.75 ms, 0.65 of them the neighbours' reads.
@@ -404,15 +405,15 @@ __global__ __launch_bounds__(WG) void k_sp_sweep(SparseSweep a, int t) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const MT av = (MT)kk[u], a2 = av * av;
-            MT qk = 1, d = (MT)g[u][0], x = (MT)g[u][1];
+            MT d = (MT)g[u][0], x = (MT)g[u][1];
             if (!FIRST) {
-                qk = Pk - (MT)old[u / 2][2 * (u & 1)];
-                d = fma(d, qk, a2);
-                x = fma(x, qk, av * (Sk - (MT)old[u / 2][2 * (u & 1) + 1]));
+                const MT h = av * rcp_pos(Pk - (MT)old[u / 2][2 * (u & 1)]);
+                d = fma(av, h, d);
+                x = fma(h, Sk - (MT)old[u / 2][2 * (u & 1) + 1], x);
             }
             bad |= !(d > (MT)0);
             const MT r = rcp_pos(d);
-            const ST mp = (ST)(-(a2 * qk) * r), me = (ST)(-(av * x) * r);
+            const ST mp = (ST)(-a2 * r), me = (ST)(-(av * x) * r);
             m[u / 2][2 * (u & 1)] = mp;
             m[u / 2][2 * (u & 1) + 1] = me;
             sp += (AT)mp;
