@@ -393,7 +393,9 @@ int32_t gabp_abi_version(void);
  * the union of their tiles, one batched finalize and one batched stop rule.
  * Requests join and leave at step boundaries.  Each request has its own
  * partial sums and fixed reduction order, so its alpha is bitwise the same
- * whether it runs alone or in a mix.  Served plans materialise K'; the edge
+ * whether it runs alone or in a mix.  (A request that fits the arena only
+ * with fewer partial sums per tile than a single solve would take sums in
+ * another order than that solve.)  Served plans materialise K'; the edge
  * state (stored pair records or stateless) is chosen per request by the same
  * rule as gabp_svm_solve, and requests of the same precision and level count
  * share a launch.  A request with the GROUPED schedule advances one group

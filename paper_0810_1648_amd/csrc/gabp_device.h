@@ -2144,22 +2144,25 @@ inline hipError_t sweep_d(bool first, const SweepArgs& a, hipStream_t s, hipEven
         }
     }
     if constexpr (D == 0 && KSRC == KSRC_PLANE) {
-        // sweep a.between + 1 of its period: the planes written by the last
-        // one only (before the first period's end they are zero)
-        static_assert(kStoredPeriod == 3, "one instantiation per sweep of the period");
-        if (a.period != kStoredPeriod || a.between < 0 || a.between >= kStoredPeriod) return hipErrorInvalidValue;
+        if (a.period > 1) {
+            // sweep a.between + 1 of its period: the planes written by the
+            // last one only (before the first period's end they are zero)
+            static_assert(kStoredPeriod == 3, "one instantiation per sweep of the period");
+            if (a.period != kStoredPeriod || a.between < 0 || a.between >= kStoredPeriod) return hipErrorInvalidValue;
 #define GABP_ST(F_, X_) launch_ev(k_sweep_st<ST, MT, AT, KSRC, GK, F_, X_, X_ == kStoredPeriod - 1>, g, blk, s, e0, e1, a)
-        switch (a.between + (first ? kStoredPeriod : 0)) {
-            case 0: GABP_ST(false, 0); break;
-            case 1: GABP_ST(false, 1); break;
-            case 2: GABP_ST(false, 2); break;
-            case 3: GABP_ST(true, 0); break;
-            case 4: GABP_ST(true, 1); break;
-            default: GABP_ST(true, 2); break;
-        }
+            switch (a.between + (first ? kStoredPeriod : 0)) {
+                case 0: GABP_ST(false, 0); break;
+                case 1: GABP_ST(false, 1); break;
+                case 2: GABP_ST(false, 2); break;
+                case 3: GABP_ST(true, 0); break;
+                case 4: GABP_ST(true, 1); break;
+                default: GABP_ST(true, 2); break;
+            }
 #undef GABP_ST
-        return hipSuccess;
-    } else if constexpr (D == 0) {
+            return hipSuccess;
+        }
+    }
+    if constexpr (D == 0) {
         if (first) {
             launch_ev(k_sweep<ST, MT, AT, KSRC, GK, D, true, 0>, g, blk, s, e0, e1, a);
             return hipSuccess;

@@ -183,6 +183,7 @@ __host__ __device__ inline int part_slots(int K, int NB, int split) { return spl
 // of four would save 5% of the bytes more and take another level in registers.
 // Planes that stay in the last-level cache take the period too: N = 2,000 in
 // FP64 6.0 -> 4.4 ms, N = 4,000 in MIXED 7.3 -> 5.5 ms, N = 500 1.6 and 1.8 ms.
+// A plan whose budget has no room for the two rings more writes every sweep.
 constexpr int kStoredPeriod = 3;
 // Storage index of tile (I, J), I <= J: row-major over the upper triangle.
 __host__ __device__ inline int64_t tile_index(int I, int J, int NB) {

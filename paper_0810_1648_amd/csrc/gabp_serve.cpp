@@ -158,18 +158,17 @@ struct Req {
 constexpr int kRing = 8;   // aggregate ring slots (stateless form)
 constexpr int kSide = 3;   // streams beside the main one for a step's sweeps
 
-void plan_sizes(Req& r) {
+// Buffer sizes and footprint; row parts per tile as in a single solve, as far
+// as the request fits an arena of `cap` bytes with them.
+void plan_sizes(Req& r, size_t cap) {
     const size_t st = (r.prec == PREC_FP64) ? 8 : 4;
     const size_t plane = (size_t)r.nt * TT * st;
-    // row parts per tile, as in a single solve
     const int G = r.p.schedule == GABP_SCHED_GROUPED ? std::min(r.p.sched_groups > 0 ? r.p.sched_groups : 16, r.NB) : 0;
     r.split = tile_split(G ? 2 * r.nt / G : r.nt);
-    const size_t part = (size_t)r.NB * part_stride(r.NB, r.split) * TILE * 8;
     const size_t fe = (size_t)r.NPAD * r.m_pad;
     std::vector<size_t> z(B_COUNT, 0);
     z[B_TILES] = (size_t)r.nt * 4;
     z[B_KP] = z[B_PF] = z[B_PB] = z[B_EF] = z[B_EB] = plane;
-    z[B_PARTP] = z[B_PARTE] = part;
     z[B_X] = (size_t)r.N * r.m * 4;
     z[B_Y] = (size_t)r.N * 4;
     z[B_MEAN] = (size_t)r.m * 8;
@@ -181,13 +180,17 @@ void plan_sizes(Req& r) {
     z[B_NRM] = (size_t)r.NPAD * 4;
     z[B_KDIAG] = z[B_ADIAG] = z[B_ROWMAX] = z[B_RSUM] = z[B_ALPHA] = (size_t)r.N * 8;
     z[B_PT] = z[B_S] = (size_t)kRing * r.NPAD * 8;
-    z[B_BLK1] = z[B_BLK2] = (size_t)(r.NPAD / FB + 1) * 8;
+    z[B_BLK1] = z[B_BLK2] = (size_t)(r.NPAD / WG + 1) * 8;
     z[B_ONE] = 64;
     z[B_STATUS] = sizeof(DevStatus);
     z[B_TRACE] = (size_t)r.p.max_sweeps * 8;
+    size_t rest = 0;
+    for (size_t b : z) rest += b ? align_up(b) : 0;
+    auto part = [&](int sp) { return (size_t)r.NB * part_stride(r.NB, sp) * TILE * 8; };
+    while (r.split > 1 && rest + 2 * align_up(part(r.split)) > cap) r.split /= 2;
+    z[B_PARTP] = z[B_PARTE] = part(r.split);
     r.sizes = z;
-    r.footprint = 0;
-    for (size_t b : z) r.footprint += b ? align_up(b) : 0;
+    r.footprint = rest + 2 * align_up(part(r.split));
 }
 
 }  // namespace
@@ -307,8 +310,9 @@ hipError_t setup_request(gabp_server* S, Req& r) {
                    r.p.diag_mode, r.p.C, r.p.diag_delta, (double*)P(B_ADIAG), (double*)P(B_ROWMAX),
                    (double*)P(B_RSUM), (double*)P(B_BLK1), (double*)P(B_ONE), s));
     // edge state from the contraction bound (same rule as a single solve)
+    // (scratch: alpha, which the initial aggregates write)
     CK(launch_rho_bound(r.N, (double*)P(B_ADIAG), (double*)P(B_ROWMAX), (double*)P(B_RSUM),
-                        (double*)P(B_BLK1), (double*)P(B_ONE), s));
+                        (double*)P(B_ALPHA), (double*)P(B_ONE), s));
     double hb[3] = {0.0, 0.0, 0.0};
     CK(hipMemcpyAsync(hb, P(B_ONE), 24, hipMemcpyDeviceToHost, s));
     CK(hipStreamSynchronize(s));
@@ -409,8 +413,9 @@ hipError_t setup_request(gabp_server* S, Req& r) {
     d.Adiag = (double*)P(B_ADIAG);
     d.y = (float*)P(B_Y);
     d.alpha = (double*)P(B_ALPHA);
-    d.blk_delta = (double*)P(B_BLK1);
-    d.blk_amax = (double*)P(B_BLK2);
+    // one value per 64 nodes, in arrays that the set-up is done with
+    d.blk_delta = (double*)P(B_RSUM);
+    d.blk_amax = (double*)P(B_ROWMAX);
     d.trace = (double*)P(B_TRACE);
     d.rule = StopRule{r.p.tol_abs, r.p.tol_rel, r.p.stagnation_rel, r.p.max_sweeps, r.p.stagnation_window};
     d.nblk = (int)((r.N + FB - 1) / FB);
@@ -851,7 +856,7 @@ gabp_status gabp_server_submit(gabp_server* S, const float* X, const float* y, i
     r->nt = n_tiles(r->NB);
     r->m_pad = (int)((m + 15) / 16 * 16);
     r->lam = (params->lambda_aug < 0.0) ? 1.0 / (double)N : params->lambda_aug;
-    plan_sizes(*r);
+    plan_sizes(*r, S->arena.cap);
     std::lock_guard<std::mutex> lk(S->mu);
     if (S->dev_error) { delete r; return GABP_E_DEVICE; }
     if (r->footprint > S->arena.cap) { delete r; return GABP_E_NOMEM; }

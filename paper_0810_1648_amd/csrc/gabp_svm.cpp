@@ -272,12 +272,12 @@ struct SweepLoop {
 // Results of a solve: alpha, P~, A_ii (N doubles each) and the labels (N
 // floats), packed on the device and downloaded at once, with the trace.
 size_t out_bytes(int64_t N) { return (size_t)N * 28; }
-hipError_t fetch_results(gabp_svm* h, int64_t N, int sweeps, hipStream_t s) {
+hipError_t fetch_results(gabp_svm* h, const void* out, int64_t N, int sweeps, hipStream_t s) {
     const size_t nb = out_bytes(N), nt = (size_t)std::max(sweeps, 0) * 8;
     hipError_t e = h->pin.ensure(nb + nt);
     if (e != hipSuccess) return e;
     char* b = static_cast<char*>(h->pin.p);
-    e = hipMemcpyAsync(b + nt, h->out_d.p, nb, hipMemcpyDeviceToHost, s);
+    e = hipMemcpyAsync(b + nt, out, nb, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && nt) e = hipMemcpyAsync(b, h->trace_d.p, nt, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipEventRecord(h->evp.ev[5], s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -333,11 +333,9 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     const int m_pad = rbf ? (int)((m + 15) / 16 * 16) : 16;
     const size_t st_bytes = (prec == PREC_FP64) ? 8 : 4;
     const size_t plane = (size_t)nt * TT * st_bytes;
-    // row parts per tile of the sweeps over whole tiles
     const bool grouped = p.schedule == GABP_SCHED_GROUPED;
     const int G = grouped ? std::min(p.sched_groups > 0 ? p.sched_groups : 16, NB) : 1;
-    const int split = tile_split(grouped ? 2 * nt / G : nt);
-    const size_t part = (size_t)NB * part_stride(NB, split) * TILE * sizeof(double);
+    auto part_bytes = [&](int sp) { return (size_t)NB * part_stride(NB, sp) * TILE * sizeof(double); };
     size_t feat = 0;
     if (rbf) {
         switch (gram) {
@@ -371,7 +369,7 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
         if (p.edge_state == GABP_EDGE_STATELESS && c.stored) continue;
         if (!c.kmat && !can_recompute) continue;
         const int R = c.stored ? 1 : 8;
-        const size_t n_ = (c.stored ? 4 * plane : 0) + (c.kmat ? plane : 0) + 2 * part + feat + vecs +
+        const size_t n_ = (c.stored ? 4 * plane : 0) + (c.kmat ? plane : 0) + 2 * part_bytes(1) + feat + vecs +
                           (size_t)2 * R * NPAD * 8;
         need_min = std::min(need_min, n_);
         if (n_ <= budget) { have = true; kmat = c.kmat; stored = c.stored; need = n_; break; }
@@ -388,9 +386,16 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     // and stateless waits for the contraction bound computed after the
     // diagonal weighting; the planes are allocated only if stored wins.
     const bool probe = stored && p.edge_state == GABP_EDGE_AUTO;
-    // (synchronous stored sweeps over the plane write their records every
-    // kStoredPeriod-th sweep and keep the aggregates of the sweeps between)
-    const int period = (kmat && !grouped) ? kStoredPeriod : 1;
+    // What only makes the sweeps faster is taken where the budget has room for
+    // it beside the plan: row parts per tile (their column sums have a slot
+    // each), and the aggregates of the sweeps between two writes of the stored
+    // records over the plane.
+    int split = tile_split(grouped ? 2 * nt / G : nt);
+    while (split > 1 && need + 2 * (part_bytes(split) - part_bytes(1)) > budget) split /= 2;
+    const size_t part = part_bytes(split);
+    need += 2 * (part - part_bytes(1));
+    const size_t between = (size_t)2 * (kStoredPeriod - 1) * NPAD * 8;
+    const int period = (kmat && stored && !grouped && need + between <= budget) ? kStoredPeriod : 1;
     const int R = (stored && !probe) ? period : 8;
     {
         // buffers of the previous solve are reused where large enough (a
@@ -424,7 +429,10 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     A(h->Pt, (size_t)R * NPAD * 8); A(h->S, (size_t)R * NPAD * 8);
     A(h->alpha_d, (size_t)N * 8); A(h->tmp, (size_t)NPAD * 8);
     A(h->blk1, (size_t)(NPAD / FB + 1) * 8); A(h->blk2, (size_t)(NPAD / FB + 1) * 8);
-    A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64); A(h->out_d, out_bytes(N));
+    A(h->one, 64); A(h->status_d, sizeof(DevStatus)); A(h->flag, 64);
+    // the packed results go where the partial sums were, but for the smallest N
+    const bool out_in_part = part >= out_bytes(N);
+    if (!out_in_part) A(h->out_d, out_bytes(N));
     A(h->trace_d, (size_t)p.max_sweeps * 8);
     if (rbf) {
         A(h->Xin, (size_t)N * m * 4); A(h->mean, (size_t)m * 8); A(h->nrm, (size_t)NPAD * 4);
@@ -441,7 +449,6 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
         return fail(h, GABP_E_NOMEM, std::string("device allocation failed: ") + hipGetErrorString(ae));
     }
 
-    const int ce = p.check_every;
     SweepLoop loop(h, s);
     HIPCHK(h, loop.prepare());
     hipEvent_t* ev = h->evp.ev.data();
@@ -781,10 +788,11 @@ gabp_status solve_impl(gabp_svm* h, const float* X, const double* K, const float
     const int final_slot = std::max(hs.t, 0) % Rr;
 
     // ---- outputs
+    double* out = out_in_part ? h->partP.as<double>() : h->out_d.as<double>();
     HIPCHK(h, launch_pack_out(prec, N, h->alpha_d.as<double>(),
                               static_cast<char*>(h->Pt.p) + (size_t)final_slot * NPAD * agg_bytes, 1,
-                              h->Adiag.as<double>(), h->yd.as<float>(), nullptr, h->out_d.as<double>(), s));
-    HIPCHK(h, fetch_results(h, N, hs.t, s));
+                              h->Adiag.as<double>(), h->yd.as<float>(), nullptr, out, s));
+    HIPCHK(h, fetch_results(h, out, N, hs.t, s));
 
     h->N = N; h->m = rbf ? m : 0; h->NB = NB; h->NPAD = NPAD; h->ntiles = nt; h->m_pad = m_pad;
     h->prec = prec; h->gram = gram; h->lam = lam; h->rbf = rbf;
@@ -939,7 +947,6 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
         h->release_all();
         return fail(h, GABP_E_NOMEM, std::string("device allocation failed: ") + hipGetErrorString(ae));
     }
-    const int ce = p.check_every;
     SweepLoop loop(h, s);
     HIPCHK(h, loop.prepare());
     hipEvent_t* ev = h->evp.ev.data();
@@ -1185,7 +1192,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     // ---- outputs, back in input order
     HIPCHK(h, launch_pack_out(prec, N, h->alpha_d.as<double>(), sw.PS[hs.t & 1], 2, h->Adiag.as<double>(),
                               h->yd.as<float>(), h->sp_order.as<int32_t>(), h->out_d.as<double>(), s));
-    HIPCHK(h, fetch_results(h, N, hs.t, s));
+    HIPCHK(h, fetch_results(h, h->out_d.p, N, hs.t, s));
 
     h->N = N; h->m = m; h->NB = NB; h->NPAD = NPAD; h->ntiles = nt; h->m_pad = m_pad;
     h->prec = prec; h->gram = gram; h->lam = lam; h->rbf = true;
