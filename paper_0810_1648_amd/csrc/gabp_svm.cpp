@@ -1101,9 +1101,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     A(h->sp_len, (size_t)(N + 1) * 8); A(h->sp_row, (size_t)(N + 1) * 8);
     A(h->sp_qrow, rows); A(h->sp_edge, (rows / 4 / WG + 1) * 4 * agg);
     A(h->sp_col, rows * 4); A(h->sp_rkv, rows * 4);
-    // records: the (P, E) message into every row's node, two sweeps; packed
-    // aggregates of two sweeps
-    A(h->Pf, 2 * rows * st_bytes); A(h->Pb, 2 * rows * st_bytes);
+    // packed aggregates of two sweeps
     A(h->Ef, (size_t)2 * NPAD * 8); A(h->Eb, (size_t)2 * NPAD * 8);
     if (ae != hipSuccess) {
         h->release_all();
@@ -1141,6 +1139,23 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
                              h->sp_keys2.as<uint64_t>(), h->sp_kv.as<float>(), h->sp_offi.as<int64_t>(),
                              h->sp_offj.as<int64_t>(), h->sp_row.as<int64_t>(), h->sp_col.as<int32_t>(),
                              h->sp_rkv.as<float>(), h->sp_qrow.as<int32_t>(), s));
+    // records: the (P, E) message into every row's node, two sweeps.  Where
+    // they do not fit beside what the build is done with (36 bytes a kept pair
+    // of keys, values and sort storage, and the staged features), that goes first
+    A(h->Pf, 2 * rows * st_bytes); A(h->Pb, 2 * rows * st_bytes);
+    if (ae != hipSuccess) {
+        HIPCHK(h, hipStreamSynchronize(s));
+        for (DevBuf* b : {&h->sp_keys, &h->sp_keys2, &h->sp_kv, &h->sp_kv2, &h->sp_tmp, &h->sp_offi, &h->sp_offj,
+                          &h->sp_len, &h->sp_xb, &h->sp_Xp, &h->Xin, &h->xs32, &h->xhi, &h->xlo, &h->xlo2})
+            b->release();
+        ae = hipSuccess;
+        A(h->Pf, 2 * rows * st_bytes); A(h->Pb, 2 * rows * st_bytes);
+    }
+    if (ae != hipSuccess) {
+        h->release_all();
+        return fail(h, GABP_E_NOMEM, std::string("device allocation of the records failed: ") +
+                                         hipGetErrorString(ae));
+    }
     HIPCHK(h, hipEventRecord(ev[2], s));
 
     // ---- diagonal weighting from the sparse row sums (one partial per node)

@@ -83,3 +83,30 @@ def test_augmented_rows_of_more_than_2_32_values(torch):
     assert bool((b[:, :m] == 1).all()) and bool((a[:, :m] == 1).all())
     assert torch.equal(a[:, m].float(), nrm) and bool((a[:, m + 1] == 1).all())
     assert bool((b[:, m] == -0.5).all()) and torch.equal(b[:, m + 1].float(), -0.5 * nrm)
+
+
+# 80 bytes per kept pair hold the build (with an edge list 1.5 times the graph)
+# and, after it, the sweep: 2e8 pairs in 16 GiB, the same to the bit
+def test_records_take_the_place_of_the_sort(torch):
+    n = 20_000
+    free = torch.cuda.mem_get_info()[0]
+    if free < 60 << 30:
+        pytest.skip("needs 60 GiB of device memory")
+    rng = np.random.default_rng(6)
+    X = torch.from_numpy((0.3 * rng.standard_normal((n, 6))).astype(np.float32)).cuda()
+    y = torch.from_numpy(np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)).cuda()
+    kw = dict(kernel="rbf_sparse", sparse_tau=1e-12, gamma=0.5, C=10.0, precision="mixed", max_sweeps=3, tol_abs=0.0,
+              tol_rel=0.0, stagnation_window=0)
+    alpha = []
+    for left in (None, 16 << 30):
+        torch.cuda.empty_cache()
+        rest = torch.empty(torch.cuda.mem_get_info()[0] - left, dtype=torch.uint8, device="cuda") if left else None
+        s = gabp.GabpSVM(**kw)
+        for _ in range(2 if left else 1):          # (again on a handle that holds what it needs)
+            s.solve(X, y)
+            assert s.plan()["n_edges"] == n * (n - 1) // 2
+            alpha.append(s.alpha())
+        s.close()
+        del rest
+    torch.cuda.empty_cache()
+    assert np.array_equal(alpha[0], alpha[1]) and np.array_equal(alpha[0], alpha[2])
