@@ -223,14 +223,20 @@ __global__ void k_sp_unpack(const uint64_t* __restrict__ keys, int64_t E, int sh
     keys_t[e] = ((uint64_t)j << sh) | (uint64_t)i;
 }
 
-// off[k] = first position whose key's node (key >> sh) is >= k, k = 0 .. N:
-// every position fills the nodes that begin at it.
+// off[k] = first position whose key's node (key >> sh) is >= k, k = 0 .. N, by
+// bisection: a thread per position that fills the nodes up to its own leaves a
+// run of points without edges to one lane (490,000 points, none with an edge:
+// 24.5 of the 26.4 ms of their build).
 __global__ void k_sp_offsets(const uint64_t* __restrict__ keys, int64_t E, int sh, int64_t N, int64_t* __restrict__ off) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e > E) return;
-    const int64_t lo = (e > 0) ? (int64_t)(keys[e - 1] >> sh) + 1 : 0;
-    const int64_t hi = (e < E) ? (int64_t)(keys[e] >> sh) : N;
-    for (int64_t k = lo; k <= hi; ++k) off[k] = e;
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k > N) return;
+    int64_t lo = 0, hi = E;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if ((int64_t)(keys[mid] >> sh) < k) lo = mid + 1;
+        else hi = mid;
+    }
+    off[k] = lo;
 }
 
 // Row lengths: a node's edges of both ends in whole quads, at least one.
@@ -844,7 +850,7 @@ hipError_t launch_sp_unpack(const uint64_t* keys, int64_t E, int sh, int32_t* ei
 }
 
 hipError_t launch_sp_offsets(const uint64_t* keys, int64_t E, int sh, int64_t N, int64_t* off, hipStream_t s) {
-    hipLaunchKernelGGL(k_sp_offsets, dim3(blocks(E + 1)), dim3(WG), 0, s, keys, E, sh, N, off);
+    hipLaunchKernelGGL(k_sp_offsets, dim3(blocks(N + 1)), dim3(WG), 0, s, keys, E, sh, N, off);
     return hipGetLastError();
 }
 

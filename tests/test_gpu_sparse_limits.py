@@ -110,3 +110,26 @@ def test_records_take_the_place_of_the_sort(torch):
         del rest
     torch.cuda.empty_cache()
     assert np.array_equal(alpha[0], alpha[1]) and np.array_equal(alpha[0], alpha[2])
+
+
+# Points without edges cost the build no more than the same points with edges
+# to their neighbours (a chain of stores by one lane took ten times as long;
+# 1 ms for the timing's own spread).
+def test_isolated_points_in_parallel(torch):
+    side = 700
+    X = np.ascontiguousarray(np.indices((side, side)).reshape(2, -1).T.astype(np.float32) - side // 2)
+    y = np.where(np.random.default_rng(1).random(len(X)) < 0.5, 1.0, -1.0).astype(np.float32)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    ms = {}
+    for tau, edges in ((0.5, 0), (0.04, 2 * side * (side - 1))):       # K of neighbours: 1 / 16
+        s = gabp.GabpSVM(kernel="rbf_sparse", sparse_tau=tau, gamma=4.0 * np.log(2.0), C=1.0, precision="mixed",
+                         max_sweeps=2)
+        t = []
+        for _ in range(4):
+            s.solve(Xd, yd)
+            assert s.plan()["n_edges"] == edges
+            t.append(s.timings()["kbuild_ms"])
+        ms[edges] = min(t)
+        s.close()
+    print(f"[case] build of isolated points and of a grid: {ms} ms", flush=True)
+    assert ms[0] <= ms[2 * side * (side - 1)] + 1.0, ms
