@@ -570,13 +570,32 @@ def sweep_label(plan, edge_name, extra=""):
 def sweep_kernel_name(precision, plan):
     """rocprofv3's name of the synchronous sweep kernel a plan launches over
     the materialised K' (template arguments as above)."""
-    if plan["edge_state"] == 1:   # stored pair records (sweeps after the first)
+    if plan["edge_state"] == 1:   # stored pair records, written in every sweep
         return f"gabp::k_sweep<{TYPES[precision]}, 0, 0, 0, false, 0>"
     if plan.get("tile_chunk", 1) > 1:
         return (f"gabp::k_sweep_chunk<{TYPES[precision]}, 0, {plan['stateless_depth']}, "
                 f"{int(plan['series_reciprocal'])}, {plan['tile_chunk']}>")
     return (f"gabp::k_sweep<{TYPES[precision]}, 0, 0, {plan['stateless_depth']}, false, "
             f"{int(plan['series_reciprocal'])}>")
+
+
+def launched_sweep_names(precision, plan):
+    """rocprofv3's names of the kernels that the sweeps of a single synchronous
+    solve over the materialised K' run in turn: with stored pair records the
+    three sweeps of a period (template arguments: storage, message, aggregate
+    type, K' source, Gram kind, first period, sweeps since the records were
+    written, whether this one writes them), else one kernel."""
+    if plan["edge_state"] == 1:
+        return [f"gabp::k_sweep_st<{TYPES[precision]}, 0, 0, false, {k}, {'true' if k == 2 else 'false'}>"
+                for k in range(3)]
+    return [sweep_kernel_name(precision, plan)]
+
+
+def sweep_traffic(path, precision, plan):
+    """Traffic (GB per working launch, the mean over the kernels that take
+    turns) of a solve's sweeps, if the stored counters match the sources."""
+    t = [counter_traffic_kernel(path, n) for n in launched_sweep_names(precision, plan)]
+    return None if None in t else sum(t) / len(t)
 
 
 def main():
@@ -647,7 +666,7 @@ def main():
     stateless = plan["edge_state"] == gabp.EDGE["stateless"]
     recompute = plan["kstore"] == gabp.KSTORE["recompute"]
     edge_name = "stateless" if stateless else "stored"
-    traffic = counter_traffic_kernel(a.traffic_json, sweep_kernel_name(a.precision, plan))
+    traffic = sweep_traffic(a.traffic_json, a.precision, plan)
     if not recompute:
         # the sweep streams the K' plane (and, with stored records, the four
         # pair-record planes): HBM-bound on its algorithmic bytes
@@ -678,7 +697,7 @@ def main():
                       "err_vs_oracle": rel_err(sinfo["alpha"], aref),
                       "rel_diff_alpha_vs_main": rel_err(sinfo["alpha"], info["alpha"]),
                       "roofline": hbm_roof(sp, sk_ / max(sl_, 1), sl_, "k_sweep_st (stored, K' materialised)",
-                                           counter_traffic_kernel(a.traffic_json, sweep_kernel_name(a.precision, sp)))}
+                                           sweep_traffic(a.traffic_json, a.precision, sp))}
         print(f"[bench] stored state: {ss_} sweeps in {sw_:.3f} s", file=sys.stderr, flush=True)
 
     grouped = None
