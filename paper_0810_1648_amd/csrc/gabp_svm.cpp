@@ -889,6 +889,7 @@ gabp_status solve_sparse_impl(gabp_svm* h, const float* X, const float* y, int64
     h->have_result = false;
     h->resid_valid = false;
     h->status = GABP_E_STATE;
+    h->err.clear();
     const gabp_svm_params& p = h->p;
     if (N < 1 || m < 1 || !y) return fail(h, GABP_E_INVALID, "N >= 1, m >= 1 and y are required");
     if (mem != GABP_MEM_HOST && mem != GABP_MEM_DEVICE) return fail(h, GABP_E_INVALID, "unknown mem kind");

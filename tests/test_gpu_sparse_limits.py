@@ -133,3 +133,23 @@ def test_isolated_points_in_parallel(torch):
         s.close()
     print(f"[case] build of isolated points and of a grid: {ms} ms", flush=True)
     assert ms[0] <= ms[2 * side * (side - 1)] + 1.0, ms
+
+
+# a solve that only succeeds after it has given up what the handle held from the
+# solve before: no error message is left of its first attempt
+def test_no_message_after_a_second_attempt(torch):
+    n = 20_000
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GiB of device memory")
+    rng = np.random.default_rng(6)
+    X = torch.from_numpy((0.3 * rng.standard_normal((n, 6))).astype(np.float32)).cuda()
+    y = torch.from_numpy(np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)).cuda()
+    torch.cuda.empty_cache()
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - (16 << 30), dtype=torch.uint8, device="cuda")
+    s = gabp.GabpSVM(kernel="rbf_sparse", sparse_tau=1e-12, gamma=0.5, C=10.0, precision="mixed", tol_abs=1e30)
+    for _ in range(2):
+        assert s.solve(X, y) == gabp.OK
+        assert gabp.lib().gabp_svm_last_error(s._h) == b""
+    s.close()
+    del rest
+    torch.cuda.empty_cache()
