@@ -1109,7 +1109,11 @@ hipError_t launch_served_status(const ReqDesc* reqs, const int* slots, int nslot
 }
 
 // Above this many finalize workgroups the stop rule is a launch of its own.
-constexpr int64_t kFuseStatusMax = 512;
+// One launch less saves 1.2 us a sweep at 47 workgroups (N = 3,001: 21.6 ->
+// 20.4 us) and 0.8 at 125 (N = 8,000: 47.9 -> 47.1); the ticket that every
+// workgroup waits for before it ends costs 1.1 us more at 313 (N = 20,000:
+// 160.2 -> 161.3), 2.8 at 500 (369.2 -> 372.0) and 11 at 1,563 (3,324 -> 3,335).
+constexpr int64_t kFuseStatusMax = 256;
 
 hipError_t launch_finalize(int prec, const FinalizeArgs& f, hipStream_t s) {
     if ((f.Inv == nullptr) != (f.Mean == nullptr)) return hipErrorInvalidValue;
