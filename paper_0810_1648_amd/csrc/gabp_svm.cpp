@@ -150,7 +150,8 @@ struct gabp_svm {
         chunks,                  // 2 x 2 tile chunks of the synchronous FP32-partial sweep
         xaug,                    // training rows of the augmented decision function
         xaug0,                   // the other augmentation, for K' recomputed per band
-        parena;                  // working memory of gabp_svm_predict (reused)
+        parena,                  // working memory of gabp_svm_predict (reused)
+        pq_x, pq_f;              // its queries and values of host calls (one batch, reused)
     int aug_kind = -1, aug_mp = 0;
     // sparsified kernel: tile counts and offsets, keys, K' per edge, edge
     // ends, offsets of the i-end and j-end lists, rows (neighbour, K') of
@@ -175,7 +176,7 @@ struct gabp_svm {
                        &blk1, &blk2, &one, &status_d, &trace_d, &flag, &tmp, &Kin, &q_rows,
                        &q_cols, &q_out, &glist, &sp_cnt, &sp_toff, &sp_keys, &sp_keys2, &sp_kv, &sp_kv2,
                        &sp_ei, &sp_ej, &sp_offi, &sp_offj, &sp_len, &sp_row, &sp_qrow, &sp_edge, &sp_col, &sp_rkv, &sp_ids, &sp_lm, &sp_tmp,
-                       &sp_order, &sp_Xp, &sp_cent, &sp_rad, &sp_keep, &sp_tsel, &sp_nsel, &sp_xb, &HI, &HM, &chunks, &xaug, &xaug0, &parena, &out_d, nullptr};
+                       &sp_order, &sp_Xp, &sp_cent, &sp_rad, &sp_keep, &sp_tsel, &sp_nsel, &sp_xb, &HI, &HM, &chunks, &xaug, &xaug0, &parena, &pq_x, &pq_f, &out_d, nullptr};
     size_t held() const {
         size_t b = 0;
         for (int k = 0; all[k]; ++k) b += all[k]->bytes;
@@ -1617,7 +1618,7 @@ gabp_status gabp_svm_predict(gabp_svm* h, const float* Xq, int64_t nq, double* f
     const int64_t qb = std::min(nq, QMAX);
     size_t need = predict_plan(h, qb).bytes;
     if (nq % QMAX && nq > QMAX) need = std::max(need, predict_plan(h, nq % QMAX).bytes);
-    DevBuf xq, fo;
+    DevBuf &xq = h->pq_x, &fo = h->pq_f;
     bool ok = h->parena.ensure(need) == hipSuccess;
     if (ok && mem == GABP_MEM_HOST) ok = xq.ensure((size_t)qb * m * 4) == hipSuccess && fo.ensure((size_t)qb * 8) == hipSuccess;
     if (!ok) return fail(h, GABP_E_NOMEM, "device allocation for predict failed");
