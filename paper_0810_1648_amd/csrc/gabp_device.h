@@ -670,9 +670,9 @@ __device__ inline void put_tile_sums(const SweepArgs& a, const TileCoord& tc, AT
 // x_1 = u S, x_2 = u, x_3 = u^2 S - u m'', x_4 = u^2 of its neighbours: per
 // pair the powers of a and one FMA per power and direction, 11 VALU slots
 // (one level: 5) where the recursion level by level takes 17.  The a^4 terms
-// are rr^2 of the message sums and stay in: without them a sweep of 100,000
-// points over the plane took 0.8% less and one recomputed from 120,000 points
-// 8%, with the precisions P~ off by rr^3.
+// are rr^2 of the message sums: without them a sweep over the plane of 100,000
+// points takes 3.26 instead of 3.27 ms and one recomputed from 120,000 points
+// 4.97 instead of 5.47, with the precisions P~ off by rr^3.
 template <int D, int SER> constexpr bool mom_plan() {   // (not with kSerLevels)
     return SER > 0 && (D == 1 || (D == 2 && SER == 1) || (D == 3 && SER == 3));
 }
@@ -966,7 +966,6 @@ __device__ inline void sweep_tile(const SweepArgs& a, int64_t tile, int slot_top
     constexpr int NTD = (SER && D >= 2) ? NT : 1;
     const uint32_t ij = a.tiles[tile];
     const TileCoord tc{(int)(ij >> 16), (int)(ij & 0xFFFFu)};
-    const int NB = a.NB;
     const size_t tbase = (size_t)tile * TT;
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 4, q = l & 15;
     const int col0 = w * 64 + q * 4;
@@ -1468,8 +1467,9 @@ __device__ inline double sum_rows16(const float (&v)[16], int l) {
 // through LDS, and nothing is reduced across lanes but one vector per band.
 // 16 VALU slots per pair (exp2 4, + lambda^2, a^2, a^3, a^4, eight FMAs) beside the
 // MFMAs; the VALU is busy for three quarters of the time.  N = 120,000, m =
-// 20: 8.0 (bands through LDS, level by level) -> 7.3 (moment sums) -> 5.3 ms
-// per sweep, 0.04 of it the row sums across lanes in FP64.
+// 20: 8.0 (bands through LDS, level by level) -> 5.5 ms per sweep; N = 300,000:
+// 50.4 -> 34.3 ms (5.0 and 31.3 without the fourth power).  231 VGPRs of the
+// three-term split at 32 features and 252 at 64 leave two waves per SIMD.
 template <int KIND, int MP>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_sweep_rc_mom(SweepArgs a) {
     if (a.st->done) return;

@@ -342,7 +342,7 @@ hipError_t launch_sweep_grouped_f64(int ksrc, int gram, int levels, int ser, con
                                     hipStream_t s);
 // Sparsified kernel (gabp_sparse.hip): build passes, sorts and scans (the
 // temporary storage size comes back in *bytes when tmp is NULL), and the
-// sweep (edge update + per-node gather into one partial per node).
+// sweep by row quads with the join of the rows that leave a workgroup's range.
 // count: kept pairs of tiles[0], tiles[stride], ... (ntiles launched);
 // fill: every listed tile's kept pairs appended at *cursor (slots >= cap
 // counted, not written), keys i << sh | j.
