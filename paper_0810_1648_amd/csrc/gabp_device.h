@@ -2120,10 +2120,11 @@ inline hipError_t served_sweep(int levels, int ser, bool grouped, const ReqDesc*
 
 // Launches `kern` on `s`. With an event pair the events take the dispatch's
 // own begin and end timestamps (no marker packets around the kernel, so the
-// span is the kernel's duration alone); without, a plain launch.
+// span is the kernel's duration alone), either of which may be missing (one
+// sweep in several launches); without, a plain launch.
 template <class K, class... Args>
 inline void launch_ev(K kern, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipEvent_t e1, Args... args) {
-    if (e0)
+    if (e0 || e1)
         hipExtLaunchKernelGGL(kern, g, b, 0, s, e0, e1, 0, args...);
     else
         hipLaunchKernelGGL(kern, g, b, 0, s, args...);
@@ -2133,6 +2134,21 @@ inline void launch_ev(K kern, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipE
 
 template <class ST, class MT, class AT, int KSRC, int GK, int D, int SER>
 inline hipError_t sweep_d(bool first, const SweepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (a.ntiles * a.split > kMaxBlocks) {
+        // (only without planes: K' of so many tiles does not fit the memory)
+        if constexpr (KSRC == KSRC_RECOMPUTE && D >= 1) {
+            if (a.split != 1) return hipErrorInvalidValue;
+            return in_launches(a.ntiles, [&](int64_t o, int64_t n) {
+                SweepArgs p = a;
+                p.tiles = a.tiles + o;
+                p.ntiles = n;
+                return sweep_d<ST, MT, AT, KSRC, GK, D, SER>(first, p, s, o == 0 ? e0 : nullptr,
+                                                             o + n == a.ntiles ? e1 : nullptr);
+            });
+        } else {
+            return hipErrorInvalidValue;
+        }
+    }
     const dim3 g((unsigned)(a.ntiles * a.split)), blk(WG);
     if (a.chunk > 1) {
         if constexpr (chunk_sweep_ok<ST, MT, AT, KSRC, D, SER>()) {
@@ -2205,8 +2221,11 @@ inline hipError_t sweep_depth(int levels, bool first, int ser, const SweepArgs& 
 // ---- grouped schedule dispatch: one group visit
 template <class ST, class MT, class AT, int KSRC, int GK, int D, int SER>
 inline void grouped_d(const SweepArgs& a, const uint32_t* list, int n, int t, hipStream_t s) {
-    if (n > 0)
-        hipLaunchKernelGGL((k_sweep_dir<ST, MT, AT, KSRC, GK, D, SER>), dim3((unsigned)(n * a.split)), dim3(WG), 0, s, a, list, t);
+    (void)in_launches((int64_t)n * a.split, [&](int64_t o, int64_t m) {     // (kMaxBlocks holds whole entries)
+        hipLaunchKernelGGL((k_sweep_dir<ST, MT, AT, KSRC, GK, D, SER>), dim3((unsigned)m), dim3(WG), 0, s, a,
+                           list + o / a.split, t);
+        return hipSuccess;
+    });
 }
 
 // Stored records (levels 0): the tiles inside the group in `within` (both

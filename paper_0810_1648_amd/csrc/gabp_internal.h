@@ -81,6 +81,19 @@ gabp_status check_params(const gabp_svm_params* p, std::string& why);
 
 inline int64_t n_tiles(int NB) { return (int64_t)NB * (NB + 1) / 2; }
 
+// Workgroups (of WG threads) per launch.  A launch holds fewer than 2^32 threads
+// and silently drops the rest: 2^24 workgroups, the tiles of 1.48 M points.
+// in_launches calls f(first, count) for consecutive parts of n workgroups.
+constexpr int64_t kMaxBlocks = (int64_t)1 << 23;
+template <class F>
+inline hipError_t in_launches(int64_t n, F&& f) {
+    for (int64_t o = 0; o < n; o += kMaxBlocks) {
+        const hipError_t e = f(o, std::min(kMaxBlocks, n - o));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // Stateless plan from the contraction bound.  rr = 1.25 rho bounds
 // |A_ij| / Q_ij, the factor with which a reverse message enters the next
 // one, so unrolling `levels` levels truncates the recursion by about

@@ -990,6 +990,11 @@ hipError_t launch_fill_value(double* dst, int64_t n, double v, hipStream_t s) {
 hipError_t launch_rowsum(const void* Kp, int prec, int ksrc, const Features& F, const KernelParams& kp,
                          const uint32_t* tiles, int64_t ntiles, int NB, double* psum, double* pmax,
                          hipStream_t s) {
+    if (ntiles > kMaxBlocks && ksrc == KSRC_PLANE) return hipErrorInvalidValue;
+    if (ntiles > kMaxBlocks)
+        return in_launches(ntiles, [&](int64_t o, int64_t n) {
+            return launch_rowsum(Kp, prec, ksrc, F, kp, tiles + o, n, NB, psum, pmax, s);
+        });
     const dim3 g((unsigned)ntiles), b(WG);
     if (ksrc == KSRC_PLANE) {
         if (prec == PREC_FP64)
@@ -1013,20 +1018,28 @@ hipError_t launch_residual(const void* Kp, int prec, int ksrc, const Features& F
                            const double* alpha, const float* y, const double* Adiag, const double* rsum,
                            double* w, double* part, double* blk1, double* blk2, double* out, hipStream_t s) {
     hipLaunchKernelGGL(k_weights, dim3(grid1(NPAD)), dim3(WG), 0, s, N, NPAD, alpha, y, w);
-    const dim3 g((unsigned)ntiles), b(WG);
+    if (ntiles > kMaxBlocks && ksrc == KSRC_PLANE) return hipErrorInvalidValue;
+    const dim3 b(WG);
     if (ksrc == KSRC_PLANE) {
+        const dim3 g((unsigned)ntiles);
         if (prec == PREC_FP64)
             hipLaunchKernelGGL((k_apply<double, KSRC_PLANE, GRAM_F64>), g, b, 0, s, (const double*)Kp, F, kp, tiles, NB, w, part);
         else
             hipLaunchKernelGGL((k_apply<float, KSRC_PLANE, GRAM_F32>), g, b, 0, s, (const float*)Kp, F, kp, tiles, NB, w, part);
     } else {
-        switch (F.kind) {
-            case GRAM_F32: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_F32>), g, b, 0, s, nullptr, F, kp, tiles, NB, w, part); break;
-            case GRAM_BF16: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_BF16>), g, b, 0, s, nullptr, F, kp, tiles, NB, w, part); break;
-            case GRAM_BF16X3: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_BF16X3>), g, b, 0, s, nullptr, F, kp, tiles, NB, w, part); break;
-            case GRAM_BF16X6: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_BF16X6>), g, b, 0, s, nullptr, F, kp, tiles, NB, w, part); break;
-            default: return hipErrorInvalidValue;
-        }
+        const hipError_t e = in_launches(ntiles, [&](int64_t o, int64_t n) {
+            const dim3 g((unsigned)n);
+            const uint32_t* t = tiles + o;
+            switch (F.kind) {
+                case GRAM_F32: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_F32>), g, b, 0, s, nullptr, F, kp, t, NB, w, part); break;
+                case GRAM_BF16: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_BF16>), g, b, 0, s, nullptr, F, kp, t, NB, w, part); break;
+                case GRAM_BF16X3: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_BF16X3>), g, b, 0, s, nullptr, F, kp, t, NB, w, part); break;
+                case GRAM_BF16X6: hipLaunchKernelGGL((k_apply<float, KSRC_RECOMPUTE, GRAM_BF16X6>), g, b, 0, s, nullptr, F, kp, t, NB, w, part); break;
+                default: return hipErrorInvalidValue;
+            }
+            return hipGetLastError();
+        });
+        if (e != hipSuccess) return e;
     }
     const unsigned nb = grid1(N);
     hipLaunchKernelGGL(k_residual_blocks, dim3(nb), dim3(WG), 0, s, N, NB, part, Adiag, rsum, alpha, y, blk1, blk2);

@@ -756,17 +756,20 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + WG - 1) / WG); }
 
 hipError_t launch_sp_count(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles,
                            int64_t stride, int64_t N, float cut, int64_t* counts, hipStream_t s) {
-    if (ntiles <= 0) return hipSuccess;
-    return sp_build(false, FA, FB, tiles, ntiles, stride, N, cut, 0.0f, 0.0f, counts, 0, nullptr, 0, nullptr,
-                    nullptr, s);
+    return in_launches(ntiles, [&](int64_t o, int64_t n) {
+        return sp_build(false, FA, FB, tiles + o * stride, n, stride, N, cut, 0.0f, 0.0f, counts + o, 0, nullptr, 0,
+                        nullptr, nullptr, s);
+    });
 }
 
 hipError_t launch_sp_fill(const Features& FA, const Features& FB, const uint32_t* tiles, int64_t ntiles, int64_t N,
                           float cut, float neg_gamma_log2e, float lam2, int64_t cap, unsigned long long* cursor, int sh,
                           uint64_t* keys, float* kv, hipStream_t s) {
-    if (ntiles <= 0) return hipSuccess;
-    return sp_build(true, FA, FB, tiles, ntiles, 1, N, cut, neg_gamma_log2e, lam2, nullptr, cap, cursor, sh, keys, kv,
-                    s);
+    // (kMaxBlocks tiles at a time, whose workgroups take SP_TPW each)
+    return in_launches(ntiles, [&](int64_t o, int64_t n) {
+        return sp_build(true, FA, FB, tiles + o, n, 1, N, cut, neg_gamma_log2e, lam2, nullptr, cap, cursor, sh, keys,
+                        kv, s);
+    });
 }
 
 hipError_t launch_sp_augment(int64_t NPAD, int64_t m, int m_pad, int kind, const float* nrm, float* f32a,
